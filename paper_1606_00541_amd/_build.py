@@ -20,8 +20,23 @@ ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
 HIPCC = os.path.join(ROCM, "bin", "hipcc")
 
 HOST_SRCS = ["analysis.cpp", "factor.cpp"]
-HIP_SRCS = ["tri_kernels.hip", "krylov.hip", "refactor.hip", "capi.hip"]
-HEADERS = ["hec_host.h", "hec_dev.h"]
+HIP_SRCS = ["tri_kernels.hip", "krylov.hip", "refactor.hip", "capi.hip", "dataflow_inst.hip"]
+HEADERS = ["hec_host.h", "hec_dev.h", "tri_dev.h", "dataflow.h"]
+
+
+def _hip_units():
+    """(source, object name, defines) of every HIP compilation: the dataflow
+    kernels' instances are one source compiled per value type, right-hand-side
+    form and clock trace, side by side."""
+    units = [(f, f + ".o", []) for f in HIP_SRCS if f != "dataflow_inst.hip"]
+    for t, typ in (("f64", "double"), ("f32", "float")):
+        for r, one in (("one", "true"), ("many", "false")):
+            for s, trace in (("", "false"), ("_tr", "true")):
+                name = "df_%s_%s%s" % (t, r, s)
+                units.append(("dataflow_inst.hip", name + ".o",
+                              ["-DHEC_DF_T=" + typ, "-DHEC_DF_R1=" + one, "-DHEC_DF_TRACE=" + trace,
+                               "-DHEC_DF_NAME=" + name]))
+    return units
 
 COMMON = ["-O3", "-fPIC", "-std=c++17", "-Wall", "-I" + os.path.join(ROOT, "include"), "-I" + CSRC]
 HOST_FLAGS = COMMON + ["-ffp-contract=off", "-D__HIP_PLATFORM_AMD__", "-I" + os.path.join(ROCM, "include")]
@@ -61,10 +76,10 @@ def build(force: bool = True, verbose: bool = False, incremental: bool = False) 
         if not incremental or _stale(os.path.join(CSRC, f), o):
             jobs.append(["g++"] + HOST_FLAGS + ["-c", os.path.join(CSRC, f), "-o", o])
         objs.append(o)
-    for f in HIP_SRCS:
-        o = os.path.join(BUILD, f + ".o")
+    for f, name, defs in _hip_units():
+        o = os.path.join(BUILD, name)
         if not incremental or _stale(os.path.join(CSRC, f), o):
-            jobs.append([HIPCC] + HIP_FLAGS + ["-c", os.path.join(CSRC, f), "-o", o])
+            jobs.append([HIPCC] + HIP_FLAGS + defs + ["-c", os.path.join(CSRC, f), "-o", o])
         objs.append(o)
     procs = [(j, subprocess.Popen(j, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)) for j in jobs]
     failed = []

@@ -583,7 +583,14 @@ int32_t dataflow_max_block(int32_t /*w*/) { return 512; }
 size_t dataflow_lds_bytes(int32_t rows, int32_t ints, int32_t R, size_t tsize)
 {
     const size_t vals = (size_t)rows * R * tsize;
-    return ((vals + 15) & ~(size_t)15) + (((size_t)ints * 4 + 15) & ~(size_t)15);
+    return ((vals + 15) & ~(size_t)15) + (((size_t)ints * 4 + 15) & ~(size_t)15) + kDataflowCtlBytes;
+}
+
+DataflowRecord::DataflowRecord(int32_t w_, int32_t ld_, int32_t tsize_) : w(w_), ld(ld_), tsize(tsize_)
+{
+    const int32_t nb = w * (tsize / 4) + (w + 1) / 2;
+    chunks = nb / 4 + (nb % 4 == 3 ? 1 : 0);
+    rest = nb % 4 == 3 ? 0 : nb % 4;
 }
 
 namespace {
@@ -652,7 +659,7 @@ void make_dataflow(Schedule &s, ExecHost &ex, const std::vector<int32_t> &xlev,
         s.max_imp = std::max(s.max_imp, ni);
         s.df_rows = std::max(s.df_rows, 2 * (s.window[2 * g + 1] - s.window[2 * g]) + ni + 1);
         s.df_ints = std::max(s.df_ints, ni + (s.exp_ptr[g + 1] - s.exp_ptr[g]) +
-                                            2 * (s.step_ptr[g + 1] - s.step_ptr[g]));
+                                            (s.step_ptr[g + 1] - s.step_ptr[g]) + kDataflowPad);
         // 3. columns become rows of the group's LDS value area: its own rows
         // 0..win-1, imports from 2*win (after the right-hand-side copy), and a
         // zero row 2*win + nimp for ELL padding (padding then subtracts 0 * 0,
@@ -679,6 +686,12 @@ void make_dataflow(Schedule &s, ExecHost &ex, const std::vector<int32_t> &xlev,
         if (k != ns) fail(HEC_ERR_INVALID_ARG, "internal: wavefront pieces out of order");
     }
     s.wave_ptr[(size_t)G * waves] = s.step_ptr[G];
+    // 5. step descriptors (a step has 1..64 rows, a window fewer than 2^16)
+    s.step_pack.resize((size_t)s.nsteps());
+    for (int32_t g = 0; g < G; ++g)
+        for (int32_t q = s.step_ptr[g]; q < s.step_ptr[g + 1]; ++q)
+            s.step_pack[q] = (s.step_row[2 * q] - s.window[2 * g]) |
+                             (s.step_row[2 * q + 1] - s.step_row[2 * q] - 1) * 16 << 16;
     s.dataflow = true;
 }
 
@@ -1099,8 +1112,8 @@ void build_exec(TriHost &t, const Csr &a, const Tune &tune, const DeviceShape &d
     if (want_df && dataflow_width(w) != w)
         fail(HEC_ERR_INVALID_ARG, "dataflow kernel: ELL width must be 1..8, 10, 12 or 16");
     if (want_df && R > 64) fail(HEC_ERR_INVALID_ARG, "dataflow kernel: max_nrhs above 64");
-    if (want_df && (size_t)w * ld * 8 > (size_t)INT32_MAX)
-        fail(HEC_ERR_CAPACITY, "dataflow kernel: ELL part beyond 2 GiB (32-bit buffer offsets)");
+    if (want_df && DataflowRecord(w, ld, t.dt == HEC_F64 ? 8 : 4).bytes() > (size_t)UINT32_MAX)
+        fail(HEC_ERR_CAPACITY, "dataflow kernel: ELL part beyond 4 GiB (32-bit buffer offsets)");
     if (want_df && tune.block_threads > dataflow_max_block(w) - 128)
         fail(HEC_ERR_CAPACITY, "dataflow kernel: block_threads above " + std::to_string(dataflow_max_block(w) - 128) +
                                    " for ELL width " + std::to_string(w) + " (two more wavefronts are added)");

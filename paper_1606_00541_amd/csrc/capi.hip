@@ -94,8 +94,31 @@ void upload_tri(DevTri &d, const TriHost &t, int32_t max_nrhs)
     d.kind = ex.sched.kind;
     d.unit = t.unit;
     d.has_tail = !ex.tail_ptr.empty();
-    upload(d.ell_col, ex.ell_col);
-    upload_values(d.ell_val, ex.ell_val, t.dt);
+    if (ex.sched.dataflow) {
+        // one record per row: values and 16-bit columns together
+        const DataflowRecord rec(ex.w, ex.ld, (int32_t)vsize(t.dt));
+        std::vector<unsigned char> buf(rec.bytes(), 0);
+        for (int32_t e = 0; e < ex.w; ++e) {
+            const int32_t dv = rec.value_dword(e), dc = rec.column_dword(e);
+            unsigned char *pv = buf.data() + rec.first(dv), *pc = buf.data() + rec.first(dc) + 2 * (e & 1);
+            const size_t sv = rec.stride(dv), sc = rec.stride(dc);
+            const double *v = ex.ell_val.data() + (size_t)e * ex.ld;
+            const int32_t *c = ex.ell_col.data() + (size_t)e * ex.ld;
+            for (int32_t x = 0; x < ex.n; ++x, pv += sv, pc += sc) {
+                if (t.dt == HEC_F64) std::memcpy(pv, v + x, 8);
+                else {
+                    const float f = (float)v[x];
+                    std::memcpy(pv, &f, 4);
+                }
+                const uint16_t col = (uint16_t)c[x];
+                std::memcpy(pc, &col, 2);
+            }
+        }
+        upload(d.ell_val, buf);
+    } else {
+        upload(d.ell_col, ex.ell_col);
+        upload_values(d.ell_val, ex.ell_val, t.dt);
+    }
     if (d.has_tail) {
         upload(d.tail_ptr, ex.tail_ptr);
         upload(d.tail_col, ex.tail_col);
@@ -136,6 +159,7 @@ void upload_tri(DevTri &d, const TriHost &t, int32_t max_nrhs)
             d.df_waves = s.df_waves;
             d.queue = s.queue;
             upload(d.wave_ptr, s.wave_ptr);
+            upload(d.step_pack, s.step_pack);
             d.df_step_rows = 0;
             for (int32_t q = 0; q < s.nsteps(); ++q)
                 d.df_step_rows = std::max(d.df_step_rows, s.step_row[2 * q + 1] - s.step_row[2 * q]);
@@ -428,8 +452,10 @@ void build_refactor(ilu_s &f, const int32_t *rowptr, const int32_t *col)
         }
     }
     // plan positions: the off-diagonals of a row keep their order in both layouts
-    auto place = [](const ExecHost &ex, int32_t x, int32_t e) {
-        return e < ex.w ? e * ex.ld + x : -1 - (ex.tail_ptr[x] + (e - ex.w));
+    auto place = [&f](const ExecHost &ex, int32_t x, int32_t e) -> int32_t {
+        if (e >= ex.w) return -1 - (ex.tail_ptr[x] + (e - ex.w));
+        if (ex.sched.dataflow) return (int32_t)DataflowRecord(ex.w, ex.ld, (int32_t)vsize(f.fdt)).value(x, e);
+        return e * ex.ld + x;
     };
     std::vector<int32_t> l_src, l_dst, u_src, u_dst, u_diag, d_src(n);
     const ExecHost &el = f.L.h.ex, &eu = f.U.h.ex;

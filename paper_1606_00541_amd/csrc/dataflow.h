@@ -1,0 +1,587 @@
+// Dataflow owner kernel: one launch per triangle, no per-level barrier.
+//
+// A workgroup owns a part of the rows (a contiguous device-row window) and
+// runs three kinds of wavefronts:
+//   compute waves  walk their own contiguous pieces of the part in level
+//                  order, a step (at most 64 (row, rhs) items of one level)
+//                  at a time, one item per lane.  Each dependency is read
+//                  from LDS and re-read until it no longer holds the
+//                  sentinel, so a row starts as soon as its own inputs exist.
+//                  Compute waves issue no global stores, so their waits cover
+//                  loads only.
+//   import wave    polls the mailbox slots this group reads (lane l takes
+//                  imports l, l+64, ... in order of first use) and copies
+//                  each value into LDS when it arrives;
+//   export wave    watches the group's exported rows in LDS and writes each
+//                  one to its mailbox slot as soon as it is solved.
+// Any row waits only on rows of lower levels, and every wave handles its
+// items in level order, so the row of lowest level not yet solved can always
+// proceed: the grid drains as long as all workgroups are co-resident.
+// The summation order (ELL slots, then the CSR tail, on a right-hand side
+// scaled by the reciprocal diagonal) is the one of k_level, so results are
+// bit-identical to it.
+//
+// What bounds it: the chain of levels.  A step is LDS write -> LDS read ->
+// multiply-adds -> test (measured on one wavefront: 96 cycles for write, three
+// reads and three FP64 multiply-adds, 20 more for the test), and a wavefront
+// alone on its SIMD issues an instruction every 4-5 cycles, so every
+// instruction of a step costs time although the unit it uses is idle.  Hence
+// a row is one packed record (2 loads instead of 6 for three FP64 entries),
+// LDS addresses start at 0 and are formed by one multiply-add from 16-bit
+// columns before they are needed, a step's descriptor is a broadcast LDS read
+// (decoding it with v_readlane and scalar instructions cost 40 cycles a step)
+// and the polling code is out of line.  Against one 32-bit column and one
+// value load per entry with the columns converted after the previous step:
+// 64^2 ILU(0) 115.6 -> 106.2 us per L+U, 128^3 331.7 -> 309.8 us (FP64,
+// three factors in turn), 100^3 ILUT(1e-3, 10) FP32 1910 -> 1395 us.
+#pragma once
+
+#include "tri_dev.h"
+
+namespace hec {
+
+template <typename T> __device__ __forceinline__ T lds_get(const T *p)
+{
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+template <typename T> __device__ __forceinline__ void lds_put(T *p, T v)
+{
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// A value of the LDS value area by its byte offset.  The kernels of this file
+// have no static LDS, so their dynamic LDS, which starts with the value area,
+// starts at LDS address 0 (checked at launch): an offset is an address, with
+// no base to add on the dependency chain.
+template <typename T> using LdsPtr = __attribute__((address_space(3))) T *;
+template <typename T> __device__ __forceinline__ T lds_at(unsigned off)
+{
+    return __hip_atomic_load((LdsPtr<T>)(uintptr_t)off, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+template <typename T> __device__ __forceinline__ void lds_set(unsigned off, T v)
+{
+    __hip_atomic_store((LdsPtr<T>)(uintptr_t)off, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// A row as the kernel loads it: W values, then W 16-bit LDS value rows (own
+// rows, imports, the zero row of ELL padding), in 16-byte chunks and a
+// remainder of 0..2 dwords, each chunk an array over the rows.  Three
+// dwords are padded to a chunk.  (dataflow_record on the host.)
+template <typename T, int W> struct DfRec {
+    static constexpr int V = W * (int)sizeof(T) / 4;  // dwords of values
+    static constexpr int NB = V + (W + 1) / 2;
+    static constexpr int CH = NB / 4 + (NB % 4 == 3 ? 1 : 0);
+    static constexpr int RE = NB % 4 == 3 ? 0 : NB % 4;
+    static constexpr int ND = 4 * CH + RE;
+    static constexpr int LOADS = CH + (RE > 0 ? 1 : 0);
+    // register sets in rotation: as many as the vector-memory counter (63
+    // outstanding loads) and about 144 registers hold, at most 16
+    static constexpr int byreg = 144 / ND < 3 ? 3 : 144 / ND;
+    static constexpr int bycnt = 60 / LOADS + 1;
+    static constexpr int k0 = byreg < bycnt ? byreg : bycnt;
+    static constexpr int K = k0 < 16 ? k0 : 16;
+    static_assert(K <= kDataflowPad, "descriptors are read K steps ahead");
+};
+
+template <int ND> struct DfSet {
+    uint32_t d[ND];
+};
+
+template <typename T, int W> __device__ __forceinline__ T df_val(const DfSet<DfRec<T, W>::ND> &u, int e)
+{
+    if constexpr (sizeof(T) == 8)
+        return __builtin_bit_cast(T, (unsigned long long)u.d[2 * e] | ((unsigned long long)u.d[2 * e + 1] << 32));
+    else
+        return __builtin_bit_cast(T, u.d[e]);
+}
+// LDS byte offset of ELL slot e: its value row times the bytes of a row, plus
+// the lane's right-hand side.  One multiply-add on a half of the packed dword.
+template <typename T, int W, bool R1>
+__device__ __forceinline__ unsigned df_off(const DfSet<DfRec<T, W>::ND> &u, int e, unsigned rowbytes, unsigned kbytes)
+{
+    const unsigned d = u.d[DfRec<T, W>::V + e / 2];
+    unsigned r;
+    if constexpr (R1 && sizeof(T) == 8) {
+        if (e & 1) asm volatile("v_mad_u32_u16 %0, %1, 8, 0 op_sel:[1,0,0,0]" : "=v"(r) : "v"(d));
+        else asm volatile("v_mad_u32_u16 %0, %1, 8, 0" : "=v"(r) : "v"(d));
+    } else if constexpr (R1) {
+        if (e & 1) asm volatile("v_mad_u32_u16 %0, %1, 4, 0 op_sel:[1,0,0,0]" : "=v"(r) : "v"(d));
+        else asm volatile("v_mad_u32_u16 %0, %1, 4, 0" : "=v"(r) : "v"(d));
+    } else {
+        if (e & 1) asm volatile("v_mad_u32_u16 %0, %1, %2, %3 op_sel:[1,0,0,0]" : "=v"(r) : "v"(d), "s"(rowbytes), "v"(kbytes));
+        else asm volatile("v_mad_u32_u16 %0, %1, %2, %3" : "=v"(r) : "v"(d), "s"(rowbytes), "v"(kbytes));
+    }
+    return r;
+}
+
+// A workgroup's part of one triangle and its place in LDS: x [win][R], b
+// [win][R], imports [nimp][R], one zero row (the target of ELL padding), then
+// import slots, export rows (window offsets) and step descriptors (first
+// window row | 16 (number of rows - 1) << 16) with kDataflowPad zeros behind.
+template <typename T> struct DfPart {
+    int g, lo, win, i0, nimp, e0, nex, s0, ns;
+    T *xl, *bl, *im;
+    int *isl, *erl, *stl;
+    unsigned long long *ltr;
+};
+
+template <typename T> __device__ __forceinline__ DfPart<T> df_part(const TriArgs &a, int g, int R, unsigned char *smem)
+{
+    DfPart<T> p;
+    p.g = g;
+    p.lo = a.window[2 * g];
+    p.win = a.window[2 * g + 1] - p.lo;
+    p.i0 = a.imp_ptr[g];
+    p.nimp = a.imp_ptr[g + 1] - p.i0;
+    p.e0 = a.exp_ptr[g];
+    p.nex = a.exp_ptr[g + 1] - p.e0;
+    p.s0 = a.step_ptr[g];
+    p.ns = a.step_ptr[g + 1] - p.s0;
+    p.xl = reinterpret_cast<T *>(smem);
+    p.bl = p.xl + (size_t)p.win * R;
+    p.im = p.bl + (size_t)p.win * R;
+    const size_t ib = (((size_t)2 * p.win + p.nimp + 1) * R * sizeof(T) + 15) & ~(size_t)15;
+    p.isl = reinterpret_cast<int *>(smem + ib);
+    p.erl = p.isl + p.nimp;
+    p.stl = p.erl + p.nex;
+    // when tracing: 2*ns clocks after the ints, at an 8-byte boundary
+    p.ltr = reinterpret_cast<unsigned long long *>(smem + ((ib + (size_t)(p.nimp + p.nex + p.ns + kDataflowPad) * 4 + 7) & ~(size_t)7));
+    return p;
+}
+
+// LDS words all wavefronts share, behind everything else (the value area
+// starts at LDS address 0, so that a value's address is its row times a
+// constant).
+struct DfCtl {
+    unsigned epoch;
+    int abort, part, pad;
+};
+
+constexpr int kDfFill = 8;  // independent loads a thread keeps in flight while LDS is filled
+
+__device__ __forceinline__ void df_copy_ints(int *dst, const int32_t *src, int count, int add)
+{
+    const int nt = blockDim.x;
+    for (int t0 = threadIdx.x; t0 < count; t0 += kDfFill * nt) {
+        int v[kDfFill];
+#pragma unroll
+        for (int u = 0; u < kDfFill; ++u) v[u] = src[min(t0 + u * nt, count - 1)];
+#pragma unroll
+        for (int u = 0; u < kDfFill; ++u)
+            if (t0 + u * nt < count) dst[t0 + u * nt] = v[u] + add;
+    }
+}
+
+// Everything but the right-hand side: sentinels, the zero row, index lists,
+// and this part's slots of the mailbox's other half for the next launch.
+template <typename T> __device__ __forceinline__ void df_fill_lists(const TriArgs &a, const DfPart<T> &p, int R, T *other)
+{
+    const int tid = threadIdx.x, nt = blockDim.x;
+    for (int t = tid; t < p.win * R; t += nt) p.xl[t] = sentinel<T>();
+    for (int t = tid; t < (p.nimp + 1) * R; t += nt) p.im[t] = t < p.nimp * R ? sentinel<T>() : T(0);
+    df_copy_ints(p.isl, a.imp_slot + p.i0, p.nimp, 0);
+    df_copy_ints(p.erl, a.exp_row + p.e0, p.nex, -p.lo);
+    df_copy_ints(p.stl, a.step_pack + p.s0, p.ns, 0);
+    if (tid < kDataflowPad) p.stl[p.ns + tid] = 0;
+    if (a.nexp > 0) {
+        const size_t m0 = (size_t)p.e0 * a.mbox_stride, m1 = (size_t)(p.e0 + p.nex) * a.mbox_stride;
+        for (size_t i = m0 + tid; i < m1; i += nt) other[i] = sentinel<T>();
+    }
+}
+
+// The right-hand side, gathered and scaled.  The gather indices of a round
+// are loaded while the values of the round before are in flight.
+template <typename T, bool UNIT, bool R1, typename TIn>
+__device__ __forceinline__ void df_fill_b(const TriArgs &a, const DfPart<T> &p, int R, const TIn *bin)
+{
+    const int tid = threadIdx.x, nt = blockDim.x, cnt = p.win * R;
+    int gi[kDfFill];
+    T dd[kDfFill];
+    auto index = [&](int t0) {
+#pragma unroll
+        for (int u = 0; u < kDfFill; ++u) {
+            const int t = min(t0 + u * nt, cnt - 1);
+            gi[u] = a.gather[p.lo + (R1 ? t : t / R)];
+        }
+    };
+    if (tid < cnt) index(tid);
+    for (int t0 = tid; t0 < cnt; t0 += kDfFill * nt) {
+        TIn bv[kDfFill];
+#pragma unroll
+        for (int u = 0; u < kDfFill; ++u) {
+            const int t = min(t0 + u * nt, cnt - 1);
+            bv[u] = bin[(size_t)gi[u] * R + (R1 ? 0 : t % R)];
+            if (!UNIT) dd[u] = static_cast<const T *>(a.dinv)[p.lo + (R1 ? t : t / R)];
+        }
+        if (t0 + kDfFill * nt < cnt) index(t0 + kDfFill * nt);
+#pragma unroll
+        for (int u = 0; u < kDfFill; ++u) {
+            T v = canon(static_cast<T>(bv[u]));
+            if (!UNIT) v = scale_rhs(v, dd[u]);
+            if (t0 + u * nt < cnt) p.bl[t0 + u * nt] = v;
+        }
+    }
+}
+
+// One part of one triangle, from filled LDS to solved LDS.  `fill` puts the
+// part's right-hand side and lists into LDS; the compute wavefronts issue
+// their first matrix loads before it.
+template <typename T, int W, bool TAIL, bool R1, bool TRACE, typename Fill>
+__device__ __forceinline__ void df_sweep(const TriArgs &a, const DfPart<T> &pt, int R, T *mrd, int *s_abort,
+                                         unsigned long long &t_fill, Fill fill)
+{
+    using Rec = DfRec<T, W>;
+    constexpr int K = Rec::K;
+    const int tid = threadIdx.x, nt = blockDim.x;
+    const int lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int nwc = (nt >> 6) - 2;
+    const int lo = pt.lo;
+    T *xl = pt.xl;
+    // the lane's row and right-hand side within any step (lanes past a
+    // step's rows repeat its last row)
+    const unsigned q0 = R1 ? lane : lane / R;
+    const unsigned q16 = q0 * 16u;
+    const unsigned rowb = (R1 ? 1u : (unsigned)R) * (unsigned)sizeof(T);
+    const unsigned kb = R1 ? 0u : (lane - q0 * R) * (unsigned)sizeof(T);
+    const unsigned bofs = (unsigned)(reinterpret_cast<unsigned char *>(pt.bl) - reinterpret_cast<unsigned char *>(xl));
+    const unsigned long long nbytes = (unsigned long long)Rec::ND * 4u * (unsigned)a.ld;
+    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<void *>(a.ell_val), 0, (int)(unsigned)(nbytes > 0xffffffffull ? 0xffffffffull : nbytes), 0x00020000);
+    // the part's rows begin at lo: chunk c of its row r is 16 bytes at
+    // (lo + c * ld + r) * 16, the remainder behind all chunks
+    const unsigned ld = (unsigned)a.ld, base = (unsigned)lo * 16u, rbase = Rec::CH * ld * 16u + (unsigned)lo * (Rec::RE * 4u);
+    DfSet<Rec::ND> S[K];
+    unsigned xo[K];  // LDS byte offset of the item's value
+    // Loads of the step with descriptor dsc into set i.  All of it is vector
+    // work on a descriptor every lane holds: no scalar register is written by
+    // a vector instruction, which would cost wait states before its use.
+    auto load = [&](int i, unsigned dsc) {
+        DfSet<Rec::ND> &u = S[i];
+        unsigned vo;
+        asm("v_mad_u32_u16 %0, %1, 16, %2" : "=v"(vo) : "v"(dsc), "v"(min(q16, dsc >> 16)));
+#pragma unroll
+        for (int c = 0; c < Rec::CH; ++c) {
+            auto v = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)vo, (int)(base + c * ld * 16u), 0);
+            u.d[4 * c] = v[0];
+            u.d[4 * c + 1] = v[1];
+            u.d[4 * c + 2] = v[2];
+            u.d[4 * c + 3] = v[3];
+        }
+        if constexpr (Rec::RE == 1) u.d[4 * Rec::CH] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, (int)(vo / 4u), (int)rbase, 0);
+        if constexpr (Rec::RE == 2) {
+            auto v = __builtin_amdgcn_raw_buffer_load_b64(rsrc, (int)(vo / 2u), (int)rbase, 0);
+            u.d[4 * Rec::CH] = v[0];
+            u.d[4 * Rec::CH + 1] = v[1];
+        }
+        xo[i] = R1 ? vo / (16u / (unsigned)sizeof(T)) : (vo / 16u) * rowb + kb;
+        asm volatile("" : "+v"(xo[i]));  // here, not on the dependency chain
+    };
+    int j = 0, jend = 0;
+    if (wv < nwc) {
+        j = a.wave_ptr[pt.g * nwc + wv] - pt.s0;
+        jend = a.wave_ptr[pt.g * nwc + wv + 1] - pt.s0;
+        if (j < jend) {
+            const int tab = a.step_pack[pt.s0 + min(j + lane, jend - 1)];
+#pragma unroll
+            for (int p = 0; p < K - 1; ++p) {
+                load(p, (unsigned)__builtin_amdgcn_readlane(tab, p));
+                // in order: the first wait of the loop then covers one set
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    }
+    fill();
+    __syncthreads();
+    t_fill = TRACE ? __builtin_amdgcn_s_memrealtime() : 0ull;
+
+    if (wv < nwc) {
+        const T *tv = static_cast<const T *>(a.tail_val);
+        const int ntr = TRACE ? min(pt.ns, a.trace_stride - 1) : 0;
+        bool aborted = false;
+        T bv[K], dep[W];
+        unsigned dsc = 0;  // descriptor of the step whose loads are issued next
+        unsigned stp = 0;  // LDS address of descriptor j
+        unsigned on[W];  // LDS byte offsets of the next step's inputs
+        auto rhs = [&](int i) { bv[i] = *(LdsPtr<T>)(uintptr_t)(xo[i] + bofs); };
+        auto offsets = [&](const DfSet<Rec::ND> &u) {
+#pragma unroll
+            for (int e = 0; e < W; ++e) on[e] = df_off<T, W, R1>(u, e, rowb, kb);
+        };
+        auto read = [&](const unsigned *o) {
+#pragma unroll
+            for (int e = 0; e < W; ++e) dep[e] = lds_at<T>(o[e]);
+        };
+        auto step = [&](int p, bool more) {  // more: also issue the loads of step p + K - 1
+            const DfSet<Rec::ND> &u = S[p];
+            if (TRACE && j + p < ntr && lane == 0) pt.ltr[2 * (j + p)] = __builtin_amdgcn_s_memrealtime();
+            if (more) {
+                load((p + K - 1) % K, dsc);
+                dsc = *(LdsPtr<unsigned>)(uintptr_t)(stp + 4u * (unsigned)(p + K));
+            }
+            rhs((p + 2) % K);
+            offsets(S[(p + 1) % K]);
+            __builtin_amdgcn_sched_barrier(0);
+            T acc = bv[p];
+#pragma unroll
+            for (int e = 0; e < W; ++e) acc -= df_val<T, W>(u, e) * dep[e];
+            if (__builtin_expect(__ballot(acc != acc) != 0, 0)) {
+                bool pend = false;
+                unsigned oc[W];
+#pragma unroll
+                for (int e = 0; e < W; ++e) oc[e] = df_off<T, W, R1>(u, e, rowb, kb);
+#pragma unroll
+                for (int e = 0; e < W; ++e) pend |= is_sentinel(dep[e]);
+                unsigned spins = 0;
+                while (pend) {
+                    read(oc);
+                    pend = false;
+#pragma unroll
+                    for (int e = 0; e < W; ++e) pend |= is_sentinel(dep[e]);
+                    if (pend && (++spins & 63u) == 0) {
+                        if (lds_get(s_abort)) {
+                            aborted = true;
+                            break;
+                        }
+                        if (spins > (a.spin << 4)) {
+                            lds_put(s_abort, 2);
+                            aborted = true;
+                            break;
+                        }
+                    }
+                }
+                acc = bv[p];
+#pragma unroll
+                for (int e = 0; e < W; ++e) acc -= df_val<T, W>(u, e) * dep[e];
+            }
+            if (TAIL) {
+                const unsigned x = lo + (R1 ? xo[p] / (unsigned)sizeof(T) : (xo[p] - kb) / rowb);
+                for (int t = a.tail_ptr[x]; t < a.tail_ptr[x + 1]; ++t) {
+                    const unsigned o = (unsigned)a.tail_col[t] * rowb + kb;
+                    T dd = lds_at<T>(o);
+                    unsigned sp = 0;
+                    while (is_sentinel(dd)) {
+                        dd = lds_at<T>(o);
+                        if ((++sp & 63u) == 0) {
+                            if (lds_get(s_abort)) {
+                                aborted = true;
+                                break;
+                            }
+                            if (sp > (a.spin << 4)) {
+                                lds_put(s_abort, 2);
+                                aborted = true;
+                                break;
+                            }
+                        }
+                    }
+                    acc -= tv[t] * dd;
+                }
+            }
+            lds_set(xo[p], acc);
+            read(on);
+            __builtin_amdgcn_sched_barrier(0);
+            if (TRACE && j + p < ntr && lane == 0) pt.ltr[2 * (j + p) + 1] = __builtin_amdgcn_s_memrealtime();
+        };
+        if (j < jend) {
+            stp = (unsigned)(uintptr_t)(LdsPtr<int>)(pt.stl + j);
+            asm volatile("" : "+v"(stp));
+            dsc = *(LdsPtr<unsigned>)(uintptr_t)(stp + 4u * (unsigned)(K - 1));
+            // the first sets have arrived (vmcnt 0, other counters as they
+            // are): the loop's waits then count its own loads only
+            __builtin_amdgcn_s_waitcnt(0x0f70);
+            rhs(0);
+            rhs(1);
+            offsets(S[0]);
+            read(on);
+            const int rounds = (jend - j) / K, rest = (jend - j) - K * rounds;
+            for (int q = 0; q < rounds; ++q) {
+#pragma unroll
+                for (int p = 0; p < K; ++p) step(p, true);
+                if (__ballot(aborted) != 0) break;
+                j += K;
+                stp += 4u * K;
+            }
+#pragma unroll
+            for (int p = 0; p < K - 1; ++p)
+                if (rest > p && __ballot(aborted) == 0) step(p, false);
+        }
+    } else if (wv == nwc) {
+        // import wave: lane l owns items l, l+64, l+128, ... (level order).
+        // Each poll round reads those of the lane's next kLook items that have
+        // not arrived yet, copies every new arrival into LDS, and moves the
+        // lane past the delivered prefix.  One round trip thus delivers
+        // several levels' worth of a lane's items without re-reading any.
+        constexpr int kLook = 2;
+        const int items = pt.nimp * R;
+        const int xoff = 2 * pt.win * R;
+        int it = lane;
+        unsigned got = 0;  // bit u: item it + 64 u already delivered
+        unsigned idle = 0;
+        while (__ballot(it < items) != 0) {
+            if (it < items) {
+                T v[kLook];
+#pragma unroll
+                for (int u = 0; u < kLook; ++u) {
+                    const int i2 = it + 64 * u;
+                    v[u] = sentinel<T>();
+                    if (i2 < items && !((got >> u) & 1u)) {
+                        const int q = R1 ? i2 : i2 / R, k = R1 ? 0 : i2 - q * R;
+                        v[u] = __hip_atomic_load(mrd + (size_t)pt.isl[q] * a.mbox_stride + k, __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_AGENT);
+                    }
+                }
+                bool fresh = false;
+#pragma unroll
+                for (int u = 0; u < kLook; ++u) {
+                    if (!is_sentinel(v[u])) {
+                        lds_put(xl + xoff + it + 64 * u, v[u]);
+                        got |= 1u << u;
+                        fresh = true;
+                    }
+                }
+                while (got & 1u) {
+                    got >>= 1;
+                    it += 64;
+                }
+                if (fresh) {
+                    idle = 0;
+                } else if (++idle > a.spin) {
+                    lds_put(s_abort, 2);
+                    it = items;
+                } else if ((idle & 255u) == 0 &&
+                           __hip_atomic_load(a.err_dev, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
+                    lds_put(s_abort, 1);  // another workgroup gave up
+                    it = items;
+                }
+            }
+            if (lds_get(s_abort)) break;
+        }
+    } else {
+        // export wave: each lane watches its next exported item; a round in
+        // which no lane found a new value sleeps briefly, so the wave does
+        // not take issue slots and LDS bandwidth from the compute waves
+        const int items = pt.nex * R;
+        int it = lane;
+        unsigned idle = 0, rounds = 0;
+        int q = R1 ? it : it / R, k = R1 ? 0 : it - q * R;
+        int row = it < items ? pt.erl[q] : 0;
+        while (__ballot(it < items) != 0) {
+            bool moved = false;
+            if (it < items) {
+                const T v = lds_get(xl + row * R + k);
+                if (!is_sentinel(v)) {
+                    __hip_atomic_store(mrd + (size_t)(pt.e0 + q) * a.mbox_stride + k, v, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_AGENT);
+                    it += 64;
+                    idle = 0;
+                    moved = true;
+                    if (it < items) {
+                        q = R1 ? it : it / R;
+                        k = R1 ? 0 : it - q * R;
+                        row = pt.erl[q];
+                    }
+                } else if (++idle > (a.spin << 4)) {
+                    lds_put(s_abort, 2);
+                    it = items;
+                }
+            }
+            if (__ballot(moved) == 0) {
+                __builtin_amdgcn_s_sleep(1);
+                if ((++rounds & 15u) == 0 && lds_get(s_abort)) break;
+            }
+        }
+    }
+    __syncthreads();
+}
+
+// The part's solution from LDS to the workspace and / or the caller's vector.
+template <typename T> __device__ __forceinline__ void df_store(const TriArgs &a, const DfPart<T> &p, int R)
+{
+    const int nt = blockDim.x;
+    for (int t = threadIdx.x; t < p.win * R; t += nt) {
+        const int q = t / R, k = t - q * R;
+        const int x = p.lo + q;
+        const T v = p.xl[t];
+        if (a.write_xw) static_cast<T *>(a.xw)[(size_t)x * R + k] = v;
+        if (a.xout) {
+            const int d = a.scatter[x];  // negative: the row is not written (RAS overlap rows)
+            if (d >= 0) {
+                const size_t dst = (size_t)d * R + k;
+                if (a.out_f64) static_cast<double *>(a.xout)[dst] = static_cast<double>(v);
+                else static_cast<float *>(a.xout)[dst] = static_cast<float>(v);
+            }
+        }
+    }
+}
+
+// Report a wait that gave up (abort 2) to the other workgroups and the host.
+__device__ __forceinline__ void df_report(const TriArgs &a, DfCtl *ctl)
+{
+    if (threadIdx.x == 0 && ctl->abort == 2) {
+        __hip_atomic_store(a.err_dev, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(a.err_host, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        ctl->abort = 1;
+    }
+}
+
+// The last workgroup out resets the plan's counters and advances its epoch.
+__device__ __forceinline__ void df_leave(const TriArgs &a, unsigned epoch)
+{
+    const unsigned done = __hip_atomic_fetch_add(&a.epoch[1], 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+    if (done == gridDim.x - 1) {
+        __hip_atomic_store(&a.epoch[2], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&a.epoch[1], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&a.epoch[0], epoch + 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+
+template <typename T, int W, bool UNIT, bool TAIL, bool R1, bool TRACE>
+__global__ void __launch_bounds__(512) k_dataflow(TriArgs a)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    DfCtl *ctl = reinterpret_cast<DfCtl *>(smem + a.lds_ctl);
+    const int tid = threadIdx.x;
+    const int R = R1 ? 1 : a.R;
+    if (tid == 0) {
+        ctl->epoch = __hip_atomic_load(a.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        ctl->abort = 0;
+    }
+    __syncthreads();
+    const unsigned par = ctl->epoch & 1u;
+    T *mbox = static_cast<T *>(a.mbox);
+    const size_t half = (size_t)a.nexp * a.mbox_stride;
+    T *mrd = mbox + (par ? half : 0), *other = mbox + (par ? 0 : half);
+    for (int round = 0;; ++round) {
+        if (a.queue) {
+            if (tid == 0) ctl->part = (int)__hip_atomic_fetch_add(&a.epoch[2], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __syncthreads();
+        } else if (round > 0) {
+            break;
+        }
+        const int g = a.queue ? ctl->part : (int)blockIdx.x;
+        if (g >= a.nparts) break;
+        const DfPart<T> pt = df_part<T>(a, g, R, smem);
+        unsigned long long t_fill = 0;
+        df_sweep<T, W, TAIL, R1, TRACE>(a, pt, R, mrd, &ctl->abort, t_fill, [&]() {
+            if (a.in_f64) df_fill_b<T, UNIT, R1>(a, pt, R, static_cast<const double *>(a.bin));
+            else df_fill_b<T, UNIT, R1>(a, pt, R, static_cast<const float *>(a.bin));
+            df_fill_lists(a, pt, R, other);
+        });
+        const unsigned long long t_done = TRACE ? __builtin_amdgcn_s_memrealtime() : 0ull;
+        df_report(a, ctl);
+        if (TRACE) {
+            const int ntr = min(pt.ns, a.trace_stride - 1);
+            for (int t = tid; t < 2 * ntr; t += blockDim.x) a.trace[2 * (size_t)g * a.trace_stride + t] = pt.ltr[t];
+            if (tid == 0) {
+                a.trace[2 * ((size_t)g * a.trace_stride + a.trace_stride - 1)] = t_fill;
+                a.trace[2 * ((size_t)g * a.trace_stride + a.trace_stride - 1) + 1] = t_done;
+            }
+        }
+        if (!ctl->abort) df_store(a, pt, R);
+        __syncthreads();  // LDS is refilled by the next part
+        if (ctl->abort) break;
+    }
+    if (tid == 0) df_leave(a, ctl->epoch);
+}
+
+}  // namespace hec

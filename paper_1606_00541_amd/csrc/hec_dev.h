@@ -113,11 +113,26 @@ struct TriArgs {
     unsigned long long *trace;   // optional per-step clocks [groups][trace_stride][2]
     int32_t trace_stride;
     unsigned spin;               // polls before a bounded wait gives up
+    const int32_t *step_pack;    // dataflow kernel: per step its first window row | 16 (rows - 1) << 16
+    int32_t lds_ctl;             // dataflow kernel: LDS offset of the control words
     int32_t nparts;              // dataflow kernel: parts of the plan; system queue: systems
     int32_t queue;               // dataflow kernel: workgroups take parts from a counter (epoch[2])
     const int32_t *sq_lvp, *sq_lvrow, *sq_ring;  // system queue: levels per system, level rows, rings
     const int8_t *sq_keep;                        // system queue: rows also stored to xw (read beyond a ring)
 };
+
+// Kernels of one launch per triangle that take nothing but TriArgs.
+using OwnerKernel = void (*)(TriArgs);
+// Dataflow kernel for an ELL width (null if it is not built for it): value
+// type, one or several right-hand sides, _tr with per-step clocks.
+OwnerKernel df_f64_one(int w, bool unit, bool tail);
+OwnerKernel df_f64_many(int w, bool unit, bool tail);
+OwnerKernel df_f32_one(int w, bool unit, bool tail);
+OwnerKernel df_f32_many(int w, bool unit, bool tail);
+OwnerKernel df_f64_one_tr(int w, bool unit, bool tail);
+OwnerKernel df_f64_many_tr(int w, bool unit, bool tail);
+OwnerKernel df_f32_one_tr(int w, bool unit, bool tail);
+OwnerKernel df_f32_many_tr(int w, bool unit, bool tail);
 
 // Polls of a bounded device-side wait before it is declared hung (a plan may
 // set its own, tri_plan_set_wait_limit); at most kMaxSpin so that the
@@ -137,7 +152,7 @@ struct DevTri {
     DevMem step_ptr, step_row, step_lanes, window, exp_slot, exp_ptr, chunk_ptr, chunk_step, rem_ptr, rem_ent;
     int32_t variant = 0;           // persistent kernel choice (hec_tune_t.kernel_variant)
     bool dataflow = false;         // columns encode group-local imports (dataflow kernel only)
-    DevMem imp_ptr, imp_slot, exp_row, wave_ptr;
+    DevMem imp_ptr, imp_slot, exp_row, wave_ptr, step_pack;
     DevMem seg;                    // device row -> independent system (batches; empty: one system)
     const int8_t *act = nullptr;   // per-launch: active (system, rhs) problems; others may be skipped
     int32_t df_waves = 0;          // compute wavefronts per group (block = 64 * df_waves + 128)

@@ -89,7 +89,8 @@ struct Schedule {
     std::vector<int32_t> exp_row;    // [nexp]: device row of each mailbox slot
     int32_t max_imp = 0;             // most imports of one group
     int32_t df_rows = 0;             // max over groups of 2 * window rows + imports + 1
-    int32_t df_ints = 0;             // max over groups of imports + exports + 2 * steps
+    int32_t df_ints = 0;             // max over groups of imports + exports + steps + kDataflowPad
+    std::vector<int32_t> step_pack;  // per step: first window row | 16 (rows - 1) << 16
     int32_t df_waves = 0;            // compute wavefronts per group
     std::vector<int32_t> wave_ptr;   // [groups*df_waves+1]: steps of wavefront w of group g
     // queue mode: `groups` parts, more than the workgroups that run them; the
@@ -156,12 +157,38 @@ struct Tune {
 };
 // LDS bytes of the dataflow owner kernel: `rows` value rows (x window, b
 // window and imports) of R right-hand sides, then `ints` int32 entries
-// (import slots, export rows, step bounds).
+// (import slots, export rows, step descriptors) and the control words.
+constexpr int32_t kDataflowCtlBytes = 16;
+constexpr int32_t kDataflowPad = 16;  // descriptors the kernel may read past a part's last step
 size_t dataflow_lds_bytes(int32_t rows, int32_t ints, int32_t R, size_t tsize);
 // Smallest ELL width >= w the dataflow kernel is built for (1..8, 10, 12,
 // 16), or -1 above 16; and its largest workgroup (threads) at that width.
 int32_t dataflow_width(int32_t w);
 int32_t dataflow_max_block(int32_t w);
+// Record of a row as the dataflow kernel loads it: w values, then w 16-bit LDS
+// value rows, cut into 16-byte chunks (each chunk an array over the ld rows)
+// and a remainder of 0..2 dwords behind them (three dwords fill a chunk).
+struct DataflowRecord {
+    int32_t w, ld;
+    int32_t chunks, rest;  // 16-byte chunks, dwords of the remainder
+    int32_t tsize;         // bytes of a value
+    DataflowRecord(int32_t w_, int32_t ld_, int32_t tsize_);
+    size_t bytes() const { return (size_t)ld * (16 * (size_t)chunks + 4 * (size_t)rest); }
+    // byte offset of a dword of row x: first(dword) + x * stride(dword)
+    size_t first(int32_t dword) const
+    {
+        return dword < 4 * chunks ? (size_t)(dword / 4) * ld * 16 + 4 * (size_t)(dword % 4)
+                                  : (size_t)chunks * ld * 16 + 4 * (size_t)(dword - 4 * chunks);
+    }
+    size_t stride(int32_t dword) const { return dword < 4 * chunks ? 16 : 4 * (size_t)rest; }
+    int32_t value_dword(int32_t e) const { return e * (tsize / 4); }
+    int32_t column_dword(int32_t e) const { return w * (tsize / 4) + e / 2; }  // high half for odd e
+    // position of value e of row x in an array of values
+    size_t value(int32_t x, int32_t e) const
+    {
+        return (first(value_dword(e)) + x * stride(value_dword(e))) / tsize;
+    }
+};
 // Tuning with every field at its documented default.
 Tune default_tune();
 Tune tune_from(const hec_tune_t *t);

@@ -29,46 +29,14 @@
 #include <tuple>
 #include <type_traits>
 
-#include "hec_dev.h"
+#include "tri_dev.h"
 
 namespace hec {
 
 namespace {
 
 
-int32_t capacity_of(const void *kern, int32_t block, size_t lds);
-
-template <typename T> __device__ __forceinline__ T sentinel();
-template <> __device__ __forceinline__ double sentinel<double>() { return __longlong_as_double((long long)kSentinel64); }
-template <> __device__ __forceinline__ float sentinel<float>() { return __uint_as_float(kSentinel32); }
-__device__ __forceinline__ bool is_sentinel(double v) { return __double_as_longlong(v) == (long long)kSentinel64; }
-__device__ __forceinline__ bool is_sentinel(float v) { return __float_as_uint(v) == kSentinel32; }
-
-// A right-hand-side value as a kernel publishes it: an input whose bits
-// happen to equal the sentinel becomes the canonical quiet NaN, so that no
-// input value can stand for "not solved yet" (a row without dependencies
-// publishes its right-hand side unchanged).
-template <typename T> __device__ __forceinline__ T canon(T v)
-{
-    return is_sentinel(v) ? __builtin_nan("") : v;
-}
-template <> __device__ __forceinline__ float canon<float>(float v)
-{
-    return is_sentinel(v) ? __builtin_nanf("") : v;
-}
-
-// Right-hand side times the reciprocal diagonal, rounded on its own (never
-// contracted into the first multiply-add), identically in every kernel.
-__device__ __forceinline__ double scale_rhs(double b, double d)
-{
-#pragma clang fp contract(off)
-    return b * d;
-}
-__device__ __forceinline__ float scale_rhs(float b, float d)
-{
-#pragma clang fp contract(off)
-    return b * d;
-}
+int32_t capacity_of(const void *kern, int32_t block, size_t lds, bool lds_at_zero = false);
 
 // Per-launch state of the persistent kernel shared by the row routine.
 template <typename T> struct Ctx {
@@ -484,7 +452,6 @@ size_t owner_lds_bytes(int win, int R, int W, int rows_per_chunk, bool unit, siz
     return win_bytes + 2 * buf;
 }
 
-using OwnerKernel = void (*)(TriArgs);
 
 template <typename T, int W, int RPT>
 OwnerKernel owner_kernel_w(bool unit)
@@ -776,487 +743,6 @@ __global__ void __launch_bounds__(128) k_owner_split(TriArgs a)
             __hip_atomic_store(&a.epoch[0], s_epoch + 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
         }
     }
-}
-
-// Dataflow owner kernel.  A workgroup owns a part of the rows (a contiguous
-// device-row window in level order) and runs three kinds of wavefronts:
-//   compute waves  take the group's steps round-robin; a step is one level
-//                  piece of at most 64 (row, rhs) items, solved one item per
-//                  lane.  Each dependency is read from LDS and re-read until
-//                  it no longer holds the sentinel, so a row starts as soon
-//                  as its own inputs exist: there is no per-level barrier.
-//                  The matrix data of a wave's next step is loaded into
-//                  registers while the current one is solved; compute waves
-//                  issue no global stores, so their waits cover loads only.
-//   import wave    polls the mailbox slots this group reads (lane l takes
-//                  imports l, l+64, ... in order of first use) and copies
-//                  each value into LDS when it arrives;
-//   export wave    watches the group's exported rows in LDS and writes each
-//                  one to its mailbox slot as soon as it is solved.
-// Any row waits only on rows of lower levels, and every wave handles its
-// items in level order, so the row of lowest level not yet solved can always
-// proceed: the grid drains as long as all workgroups are co-resident.
-// The summation order (ELL slots, then the CSR tail, then the reciprocal
-// diagonal) is the one of k_level, so results are bit-identical to it.
-template <typename T> __device__ __forceinline__ T lds_get(const T *p)
-{
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-template <typename T> __device__ __forceinline__ void lds_put(T *p, T v)
-{
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-
-template <typename T, int W> struct DfRegs {
-    int c[W];  // columns as loaded, then LDS byte offsets
-    T v[W];
-    T b;       // right-hand side of the lane's item
-    int r, k;  // the lane's item: window row, right-hand side
-    int xo;    // LDS byte offset of the item's value
-};
-
-// TRACE: per-step clocks (tri_plan_trace).  Untraced instances read no clock
-// in the step loop: the clock is a scalar-memory read, and with one possibly
-// outstanding the compiler must drain every LDS access before the next step.
-template <typename T, int W, bool UNIT, bool TAIL, bool R1, bool TRACE>
-__global__ void __launch_bounds__(512) k_dataflow(TriArgs a)
-{
-    extern __shared__ __align__(16) unsigned char smem[];
-    __shared__ unsigned s_epoch;
-    __shared__ int s_abort;
-    __shared__ int s_part;
-    const int tid = threadIdx.x, nt = blockDim.x;
-    const int lane = tid & 63;
-    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int nwc = (nt >> 6) - 2;
-    const int R = R1 ? 1 : a.R;
-    if (tid == 0) {
-        s_epoch = __hip_atomic_load(a.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        s_abort = 0;
-    }
-    __syncthreads();
-    const unsigned par = s_epoch & 1u;
-    T *mbox = static_cast<T *>(a.mbox);
-    const size_t half = (size_t)a.nexp * a.mbox_stride;
-    T *mrd = mbox + (par ? half : 0);
-    // Parts: workgroup g runs part g, or (queue mode) the workgroups take
-    // parts from a counter in index order until none is left.  Queue-mode
-    // parts are numbered so that a part reads only from lower-numbered ones,
-    // and a part is taken only by a running workgroup, so the solve needs no
-    // more workgroups resident than one.
-    for (int round = 0;; ++round) {
-    if (a.queue) {
-        if (tid == 0) s_part = (int)__hip_atomic_fetch_add(&a.epoch[2], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __syncthreads();
-    } else if (round > 0) {
-        break;
-    }
-    const int g = a.queue ? s_part : (int)blockIdx.x;
-    if (g >= a.nparts) break;
-    const int lo = a.window[2 * g], hi = a.window[2 * g + 1], win = hi - lo;
-    const int i0 = a.imp_ptr[g], nimp = a.imp_ptr[g + 1] - i0;
-    const int e0 = a.exp_ptr[g], nex = a.exp_ptr[g + 1] - e0;
-    const int s0 = a.step_ptr[g], ns = a.step_ptr[g + 1] - s0;
-    // LDS value rows: x [win][R], b [win][R], imports [nimp][R], one zero
-    // row (the target of ELL padding); then import slots, export rows
-    // (window offsets) and step bounds (window offsets)
-    T *xl = reinterpret_cast<T *>(smem);
-    T *bl = xl + (size_t)win * R;
-    T *im = bl + (size_t)win * R;
-    const size_t ib = (((size_t)2 * win + nimp + 1) * R * sizeof(T) + 15) & ~(size_t)15;
-    int *isl = reinterpret_cast<int *>(smem + ib);
-    int *erl = isl + nimp;
-    int *stl = erl + nex;
-    // when tracing: 2*ns clocks after the ints, at an 8-byte boundary
-    unsigned long long *ltr =
-        reinterpret_cast<unsigned long long *>(smem + ((ib + (size_t)(nimp + nex + 2 * ns) * 4 + 7) & ~(size_t)7));
-
-    if (a.nexp > 0) {
-        T *other = mbox + (par ? 0 : half);
-        const size_t m0 = (size_t)e0 * a.mbox_stride, m1 = (size_t)(e0 + nex) * a.mbox_stride;
-        for (size_t i = m0 + tid; i < m1; i += nt) other[i] = sentinel<T>();
-    }
-    // Fill LDS.  Every thread keeps kFill independent loads in flight (the
-    // start-up of all groups delays the first rows of the solve).
-    constexpr int kFill = 8;
-    for (int t = tid; t < win * R; t += nt) xl[t] = sentinel<T>();
-    for (int t = tid; t < (nimp + 1) * R; t += nt) im[t] = t < nimp * R ? sentinel<T>() : T(0);
-    auto fill_b = [&](const auto *bin) {
-        for (int t0 = tid; t0 < win * R; t0 += kFill * nt) {
-            int gi[kFill];
-#pragma unroll
-            for (int u = 0; u < kFill; ++u) {
-                const int t = min(t0 + u * nt, win * R - 1);
-                gi[u] = a.gather[lo + (R1 ? t : t / R)];
-            }
-            T bv[kFill], dd[kFill];
-#pragma unroll
-            for (int u = 0; u < kFill; ++u) {
-                const int t = min(t0 + u * nt, win * R - 1);
-                bv[u] = canon(static_cast<T>(bin[(size_t)gi[u] * R + (R1 ? 0 : t % R)]));
-                if (!UNIT) dd[u] = static_cast<const T *>(a.dinv)[lo + (R1 ? t : t / R)];
-            }
-            if (!UNIT) {
-#pragma unroll
-                for (int u = 0; u < kFill; ++u) bv[u] = scale_rhs(bv[u], dd[u]);
-            }
-#pragma unroll
-            for (int u = 0; u < kFill; ++u)
-                if (t0 + u * nt < win * R) bl[t0 + u * nt] = bv[u];
-        }
-    };
-    if (a.in_f64) fill_b(static_cast<const double *>(a.bin));
-    else fill_b(static_cast<const float *>(a.bin));
-    auto copy_ints = [&](int *dst, const int32_t *src, int count, int add) {
-        for (int t0 = tid; t0 < count; t0 += kFill * nt) {
-            int v[kFill];
-#pragma unroll
-            for (int u = 0; u < kFill; ++u) v[u] = src[min(t0 + u * nt, count - 1)];
-#pragma unroll
-            for (int u = 0; u < kFill; ++u)
-                if (t0 + u * nt < count) dst[t0 + u * nt] = v[u] + add;
-        }
-    };
-    copy_ints(isl, a.imp_slot + i0, nimp, 0);
-    copy_ints(erl, a.exp_row + e0, nex, -lo);
-    copy_ints(stl, a.step_row + 2 * s0, 2 * ns, -lo);
-    __syncthreads();
-    const unsigned long long t_fill = TRACE ? __builtin_amdgcn_s_memrealtime() : 0ull;
-
-    if (wv < nwc) {
-        const T *ev = static_cast<const T *>(a.ell_val);
-        const T *tv = static_cast<const T *>(a.tail_val);
-        // Lanes past the step's items repeat its last item, so loads and
-        // their uses are unconditional and the compiler's load waits stay
-        // exact.  The ELL slots of a step's rows are contiguous per slot:
-        // buffer loads with one per-lane byte offset and a per-slot scalar
-        // offset (no 64-bit address arithmetic per load).
-        const int nb_col = (int)min((size_t)0x7fffffff, (size_t)a.w * a.ld * sizeof(int32_t));
-        const int nb_val = (int)min((size_t)0x7fffffff, (size_t)a.w * a.ld * sizeof(T));
-        const __amdgpu_buffer_rsrc_t rcol =
-            __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t *>(a.ell_col), 0, nb_col, 0x00020000);
-        const __amdgpu_buffer_rsrc_t rval =
-            __builtin_amdgcn_make_buffer_rsrc(const_cast<T *>(ev), 0, nb_val, 0x00020000);
-        unsigned char *xb = reinterpret_cast<unsigned char *>(xl);
-        // Everything a step needs besides its inputs is prepared when its
-        // register set is filled, steps ahead: the matrix loads, the lane's
-        // item (row r, right-hand side k), its right-hand-side value from LDS
-        // and the LDS byte offset its result goes to.
-        auto load = [&](DfRegs<T, W> &u, int rb, int re) {
-            const int it = min(lane, (re - rb) * R - 1);
-            const int q = R1 ? it : it / R;
-            u.k = R1 ? 0 : it - q * R;
-            u.r = rb + q;
-            const int x = lo + u.r;
-#pragma unroll
-            for (int e = 0; e < W; ++e) {
-                u.c[e] = (int)__builtin_amdgcn_raw_buffer_load_b32(rcol, x * (int)sizeof(int32_t),
-                                                                   e * a.ld * (int)sizeof(int32_t), 0);
-                if constexpr (sizeof(T) == 8)
-                    u.v[e] = __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(rval, x * 8, e * a.ld * 8, 0));
-                else
-                    u.v[e] = __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(rval, x * 4, e * a.ld * 4, 0));
-            }
-            u.xo = (u.r * R + u.k) * (int)sizeof(T);
-            u.b = bl[u.r * R + u.k];
-        };
-        // columns (LDS value rows; ELL padding names the zero row) become
-        // LDS byte offsets one step before their use
-        auto to_offsets = [&](DfRegs<T, W> &u) {
-#pragma unroll
-            for (int e = 0; e < W; ++e) u.c[e] = (R1 ? u.c[e] : u.c[e] * R + u.k) * (int)sizeof(T);
-        };
-        const int ntr = TRACE ? min(ns, a.trace_stride - 1) : 0;
-        bool aborted = false;
-        // Solve step j from registers u.  Its inputs are read first; while
-        // they are in flight the loads of step j+K-1 (bounds fb, fe, read one
-        // step earlier) go into `fill` and the bounds of step j+K are read;
-        // after the result is stored the next step's columns become offsets.  Padding subtracts 0 * 0,
-        // which leaves the value unchanged bit for bit.  An input not solved
-        // yet holds the sentinel (a NaN), so a lane that read one ends with a
-        // NaN: one test of the result covers every input.  Only then are the
-        // inputs checked one by one (the result may be a NaN of the data,
-        // which passes) and re-read until none holds the sentinel, and the
-        // value is recomputed in the same order.
-        auto process = [&](const DfRegs<T, W> &u, DfRegs<T, W> &fill, DfRegs<T, W> &next, int j, int &fb, int &fe,
-                           int nq) {
-            if (TRACE && j < ntr && lane == 0) ltr[2 * j] = __builtin_amdgcn_s_memrealtime();
-            T dep[W];
-#pragma unroll
-            for (int e = 0; e < W; ++e) dep[e] = lds_get(reinterpret_cast<const T *>(xb + u.c[e]));
-            __builtin_amdgcn_sched_barrier(0);  // the reads go first
-            load(fill, fb, fe);
-            fb = stl[2 * nq];
-            fe = stl[2 * nq + 1];
-            T acc = u.b;
-#pragma unroll
-            for (int e = 0; e < W; ++e) acc -= u.v[e] * dep[e];
-            if (__ballot(acc != acc) != 0) {
-                bool pend = false;
-#pragma unroll
-                for (int e = 0; e < W; ++e) pend |= is_sentinel(dep[e]);
-                unsigned spins = 0;
-                while (pend) {
-                    // re-read every input (one LDS round trip per poll; inputs
-                    // already present do not change)
-#pragma unroll
-                    for (int e = 0; e < W; ++e) dep[e] = lds_get(reinterpret_cast<const T *>(xb + u.c[e]));
-                    pend = false;
-#pragma unroll
-                    for (int e = 0; e < W; ++e) pend |= is_sentinel(dep[e]);
-                    if (pend && (++spins & 63u) == 0) {
-                        if (lds_get(&s_abort)) {
-                            aborted = true;
-                            break;
-                        }
-                        if (spins > (a.spin << 4)) {
-                            lds_put(&s_abort, 2);
-                            aborted = true;
-                            break;
-                        }
-                    }
-                }
-                acc = u.b;
-#pragma unroll
-                for (int e = 0; e < W; ++e) acc -= u.v[e] * dep[e];
-            }
-            if (TAIL) {
-                const int x = lo + u.r;
-                for (int p = a.tail_ptr[x]; p < a.tail_ptr[x + 1]; ++p) {
-                    const int o = a.tail_col[p] * R + u.k;
-                    T dd = lds_get(xl + o);
-                    unsigned sp = 0;
-                    while (is_sentinel(dd)) {
-                        dd = lds_get(xl + o);
-                        if ((++sp & 63u) == 0) {
-                            if (lds_get(&s_abort)) {
-                                aborted = true;
-                                break;
-                            }
-                            if (sp > (a.spin << 4)) {
-                                lds_put(&s_abort, 2);
-                                aborted = true;
-                                break;
-                            }
-                        }
-                    }
-                    acc -= tv[p] * dd;
-                }
-            }
-            // lanes past the items store the same value as the last item's lane;
-            // the store is the end of the dependency chain, so nothing of the
-            // next step (which waits for this step's bounds read) is
-            // scheduled above it
-            lds_put(reinterpret_cast<T *>(xb + u.xo), acc);
-            __builtin_amdgcn_sched_barrier(0);
-            to_offsets(next);
-            if (TRACE && j < ntr && lane == 0) ltr[2 * j + 1] = __builtin_amdgcn_s_memrealtime();
-        };
-        // The wave walks its own steps [j, jend) in order.  K register sets
-        // rotate: while step j is solved from one, the next K-2 steps have
-        // their matrix loads in flight and step j+K-1's loads are issued into
-        // the set just freed.  K is as large as the vector-memory counter
-        // allows (it holds 63 outstanding loads; a step issues 2W), so a step
-        // finds its data loaded although the memory latency spans several
-        // steps.  Loads past the last step repeat it, so every path issues
-        // the same loads; the loop runs whole rotations with a single exit at
-        // the bottom and no register moves, so the compiler's load waits are
-        // exact.
-        int j = a.wave_ptr[g * nwc + wv] - s0;
-        const int jend = a.wave_ptr[g * nwc + wv + 1] - s0;
-        const int last = jend - 1;
-        constexpr int K = W == 1 ? 12 : (W == 2 ? 10 : (W == 3 ? (R1 ? 9 : 8) : (W <= 5 ? 6 : (W <= 8 ? 4 : 3))));
-        constexpr int kAhead = K - 1;
-        DfRegs<T, W> S[K];
-        auto first = [&](DfRegs<T, W> &u, int q) {
-            q = min(q, last);
-            load(u, stl[2 * q], stl[2 * q + 1]);
-        };
-        int fb = 0, fe = 0;
-        auto run = [&](const DfRegs<T, W> &u, DfRegs<T, W> &fill, DfRegs<T, W> &next) {
-            process(u, fill, next, j, fb, fe, min(j + kAhead + 1, last));
-            j += 1;
-        };
-        if (j < jend) {
-#pragma unroll
-            for (int p = 0; p < K - 1; ++p) first(S[p], j + p);
-            to_offsets(S[0]);
-            fb = stl[2 * min(j + kAhead, last)];
-            fe = stl[2 * min(j + kAhead, last) + 1];
-            const int rounds = (jend - j) / K, rest = (jend - j) - K * rounds;
-            for (int q = 0; q < rounds; ++q) {
-#pragma unroll
-                for (int p = 0; p < K; ++p) run(S[p], S[(p + K - 1) % K], S[(p + 1) % K]);
-                if (__ballot(aborted) != 0) break;
-            }
-#pragma unroll
-            for (int p = 0; p < K - 1; ++p)
-                if (rest > p && __ballot(aborted) == 0) run(S[p], S[(p + K - 1) % K], S[(p + 1) % K]);
-        }
-    } else if (wv == nwc) {
-        // import wave: lane l owns items l, l+64, l+128, ... (level order).
-        // Each poll round reads those of the lane's next kLook items that have
-        // not arrived yet, copies every new arrival into LDS, and moves the
-        // lane past the delivered prefix.  One round trip thus delivers
-        // several levels' worth of a lane's items without re-reading any.
-        constexpr int kLook = 2;
-        const int items = nimp * R;
-        const int xoff = 2 * win * R;
-        int it = lane;
-        unsigned got = 0;  // bit u: item it + 64 u already delivered
-        unsigned idle = 0;
-        while (__ballot(it < items) != 0) {
-            if (it < items) {
-                T v[kLook];
-#pragma unroll
-                for (int u = 0; u < kLook; ++u) {
-                    const int i2 = it + 64 * u;
-                    v[u] = sentinel<T>();
-                    if (i2 < items && !((got >> u) & 1u)) {
-                        const int q = i2 / R, k = i2 - q * R;
-                        v[u] = __hip_atomic_load(mrd + (size_t)isl[q] * a.mbox_stride + k, __ATOMIC_RELAXED,
-                                                 __HIP_MEMORY_SCOPE_AGENT);
-                    }
-                }
-                bool fresh = false;
-#pragma unroll
-                for (int u = 0; u < kLook; ++u) {
-                    if (!is_sentinel(v[u])) {
-                        lds_put(xl + xoff + it + 64 * u, v[u]);
-                        got |= 1u << u;
-                        fresh = true;
-                    }
-                }
-                while (got & 1u) {
-                    got >>= 1;
-                    it += 64;
-                }
-                if (fresh) {
-                    idle = 0;
-                } else if (++idle > a.spin) {
-                    lds_put(&s_abort, 2);
-                    it = items;
-                } else if ((idle & 255u) == 0 &&
-                           __hip_atomic_load(a.err_dev, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
-                    lds_put(&s_abort, 1);  // another workgroup gave up
-                    it = items;
-                }
-            }
-            if (lds_get(&s_abort)) break;
-        }
-    } else {
-        // export wave: each lane watches its next exported item; a round in
-        // which no lane found a new value sleeps briefly, so the wave does
-        // not take issue slots and LDS bandwidth from the compute waves
-        const int items = nex * R;
-        int it = lane;
-        unsigned idle = 0, rounds = 0;
-        int q = it / R, k = it - q * R;
-        int row = it < items ? erl[q] : 0;
-        while (__ballot(it < items) != 0) {
-            bool moved = false;
-            if (it < items) {
-                const T v = lds_get(xl + row * R + k);
-                if (!is_sentinel(v)) {
-                    __hip_atomic_store(mrd + (size_t)(e0 + q) * a.mbox_stride + k, v, __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_AGENT);
-                    it += 64;
-                    idle = 0;
-                    moved = true;
-                    if (it < items) {
-                        q = it / R;
-                        k = it - q * R;
-                        row = erl[q];
-                    }
-                } else if (++idle > (a.spin << 4)) {
-                    lds_put(&s_abort, 2);
-                    it = items;
-                }
-            }
-            if (__ballot(moved) == 0) {
-                __builtin_amdgcn_s_sleep(1);
-                if ((++rounds & 15u) == 0 && lds_get(&s_abort)) break;
-            }
-        }
-    }
-    __syncthreads();
-    const unsigned long long t_done = TRACE ? __builtin_amdgcn_s_memrealtime() : 0ull;
-    if (tid == 0 && s_abort == 2) {
-        __hip_atomic_store(a.err_dev, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(a.err_host, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-        s_abort = 1;
-    }
-    if (TRACE) {
-        const int ntr = min(ns, a.trace_stride - 1);
-        for (int t = tid; t < 2 * ntr; t += nt) a.trace[2 * (size_t)g * a.trace_stride + t] = ltr[t];
-        if (tid == 0) {
-            a.trace[2 * ((size_t)g * a.trace_stride + a.trace_stride - 1)] = t_fill;
-            a.trace[2 * ((size_t)g * a.trace_stride + a.trace_stride - 1) + 1] = t_done;
-        }
-    }
-    if (!s_abort) {
-        for (int t = tid; t < win * R; t += nt) {
-            const int q = t / R, k = t - q * R;
-            const int x = lo + q;
-            const T v = xl[t];
-            if (a.write_xw) static_cast<T *>(a.xw)[(size_t)x * R + k] = v;
-            if (a.xout) {
-                const int d = a.scatter[x];  // negative: the row is not written (RAS overlap rows)
-                if (d >= 0) {
-                    const size_t dst = (size_t)d * R + k;
-                    if (a.out_f64) static_cast<double *>(a.xout)[dst] = static_cast<double>(v);
-                    else static_cast<float *>(a.xout)[dst] = static_cast<float>(v);
-                }
-            }
-        }
-    }
-    __syncthreads();  // LDS is refilled by the next part
-    if (s_abort) break;
-    }  // parts
-    if (tid == 0) {
-        const unsigned done = __hip_atomic_fetch_add(&a.epoch[1], 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
-        if (done == gridDim.x - 1) {
-            // last workgroup out: every claim is over; reset the queue
-            __hip_atomic_store(&a.epoch[2], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(&a.epoch[1], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(&a.epoch[0], s_epoch + 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-        }
-    }
-}
-
-template <typename T, bool UNIT, bool TAIL, bool R1, bool TRACE>
-OwnerKernel dataflow_kernel_w(int w)
-{
-    switch (w) {
-    case 1: return k_dataflow<T, 1, UNIT, TAIL, R1, TRACE>;
-    case 2: return k_dataflow<T, 2, UNIT, TAIL, R1, TRACE>;
-    case 3: return k_dataflow<T, 3, UNIT, TAIL, R1, TRACE>;
-    case 4: return k_dataflow<T, 4, UNIT, TAIL, R1, TRACE>;
-    case 5: return k_dataflow<T, 5, UNIT, TAIL, R1, TRACE>;
-    case 6: return k_dataflow<T, 6, UNIT, TAIL, R1, TRACE>;
-    case 7: return k_dataflow<T, 7, UNIT, TAIL, R1, TRACE>;
-    case 8: return k_dataflow<T, 8, UNIT, TAIL, R1, TRACE>;
-    case 10: return k_dataflow<T, 10, UNIT, TAIL, R1, TRACE>;
-    case 12: return k_dataflow<T, 12, UNIT, TAIL, R1, TRACE>;
-    case 16: return k_dataflow<T, 16, UNIT, TAIL, R1, TRACE>;
-    default: return nullptr;
-    }
-}
-
-template <typename T, bool R1, bool TRACE>
-OwnerKernel dataflow_kernel_r(int w, bool unit, bool tail)
-{
-    if (unit)
-        return tail ? dataflow_kernel_w<T, true, true, R1, TRACE>(w) : dataflow_kernel_w<T, true, false, R1, TRACE>(w);
-    return tail ? dataflow_kernel_w<T, false, true, R1, TRACE>(w) : dataflow_kernel_w<T, false, false, R1, TRACE>(w);
-}
-
-template <typename T>
-OwnerKernel dataflow_kernel(int w, bool unit, bool tail, int R, bool trace)
-{
-    if (trace)
-        return R == 1 ? dataflow_kernel_r<T, true, true>(w, unit, tail) : dataflow_kernel_r<T, false, true>(w, unit, tail);
-    return R == 1 ? dataflow_kernel_r<T, true, false>(w, unit, tail) : dataflow_kernel_r<T, false, false>(w, unit, tail);
 }
 
 template <typename T>
@@ -1825,17 +1311,28 @@ void launch_typed(DevTri &d, TriArgs a, hipStream_t st)
     }
     if (d.dataflow) {
         // the plan's columns name group-local imports: only this kernel reads them
-        OwnerKernel k = dataflow_kernel<T>(d.w, d.unit, d.has_tail, a.R, a.trace != nullptr);
+        const bool one = a.R == 1, f64 = sizeof(T) == 8;
+        OwnerKernel k = nullptr;
+        if (a.trace)
+            k = f64 ? (one ? df_f64_one_tr : df_f64_many_tr)(d.w, d.unit, d.has_tail)
+                    : (one ? df_f32_one_tr : df_f32_many_tr)(d.w, d.unit, d.has_tail);
+        else
+            k = f64 ? (one ? df_f64_one : df_f64_many)(d.w, d.unit, d.has_tail)
+                    : (one ? df_f32_one : df_f32_many)(d.w, d.unit, d.has_tail);
         if (!k) fail(HEC_ERR_INVALID_ARG, "internal: dataflow plan with an unsupported ELL width");
         if ((int64_t)d.df_step_rows * a.R > 64)
             fail(HEC_ERR_INVALID_ARG, "dataflow plan: nrhs exceeds the plan's max_nrhs (steps are sized for it)");
         size_t lds = dataflow_lds_bytes(d.df_rows, d.df_ints, a.R, sizeof(T));
-        if (a.trace) lds += 8 + 16 * (size_t)std::min(d.df_ints / 2, a.trace_stride);  // per-step clocks
+        a.lds_ctl = (int32_t)lds - kDataflowCtlBytes;
+        if (a.trace) {  // per-step clocks, before the control words
+            lds += 16 + 16 * (size_t)std::min(d.df_ints, a.trace_stride);
+            a.lds_ctl = (int32_t)lds - kDataflowCtlBytes;
+        }
         const int block = 64 * d.df_waves + 128;
         if (block > dataflow_max_block(d.w)) fail(HEC_ERR_INVALID_ARG, "dataflow kernel: block too large");
         if (lds > (size_t)device_max_lds())
             fail(HEC_ERR_CAPACITY, "dataflow kernel: LDS need exceeds the device limit at this nrhs");
-        const int32_t cap = capacity_of((const void *)k, block, lds);
+        const int32_t cap = capacity_of((const void *)k, block, lds, true);
         a.nparts = d.groups;
         a.queue = d.queue ? 1 : 0;
         int32_t grid = d.groups;
@@ -1903,8 +1400,9 @@ void launch_in(DevTri &d, const TriArgs &a, hec_dtype_t in_dt, hec_dtype_t out_d
 
 // Co-resident workgroups of one kernel instance on the current device
 // (cached: the occupancy query and the LDS attribute are set once per
-// kernel, block size, LDS size and device).
-int32_t capacity_of(const void *kern, int32_t block, size_t lds)
+// kernel, block size, LDS size and device).  lds_at_zero: the kernel takes its
+// dynamic LDS to start at LDS address 0, so it must have no static LDS.
+int32_t capacity_of(const void *kern, int32_t block, size_t lds, bool lds_at_zero)
 {
     struct Key {
         const void *k;
@@ -1925,6 +1423,11 @@ int32_t capacity_of(const void *kern, int32_t block, size_t lds)
         std::lock_guard<std::mutex> g(mu);
         auto it = cache.find(key);
         if (it != cache.end()) return it->second;
+    }
+    if (lds_at_zero) {
+        hipFuncAttributes fa{};
+        hip_check(hipFuncGetAttributes(&fa, kern), "hipFuncGetAttributes");
+        if (fa.sharedSizeBytes != 0) fail(HEC_ERR_HIP, "internal: a kernel addressing LDS from 0 has static LDS");
     }
     int cus = 0, per = 0;
     hip_check(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev), "attr CUs");
@@ -2033,6 +1536,7 @@ void launch_tri(DevTri &d, const void *bin, hec_dtype_t in_dt, const int32_t *ga
     a.imp_slot = d.imp_slot.as<int32_t>();
     a.exp_row = d.exp_row.as<int32_t>();
     a.wave_ptr = d.wave_ptr.as<int32_t>();
+    a.step_pack = d.step_pack.as<int32_t>();
     a.act = d.act;
     a.seg = d.seg.p ? d.seg.as<int32_t>() : nullptr;
     a.trace = d.trace;
