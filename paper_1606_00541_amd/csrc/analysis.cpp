@@ -777,6 +777,156 @@ std::vector<int32_t> queue_parts(const Csr &a, bool upper, const Levels &lv, con
     return po;
 }
 
+// Parts of the dataflow kernel under the automatic schedule.  Every handoff
+// between workgroups on a dependency chain costs about ten steps inside one,
+// so a small problem is faster on few workgroups: a 64^2 ILU(0) application
+// takes 109 us on 256 parts (30 handoffs a triangle) and 39 us on one; 32^3
+// 88 us on 256 and 50 us on 8; an irregular triangle of 20011 rows 816 us on
+// 256 and 258 us on 4.  Larger parts also hold more rows of a level, which a
+// wavefront solves 64 at a time, and take longer to fill.  The estimate walks
+// the levels with the measured costs below, for the fewest parts that fit the
+// LDS and up to eight times as many, cut into grid blocks, contiguous ranges
+// and (for independent blocks) ranges ending at block boundaries.
+struct PartModel {
+    // microseconds: a step of a wavefront by ELL width, a value read from
+    // another wavefront of the workgroup, one from another workgroup, and
+    // filling and storing a thousand values of a part
+    static double step(int32_t w) { return 0.045 + 0.013 * w; }
+    static constexpr double wave = 0.05, hop = 1.2, kvalue = 0.8;
+};
+
+// LDS bytes the dataflow kernel needs for these parts (as make_dataflow and
+// dataflow_lds_bytes count them), and the estimated time of the solve, given
+// up (infinite) once it exceeds `limit`.
+struct PartEstimate {
+    int32_t rows = 0, ints = 0;   // as Schedule::df_rows, df_ints
+    int32_t longest = 0;          // rows of the longest step
+    double us = 0.0;              // infinite when over the limit or the LDS
+};
+
+PartEstimate estimate_parts(const Csr &a, bool upper, const Levels &lv, const std::vector<int32_t> &part, int32_t P,
+                            int32_t waves, int32_t w, int32_t R, size_t ts, size_t cap, double limit)
+{
+    const int32_t n = a.n;
+    PartEstimate out;
+    // rows of each part in problem order, and the wavefront piece of each row
+    std::vector<int32_t> size((size_t)P + 1, 0), piece(n);
+    for (int32_t i = 0; i < n; ++i) size[part[i] + 1] += 1;
+    std::vector<int32_t> start(size);
+    for (int32_t g = 0; g < P; ++g) start[g + 1] += start[g];
+    std::vector<int32_t> rows(n), cur(start.begin(), start.end() - 1);
+    for (int32_t q = 0; q < n; ++q) {
+        const int32_t i = upper ? n - 1 - q : q;
+        rows[cur[part[i]]++] = i;
+    }
+    int64_t widest = 0;
+    for (int32_t g = 0; g < P; ++g) {
+        const int64_t m = start[g + 1] - start[g];
+        widest = std::max(widest, m);
+        for (int32_t w2 = 0; w2 < waves; ++w2)
+            for (int64_t u = m * w2 / waves; u < m * (w2 + 1) / waves; ++u) piece[rows[start[g] + u]] = g * waves + w2;
+    }
+    // imports and exports
+    std::vector<int32_t> stamp(n, -1);
+    std::vector<int32_t> exported((size_t)P, 0);
+    std::vector<char> is_exp(n, 0);
+    std::vector<int32_t> imports((size_t)P, 0);
+    for (int32_t g = 0; g < P; ++g)
+        for (int32_t k = start[g]; k < start[g + 1]; ++k)
+            for (int32_t p = a.rp[rows[k]]; p < a.rp[rows[k] + 1]; ++p) {
+                const int32_t j = a.ci[p];
+                if (part[j] == g || stamp[j] == g) continue;
+                stamp[j] = g;
+                imports[g] += 1;
+                if (!is_exp[j]) {
+                    is_exp[j] = 1;
+                    exported[part[j]] += 1;
+                }
+            }
+    // steps and finish times, level by level
+    const int32_t per = std::max(1, 64 / R);
+    const double ts_us = PartModel::step(w), fixed = 1e-3 * PartModel::kvalue * (double)widest * R;
+    std::vector<double> clock((size_t)P * waves, 0.0), ready((size_t)P * waves, 0.0), finish;
+    std::vector<int32_t> count((size_t)P * waves, 0), open((size_t)P * waves, -1), nsteps((size_t)P, 0), step(n), touched;
+    finish.reserve((size_t)n / 16 + 64);
+    for (int32_t l = 0; l < lv.nlev; ++l) {
+        touched.clear();
+        auto close = [&](int32_t c) {
+            clock[c] = std::max(clock[c], ready[c]) + ts_us;
+            finish[open[c]] = clock[c];
+        };
+        for (int32_t r = lv.levelptr[l]; r < lv.levelptr[l + 1]; ++r) {
+            const int32_t i = lv.perm[r], c = piece[i];
+            if (count[c] == 0) touched.push_back(c);
+            if (count[c] % per == 0) {
+                if (count[c] > 0) close(c);
+                open[c] = (int32_t)finish.size();
+                finish.push_back(0.0);
+                nsteps[part[i]] += 1;
+                ready[c] = 0.0;
+            }
+            count[c] += 1;
+            out.longest = std::max(out.longest, std::min(count[c], per));
+            step[i] = open[c];
+            for (int32_t p = a.rp[i]; p < a.rp[i + 1]; ++p) {
+                const int32_t j = a.ci[p];
+                if (j == i) continue;
+                const double t = finish[step[j]] + (piece[j] == c ? 0.0 : part[j] == part[i] ? PartModel::wave : PartModel::hop);
+                ready[c] = std::max(ready[c], t);
+            }
+        }
+        for (int32_t c : touched) {
+            close(c);
+            count[c] = 0;
+            out.us = std::max(out.us, clock[c]);
+        }
+        if (out.us + fixed > limit) {
+            out.us = INFINITY;
+            return out;
+        }
+    }
+    out.us += fixed;
+    for (int32_t g = 0; g < P; ++g) {
+        out.rows = std::max(out.rows, 2 * (start[g + 1] - start[g]) + imports[g] + 1);
+        out.ints = std::max(out.ints, imports[g] + exported[g] + nsteps[g] + kDataflowPad);
+    }
+    if (dataflow_lds_bytes(out.rows, out.ints, R, ts) > cap) out.us = INFINITY;
+    return out;
+}
+
+// Contiguous ranges of about n / P rows that end at block boundaries where
+// they can: a block of up to 5/4 of that stays whole, longer ones are cut
+// evenly.  Returns the number of parts.
+int32_t block_parts(int32_t n, const std::vector<int32_t> &ptr, int32_t P, std::vector<int32_t> &part)
+{
+    const int64_t target = (n + P - 1) / P;
+    part.assign(n, 0);
+    int32_t g = -1;
+    int64_t acc = 0;
+    bool open = false;
+    for (size_t s = 0; s + 1 < ptr.size(); ++s) {
+        const int64_t m = ptr[s + 1] - ptr[s];
+        if (m == 0) continue;
+        const int64_t k = 4 * m <= 5 * target ? 1 : (m + target - 1) / target;
+        for (int64_t c = 0; c < k; ++c) {
+            const int64_t b = ptr[s] + m * c / k, e = ptr[s] + m * (c + 1) / k;
+            if (!open || acc + (e - b) > target + target / 10) {
+                ++g;
+                acc = 0;
+                open = true;
+            }
+            acc += e - b;
+            for (int64_t i = b; i < e; ++i) part[i] = g;
+        }
+    }
+    return g + 1;
+}
+
+// Above this many rows only the full set of parts is considered: the LDS
+// leaves at most a factor of two, worth a few percent (1000^2 ILU(0) 437 us
+// on 128 parts, 460 on 256), and the estimate would cost setup time.
+constexpr int32_t kEstimateRows = 500000;
+
 // System queue: every column becomes a row of its system's LDS ring, which
 // holds the last D+1 levels of the system (D = the largest level distance of
 // a dependency in it) in D+1 slots of W rows (W = its widest level): a value
@@ -891,7 +1041,9 @@ void build_exec(TriHost &t, const Csr &a, const Tune &tune, const DeviceShape &d
     const bool want_df = kind == HEC_SCHED_OWNER_PERSISTENT && (tune.variant == 4 || tune.variant == 6);
     const bool queue = want_df && tune.variant == 6;
     const int32_t df_waves = std::max(1, tune.block_threads / 64);
+    const int32_t w0 = h.w;  // ELL width of the layout
     std::vector<std::vector<int32_t>> run_wave;  // dataflow: wavefront of each run
+    int32_t accept = 0;
 
     // 1. device-row order and owner of each row
     ex.xord.resize(n);
@@ -975,31 +1127,99 @@ void build_exec(TriHost &t, const Csr &a, const Tune &tune, const DeviceShape &d
         parts = std::max(1, std::min(parts, std::max(1, n)));
         std::vector<int32_t> part_of;
         int32_t gx = 0, gy = 0, gz = 0;
-        const bool grid = !queue && (tune.partition == 0 || tune.partition == 3) && detect_grid(a, gx, gy, gz);
-        auto contiguous = [&]() {
+        const bool shared = tune.choose_parts && tune.share_part;
+        const bool grid = !queue && !shared && (tune.partition == 0 || tune.partition == 3) && detect_grid(a, gx, gy, gz);
+        auto contiguous = [&](int32_t count) {
             std::vector<int32_t> po(n);
-            for (int32_t g = 0; g < parts; ++g) {
-                int32_t qb = (int32_t)((int64_t)n * g / parts), qe = (int32_t)((int64_t)n * (g + 1) / parts);
+            for (int32_t g = 0; g < count; ++g) {
+                int32_t qb = (int32_t)((int64_t)n * g / count), qe = (int32_t)((int64_t)n * (g + 1) / count);
                 for (int32_t q = qb; q < qe; ++q) po[t.upper ? n - 1 - q : q] = g;
             }
             return po;
         };
-        if (queue) {
-            part_of = queue_parts(a, t.upper, lv, sys_ptr, tune, dev, t.dt, parts);
-        } else if (grid) {
-            part_of = grid_parts(n, gx, gy, gz, parts);
+        auto full_set = [&]() {
+            if (!grid) return contiguous(parts);
+            std::vector<int32_t> po = grid_parts(n, gx, gy, gz, parts);
             if (tune.partition == 0) {
                 // automatic: grid blocks unless contiguous ranges put fewer
                 // workgroup handoffs on the longest dependency chain (fill-in
                 // can make chains wander across block faces)
-                std::vector<int32_t> po = contiguous();
-                if (critical_hops(a, t.upper, po) < critical_hops(a, t.upper, part_of)) part_of.swap(po);
+                std::vector<int32_t> pc = contiguous(parts);
+                if (critical_hops(a, t.upper, pc) < critical_hops(a, t.upper, po)) po.swap(pc);
             }
+            return po;
+        };
+        const bool choose = tune.choose_parts && want_df && !queue && tune.partition == 0 && tune.part_rows == 0 &&
+                            tune.num_groups == 0;
+        const size_t ts = t.dt == HEC_F64 ? 8 : 4;
+        const size_t lds_cap = dev.lds > 0 ? (size_t)dev.lds : 163840;
+        const bool blocks = sys_ptr && sys_ptr->size() > 2;
+        if (queue) {
+            part_of = queue_parts(a, t.upper, lv, sys_ptr, tune, dev, t.dt, parts);
+        } else if (choose && tune.share_part) {
+            part_of = *tune.share_part;
+            parts = tune.share_parts;
+            accept = tune.share_accept;
+        } else if (choose && n > 0 && n <= kEstimateRows) {
+            double best = INFINITY;
+            int32_t best_parts = 0;
+            auto consider = [&](std::vector<int32_t> &&po, int32_t count) {
+                if (count < 1 || count > parts) return;
+                const PartEstimate e = estimate_parts(a, t.upper, lv, po, count, df_waves, w0, R, ts, lds_cap, best);
+                if (e.us < best) {
+                    best = e.us;
+                    best_parts = count;
+                    part_of.swap(po);
+                }
+            };
+            const int64_t least = std::max<int64_t>(1, (int64_t)((2 * (size_t)n * R * ts + lds_cap - 1) / lds_cap));
+            std::vector<int32_t> counts;
+            int64_t p2 = 1;
+            while (p2 < least) p2 *= 2;
+            for (int64_t c : {least, least + 1})
+                if (c < p2 && c <= parts) counts.push_back((int32_t)c);
+            for (int64_t c = p2; c <= 8 * p2 && c < parts; c *= 2) counts.push_back((int32_t)c);
+            if (8 * p2 >= parts) counts.push_back(parts);
+            std::vector<int32_t> po;
+            for (int32_t c : counts) {
+                if (blocks) {
+                    const int32_t k = block_parts(n, *sys_ptr, c, po);
+                    consider(std::move(po), k);
+                }
+                if (grid) consider(grid_parts(n, gx, gy, gz, c), c);
+                consider(contiguous(c), c);
+            }
+            if (best_parts == 0) fail(HEC_ERR_CAPACITY, "dataflow kernel: no parts fit the LDS");
+            if (best_parts < parts) {
+                // calls with more right-hand sides than max_nrhs run in
+                // groups of columns as far as one part per compute unit
+                // would take them at once
+                const PartEstimate e = estimate_parts(a, t.upper, lv, full_set(), parts, df_waves, w0, R, ts, SIZE_MAX, INFINITY);
+                int32_t r = 64 / std::max(1, e.longest);
+                while (r > R && dataflow_lds_bytes(e.rows, e.ints, r, ts) > lds_cap) --r;
+                accept = r;
+            }
+            parts = best_parts;
+        } else if (grid) {
+            part_of = full_set();
         } else if (tune.partition != 2) {
-            part_of = contiguous();
+            part_of = contiguous(parts);
+            if (choose && blocks) {
+                // ranges that end at block boundaries need no handoffs where
+                // blocks fit; taken when they fit the LDS as well
+                std::vector<int32_t> po;
+                const int32_t k = block_parts(n, *sys_ptr, parts, po);
+                if (k <= parts && critical_hops(a, t.upper, po) < critical_hops(a, t.upper, part_of) &&
+                    estimate_parts(a, t.upper, lv, po, k, df_waves, w0, R, ts, lds_cap, INFINITY).us < INFINITY) {
+                    part_of.swap(po);
+                    parts = k;
+                }
+            }
         } else {
             part_of = bisect_parts(a, parts);
         }
+        ex.part = part_of;
+        ex.parts = parts;
         std::vector<std::vector<int32_t>> members(parts);
         for (int32_t q = 0; q < n; ++q) {
             const int32_t i = t.upper ? n - 1 - q : q;  // problem order
@@ -1103,6 +1323,7 @@ void build_exec(TriHost &t, const Csr &a, const Tune &tune, const DeviceShape &d
     // 3. schedule
     ex.sched = Schedule();
     ex.sched.kind = kind;
+    ex.sched.df_accept = accept;
     if (sysq) {
         build_sysq(ex, lv, sq_sys, sq_lvrow, sq_lvp, R, t.dt == HEC_F64 ? 8 : 4, dev);
         return;
@@ -1223,8 +1444,11 @@ TriHost analyze(const Csr &a, bool upper, bool unit, hec_dtype_t dt, const Tune 
     if (tu.schedule == HEC_SCHED_OWNER_PERSISTENT && tu.variant == 0) {
         Tune d = tu;
         d.variant = 4;
+        d.choose_parts = auto_sched;
         const bool df_ok = d.block_threads <= 384 && d.max_nrhs <= 64 && d.ell_width <= 16;
-        if (df_ok) {
+        // the parts of the other triangle first, if there is one
+        for (int pass = d.share_part && auto_sched ? 0 : 1; df_ok && pass < 2; ++pass) {
+            if (pass == 1) d.share_part = nullptr;
             try {
                 attempt(d);
                 return t;

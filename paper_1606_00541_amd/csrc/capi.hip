@@ -157,6 +157,7 @@ void upload_tri(DevTri &d, const TriHost &t, int32_t max_nrhs)
             d.df_rows = s.df_rows;
             d.df_ints = s.df_ints;
             d.df_waves = s.df_waves;
+            d.df_accept = s.df_accept;
             d.queue = s.queue;
             upload(d.wave_ptr, s.wave_ptr);
             upload(d.step_pack, s.step_pack);
@@ -384,7 +385,14 @@ void build_ilu(ilu_s &f, const Csr &L, const Csr &U, hec_dtype_t fdt, const Tune
     f.n = L.n;
     f.fdt = fdt;
     build_plan(f.L, L, false, true, fdt, tu, blocks);
-    build_plan(f.U, U, true, false, fdt, tu, blocks);
+    Tune tun = tu;
+    if (f.L.h.ex.sched.dataflow && !f.L.h.ex.sched.queue) {
+        // U on L's parts: both then finish and start a part on the same workgroup
+        tun.share_part = &f.L.h.ex.part;
+        tun.share_parts = f.L.h.ex.parts;
+        tun.share_accept = f.L.h.ex.sched.df_accept;
+    }
+    build_plan(f.U, U, true, false, fdt, tun, blocks);
     if (!tu.host_only) {
         const int32_t n = L.n;
         std::vector<int32_t> q(n);

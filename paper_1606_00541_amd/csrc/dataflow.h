@@ -210,7 +210,7 @@ __device__ __forceinline__ void df_fill_b(const TriArgs &a, const DfPart<T> &p, 
 #pragma unroll
         for (int u = 0; u < kDfFill; ++u) {
             const int t = min(t0 + u * nt, cnt - 1);
-            bv[u] = bin[(size_t)gi[u] * R + (R1 ? 0 : t % R)];
+            bv[u] = bin[(size_t)gi[u] * a.ldr + (a.k0 + (R1 ? 0 : t % R))];
             if (!UNIT) dd[u] = static_cast<const T *>(a.dinv)[p.lo + (R1 ? t : t / R)];
         }
         if (t0 + kDfFill * nt < cnt) index(t0 + kDfFill * nt);
@@ -502,11 +502,11 @@ template <typename T> __device__ __forceinline__ void df_store(const TriArgs &a,
         const int q = t / R, k = t - q * R;
         const int x = p.lo + q;
         const T v = p.xl[t];
-        if (a.write_xw) static_cast<T *>(a.xw)[(size_t)x * R + k] = v;
+        if (a.write_xw) static_cast<T *>(a.xw)[(size_t)x * a.ldr + a.k0 + k] = v;
         if (a.xout) {
             const int d = a.scatter[x];  // negative: the row is not written (RAS overlap rows)
             if (d >= 0) {
-                const size_t dst = (size_t)d * R + k;
+                const size_t dst = (size_t)d * a.ldr + a.k0 + k;
                 if (a.out_f64) static_cast<double *>(a.xout)[dst] = static_cast<double>(v);
                 else static_cast<float *>(a.xout)[dst] = static_cast<float>(v);
             }

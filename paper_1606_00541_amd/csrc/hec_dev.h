@@ -83,6 +83,7 @@ constexpr unsigned int kSentinel32 = 0x7FA0BEEFu;
 // Kernel arguments of one triangular solve launch (passed by value).
 struct TriArgs {
     int32_t n, w, ld, R;
+    int32_t ldr, k0;             // dataflow kernel: right-hand sides of a vector's row, the first of this launch
     const int32_t *ell_col;
     const void *ell_val;
     const int32_t *tail_ptr, *tail_col;
@@ -158,6 +159,7 @@ struct DevTri {
     int32_t df_waves = 0;          // compute wavefronts per group (block = 64 * df_waves + 128)
     int32_t df_rows = 0, df_ints = 0;
     int32_t df_step_rows = 0;      // longest step (one wavefront covers step rows x nrhs)
+    int32_t df_accept = 0;         // right-hand sides taken in groups of columns
     bool queue = false;            // dataflow parts taken from a counter (more parts than workgroups)
     bool sysq = false, sq_global = false;  // system queue kernel; some dependencies read from xw
     int32_t sq_lds_rows = 0;

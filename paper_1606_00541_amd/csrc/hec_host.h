@@ -92,6 +92,7 @@ struct Schedule {
     int32_t df_ints = 0;             // max over groups of imports + exports + steps + kDataflowPad
     std::vector<int32_t> step_pack;  // per step: first window row | 16 (rows - 1) << 16
     int32_t df_waves = 0;            // compute wavefronts per group
+    int32_t df_accept = 0;           // right-hand sides accepted in groups of columns beyond what fits at once
     std::vector<int32_t> wave_ptr;   // [groups*df_waves+1]: steps of wavefront w of group g
     // queue mode: `groups` parts, more than the workgroups that run them; the
     // parts are numbered so that every part reads only lower-numbered ones
@@ -126,6 +127,8 @@ struct ExecHost {
     std::vector<double> dinv;                 // empty for a unit diagonal
     std::vector<int32_t> levelptr;            // level-launch schedule: device-row bounds per level
     Schedule sched;
+    std::vector<int32_t> part;   // owner schedule: original row -> part (before workgroups are numbered)
+    int32_t parts = 0;
 };
 
 struct TriHost {
@@ -154,6 +157,11 @@ struct Tune {
     int32_t partition = 0;   // owner parts: 0 auto (grid blocks, else contiguous), 1 contiguous, 2 bisection, 3 grid
     int32_t variant = 0;     // persistent kernel: 0 auto, 1 generic, 2 owner chunked, 3 owner split waves,
                              // 4 owner dataflow
+    // set by the analysis itself:
+    bool choose_parts = false;  // dataflow kernel under an automatic schedule: pick the parts by estimate
+    // parts of another triangle over the same rows (original row -> part), to be used as they are
+    const std::vector<int32_t> *share_part = nullptr;
+    int32_t share_parts = 0, share_accept = 0;
 };
 // LDS bytes of the dataflow owner kernel: `rows` value rows (x window, b
 // window and imports) of R right-hand sides, then `ints` int32 entries

@@ -1248,6 +1248,50 @@ SqKernel sysq_pipe_kernel(int w, const std::vector<int32_t> &widths, int G, int 
     return w <= 4 ? sysq_pipe_width<T, TIn, 8, 4>(many) : sysq_pipe_width<T, TIn, 8, 8>(many);
 }
 
+// Right-hand sides one launch of a dataflow plan holds: a wavefront covers the
+// longest step, the LDS every part.
+int32_t dataflow_columns(const DevTri &d)
+{
+    const size_t ts = d.dt == HEC_F64 ? 8 : 4;
+    int32_t r = std::max(1, 64 / std::max(1, d.df_step_rows));
+    while (r > 1 && dataflow_lds_bytes(d.df_rows, d.df_ints, r, ts) > (size_t)device_max_lds()) --r;
+    return r;
+}
+
+template <typename T> void launch_dataflow(DevTri &d, TriArgs a, hipStream_t st)
+{
+    // the plan's columns name group-local imports: only this kernel reads them
+    const bool one = a.R == 1, f64 = sizeof(T) == 8;
+    OwnerKernel k = nullptr;
+    if (a.trace)
+        k = f64 ? (one ? df_f64_one_tr : df_f64_many_tr)(d.w, d.unit, d.has_tail)
+                : (one ? df_f32_one_tr : df_f32_many_tr)(d.w, d.unit, d.has_tail);
+    else
+        k = f64 ? (one ? df_f64_one : df_f64_many)(d.w, d.unit, d.has_tail)
+                : (one ? df_f32_one : df_f32_many)(d.w, d.unit, d.has_tail);
+    if (!k) fail(HEC_ERR_INVALID_ARG, "internal: dataflow plan with an unsupported ELL width");
+    size_t lds = dataflow_lds_bytes(d.df_rows, d.df_ints, a.R, sizeof(T));
+    if (a.trace) lds += 16 + 16 * (size_t)std::min(d.df_ints, a.trace_stride);  // per-step clocks
+    a.lds_ctl = (int32_t)lds - kDataflowCtlBytes;
+    const int block = 64 * d.df_waves + 128;
+    if (block > dataflow_max_block(d.w)) fail(HEC_ERR_INVALID_ARG, "dataflow kernel: block too large");
+    if (lds > (size_t)device_max_lds())
+        fail(HEC_ERR_CAPACITY, "dataflow kernel: LDS need exceeds the device limit at this nrhs");
+    const int32_t cap = capacity_of((const void *)k, block, lds, true);
+    a.nparts = d.groups;
+    a.queue = d.queue ? 1 : 0;
+    int32_t grid = d.groups;
+    if (d.queue) {
+        // parts wait only on lower-numbered parts, which running
+        // workgroups hold: any grid size makes progress
+        grid = std::max(1, std::min(d.groups, cap));
+    } else if (cap < d.groups) {
+        fail(HEC_ERR_CAPACITY, "dataflow grid exceeds the co-resident capacity");
+    }
+    hipLaunchKernelGGL(k, dim3(grid), dim3(block), lds, st, a);
+    hip_check(hipGetLastError(), "k_dataflow launch");
+}
+
 template <typename T, typename TIn, typename TOut>
 void launch_typed(DevTri &d, TriArgs a, hipStream_t st)
 {
@@ -1311,40 +1355,19 @@ void launch_typed(DevTri &d, TriArgs a, hipStream_t st)
     }
     if (d.dataflow) {
         // the plan's columns name group-local imports: only this kernel reads them
-        const bool one = a.R == 1, f64 = sizeof(T) == 8;
-        OwnerKernel k = nullptr;
-        if (a.trace)
-            k = f64 ? (one ? df_f64_one_tr : df_f64_many_tr)(d.w, d.unit, d.has_tail)
-                    : (one ? df_f32_one_tr : df_f32_many_tr)(d.w, d.unit, d.has_tail);
-        else
-            k = f64 ? (one ? df_f64_one : df_f64_many)(d.w, d.unit, d.has_tail)
-                    : (one ? df_f32_one : df_f32_many)(d.w, d.unit, d.has_tail);
-        if (!k) fail(HEC_ERR_INVALID_ARG, "internal: dataflow plan with an unsupported ELL width");
-        if ((int64_t)d.df_step_rows * a.R > 64)
-            fail(HEC_ERR_INVALID_ARG, "dataflow plan: nrhs exceeds the plan's max_nrhs (steps are sized for it)");
-        size_t lds = dataflow_lds_bytes(d.df_rows, d.df_ints, a.R, sizeof(T));
-        a.lds_ctl = (int32_t)lds - kDataflowCtlBytes;
-        if (a.trace) {  // per-step clocks, before the control words
-            lds += 16 + 16 * (size_t)std::min(d.df_ints, a.trace_stride);
-            a.lds_ctl = (int32_t)lds - kDataflowCtlBytes;
-        }
-        const int block = 64 * d.df_waves + 128;
-        if (block > dataflow_max_block(d.w)) fail(HEC_ERR_INVALID_ARG, "dataflow kernel: block too large");
-        if (lds > (size_t)device_max_lds())
+        // one launch, or (a plan whose automatic parts hold fewer right-hand
+        // sides than one part per compute unit would) one per group of columns
+        a.ldr = a.R;
+        const int32_t all = a.R, most = dataflow_columns(d);
+        if (all > most && all > d.df_accept) {
+            if ((int64_t)d.df_step_rows * all > 64)
+                fail(HEC_ERR_INVALID_ARG, "dataflow plan: nrhs exceeds the plan's max_nrhs (steps are sized for it)");
             fail(HEC_ERR_CAPACITY, "dataflow kernel: LDS need exceeds the device limit at this nrhs");
-        const int32_t cap = capacity_of((const void *)k, block, lds, true);
-        a.nparts = d.groups;
-        a.queue = d.queue ? 1 : 0;
-        int32_t grid = d.groups;
-        if (d.queue) {
-            // parts wait only on lower-numbered parts, which running
-            // workgroups hold: any grid size makes progress
-            grid = std::max(1, std::min(d.groups, cap));
-        } else if (cap < d.groups) {
-            fail(HEC_ERR_CAPACITY, "dataflow grid exceeds the co-resident capacity");
         }
-        hipLaunchKernelGGL(k, dim3(grid), dim3(block), lds, st, a);
-        hip_check(hipGetLastError(), "k_dataflow launch");
+        for (a.k0 = 0; a.k0 < all; a.k0 += a.R) {
+            a.R = std::min(most, all - a.k0);
+            launch_dataflow<T>(d, a, st);
+        }
         return;
     }
     if (d.kind == HEC_SCHED_OWNER_PERSISTENT && d.variant == 3 && a.R == 1 && !d.has_tail && d.max_lanes_one &&
@@ -1494,8 +1517,10 @@ void fill_sentinel(void *p, size_t count, hec_dtype_t dt)
     hip_check(hipDeviceSynchronize(), "hipDeviceSynchronize");
 }
 
-void launch_tri(DevTri &d, const void *bin, hec_dtype_t in_dt, const int32_t *gather, void *xw, void *xout,
-                hec_dtype_t out_dt, const int32_t *scatter, int32_t R, hipStream_t st)
+namespace {
+
+TriArgs tri_args(const DevTri &d, const void *bin, hec_dtype_t in_dt, const int32_t *gather, void *xw, void *xout,
+                 hec_dtype_t out_dt, const int32_t *scatter, int32_t R)
 {
     if (R > d.ws_R) fail(HEC_ERR_INVALID_ARG, "internal: workspace narrower than nrhs");
     TriArgs a{};
@@ -1548,6 +1573,15 @@ void launch_tri(DevTri &d, const void *bin, hec_dtype_t in_dt, const int32_t *ga
     a.sq_keep = d.sq_keep.as<int8_t>();
     a.in_f64 = in_dt == HEC_F64 ? 1 : 0;
     a.out_f64 = out_dt == HEC_F64 ? 1 : 0;
+    return a;
+}
+
+}  // namespace
+
+void launch_tri(DevTri &d, const void *bin, hec_dtype_t in_dt, const int32_t *gather, void *xw, void *xout,
+                hec_dtype_t out_dt, const int32_t *scatter, int32_t R, hipStream_t st)
+{
+    const TriArgs a = tri_args(d, bin, in_dt, gather, xw, xout, out_dt, scatter, R);
     if (d.dt == HEC_F64) launch_in<double>(d, a, in_dt, out_dt, st);
     else launch_in<float>(d, a, in_dt, out_dt, st);
 }
