@@ -36,6 +36,9 @@ def _hip_units():
                 units.append(("dataflow_inst.hip", name + ".o",
                               ["-DHEC_DF_T=" + typ, "-DHEC_DF_R1=" + one, "-DHEC_DF_TRACE=" + trace,
                                "-DHEC_DF_NAME=" + name]))
+            name = "lu_%s_%s" % (t, r)
+            units.append(("dataflow_inst.hip", name + ".o",
+                          ["-DHEC_DF_T=" + typ, "-DHEC_DF_R1=" + one, "-DHEC_DF_LU=1", "-DHEC_DF_NAME=" + name]))
     return units
 
 COMMON = ["-O3", "-fPIC", "-std=c++17", "-Wall", "-I" + os.path.join(ROOT, "include"), "-I" + CSRC]

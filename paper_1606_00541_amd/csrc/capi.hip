@@ -256,6 +256,7 @@ struct ilu_s {
     Csr Lf, Uf;                  // host FP64 factors
     tri_plan_s L, U;
     DevMem qmap;                 // U device row -> L device row of the same original row
+    bool lu_shared = false;      // both plans' parts hold the same rows: one launch runs both
     std::vector<int32_t> sys_ptr;
     hec_ilu_kind_t kind = HEC_ILU0;
     std::unique_ptr<DevRefactor> rf;  // device refactorization data (built on first use)
@@ -401,6 +402,12 @@ void build_ilu(ilu_s &f, const Csr &L, const Csr &U, hec_dtype_t fdt, const Tune
             q[x] = f.L.h.ex.xinv[f.L.h.lev.iperm[i]];
         }
         upload(f.qmap, q);
+        const ExecHost &el = f.L.h.ex, &eu = f.U.h.ex;
+        bool same = el.sched.dataflow && eu.sched.dataflow && !el.sched.queue && !eu.sched.queue && el.w == eu.w &&
+                    el.tail_ptr.empty() && eu.tail_ptr.empty() && el.sched.groups == eu.sched.groups &&
+                    el.sched.df_waves == eu.sched.df_waves;
+        for (int32_t x = 0; same && x < n; ++x) same = eu.owner[x] == el.owner[q[x]];
+        f.lu_shared = same;
     }
 }
 
@@ -416,9 +423,8 @@ void ilu_apply_impl(ilu_s *f, const void *r, void *z, int32_t nrhs, hec_dtype_t 
     ensure_workspace(f->L.d, nrhs);
     ensure_workspace(f->U.d, nrhs);
     f->L.d.act = f->U.d.act = act;
-    launch_tri(f->L.d, r, vdt, f->L.d.orig.as<int32_t>(), f->L.d.xw.p, nullptr, vdt, nullptr, nrhs, st);
-    launch_tri(f->U.d, f->L.d.xw.p, f->fdt, f->qmap.as<int32_t>(), f->U.d.xw.p, z, vdt,
-               f->U.d.orig.as<int32_t>(), nrhs, st);
+    launch_lu(f->L.d, f->U.d, f->lu_shared, r, vdt, f->L.d.orig.as<int32_t>(), f->L.d.xw.p, f->qmap.as<int32_t>(),
+              f->U.d.xw.p, z, vdt, f->U.d.orig.as<int32_t>(), nrhs, st);
     f->L.d.act = f->U.d.act = nullptr;
 }
 
@@ -573,9 +579,8 @@ void ras_apply_impl(ras_s *s, const double *r, double *z, int32_t nrhs, hipStrea
     ensure_workspace(f.U.d, nrhs);
     // restriction fused into L's gather, restricted prolongation into U's scatter
     f.L.d.act = f.U.d.act = act;
-    launch_tri(f.L.d, r, HEC_F64, s->gather_L.as<int32_t>(), f.L.d.xw.p, nullptr, HEC_F64, nullptr, nrhs, st);
-    launch_tri(f.U.d, f.L.d.xw.p, f.fdt, f.qmap.as<int32_t>(), f.U.d.xw.p, z, HEC_F64,
-               s->scatter_U.as<int32_t>(), nrhs, st);
+    launch_lu(f.L.d, f.U.d, f.lu_shared, r, HEC_F64, s->gather_L.as<int32_t>(), f.L.d.xw.p, f.qmap.as<int32_t>(),
+              f.U.d.xw.p, z, HEC_F64, s->scatter_U.as<int32_t>(), nrhs, st);
     f.L.d.act = f.U.d.act = nullptr;
 }
 
@@ -877,8 +882,8 @@ hec_status_t ilu_apply_noalloc(ilu_t f, const void *r, void *z, int32_t nrhs, he
         void *y = base;          // L's device-order output, U's input
         void *uw = base + part;  // U's own workspace (kernels that keep the solution in global memory)
         check_device_error(f->L.d, f->U.d);
-        launch_tri(f->L.d, r, vdt, f->L.d.orig.as<int32_t>(), y, nullptr, vdt, nullptr, nrhs, st);
-        launch_tri(f->U.d, y, f->fdt, f->qmap.as<int32_t>(), uw, z, vdt, f->U.d.orig.as<int32_t>(), nrhs, st);
+        launch_lu(f->L.d, f->U.d, f->lu_shared, r, vdt, f->L.d.orig.as<int32_t>(), y, f->qmap.as<int32_t>(), uw, z, vdt,
+                  f->U.d.orig.as<int32_t>(), nrhs, st);
     });
 }
 

@@ -127,16 +127,20 @@ template <typename T> struct DfPart {
 
 template <typename T> __device__ __forceinline__ DfPart<T> df_part(const TriArgs &a, int g, int R, unsigned char *smem)
 {
+    // uniform values as scalars: behind a store the compiler reads them with
+    // vector loads, and a buffer load whose offset it cannot prove uniform
+    // becomes a loop over the lanes
+    auto uni = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
     DfPart<T> p;
-    p.g = g;
-    p.lo = a.window[2 * g];
-    p.win = a.window[2 * g + 1] - p.lo;
-    p.i0 = a.imp_ptr[g];
-    p.nimp = a.imp_ptr[g + 1] - p.i0;
-    p.e0 = a.exp_ptr[g];
-    p.nex = a.exp_ptr[g + 1] - p.e0;
-    p.s0 = a.step_ptr[g];
-    p.ns = a.step_ptr[g + 1] - p.s0;
+    p.g = uni(g);
+    p.lo = uni(a.window[2 * g]);
+    p.win = uni(a.window[2 * g + 1]) - p.lo;
+    p.i0 = uni(a.imp_ptr[g]);
+    p.nimp = uni(a.imp_ptr[g + 1]) - p.i0;
+    p.e0 = uni(a.exp_ptr[g]);
+    p.nex = uni(a.exp_ptr[g + 1]) - p.e0;
+    p.s0 = uni(a.step_ptr[g]);
+    p.ns = uni(a.step_ptr[g + 1]) - p.s0;
     p.xl = reinterpret_cast<T *>(smem);
     p.bl = p.xl + (size_t)p.win * R;
     p.im = p.bl + (size_t)p.win * R;
@@ -154,7 +158,8 @@ template <typename T> __device__ __forceinline__ DfPart<T> df_part(const TriArgs
 // constant).
 struct DfCtl {
     unsigned epoch;
-    int abort, part, pad;
+    int abort, part;
+    unsigned epoch2;  // of the second triangle
 };
 
 constexpr int kDfFill = 8;  // independent loads a thread keeps in flight while LDS is filled
@@ -279,8 +284,8 @@ __device__ __forceinline__ void df_sweep(const TriArgs &a, const DfPart<T> &pt, 
     };
     int j = 0, jend = 0;
     if (wv < nwc) {
-        j = a.wave_ptr[pt.g * nwc + wv] - pt.s0;
-        jend = a.wave_ptr[pt.g * nwc + wv + 1] - pt.s0;
+        j = __builtin_amdgcn_readfirstlane(a.wave_ptr[pt.g * nwc + wv]) - pt.s0;
+        jend = __builtin_amdgcn_readfirstlane(a.wave_ptr[pt.g * nwc + wv + 1]) - pt.s0;
         if (j < jend) {
             const int tab = a.step_pack[pt.s0 + min(j + lane, jend - 1)];
 #pragma unroll
@@ -582,6 +587,79 @@ __global__ void __launch_bounds__(512) k_dataflow(TriArgs a)
         if (ctl->abort) break;
     }
     if (tid == 0) df_leave(a, ctl->epoch);
+}
+
+// U's right-hand side from L's solution, which is still in this workgroup's
+// LDS: row t of U's part is row gather[t] - lo of L's (the parts hold the same
+// rows).  Writes the b area, which L no longer needs, then the caller clears
+// the x area the values came from.
+template <typename T, bool R1>
+__device__ __forceinline__ void df_fill_y(const TriArgs &u, const DfPart<T> &p, int R, int lo)
+{
+    const int tid = threadIdx.x, nt = blockDim.x, cnt = p.win * R;
+    for (int t0 = tid; t0 < cnt; t0 += kDfFill * nt) {
+        int gi[kDfFill];
+        T dd[kDfFill];
+#pragma unroll
+        for (int v = 0; v < kDfFill; ++v) {
+            const int t = min(t0 + v * nt, cnt - 1), x = p.lo + (R1 ? t : t / R);
+            gi[v] = u.gather[x];
+            dd[v] = static_cast<const T *>(u.dinv)[x];
+        }
+#pragma unroll
+        for (int v = 0; v < kDfFill; ++v) {
+            const int t = t0 + v * nt;
+            if (t < cnt) p.bl[t] = scale_rhs(p.xl[(gi[v] - lo) * R + (R1 ? 0 : t % R)], dd[v]);
+        }
+    }
+}
+
+// Both triangles of an ILU application in one launch, for plans whose parts
+// hold the same rows (same workgroup), with one ELL width and no CSR tail: L,
+// then U on the same workgroup with L's solution taken from LDS.  Saves the
+// second launch, the drain of the first (a workgroup starts U when its own
+// part of L is done; U waits only on U), the round trip of y through memory
+// and the two dependent gathers of it.  L's values never reach memory.
+template <typename T, int W, bool R1>
+__global__ void __launch_bounds__(512) k_dataflow_lu(TriArgs l, TriArgs u)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    DfCtl *ctl = reinterpret_cast<DfCtl *>(smem + l.lds_ctl);
+    const int R = R1 ? 1 : l.R, g = blockIdx.x;
+    if (threadIdx.x == 0) {
+        ctl->epoch = __hip_atomic_load(l.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        ctl->epoch2 = __hip_atomic_load(u.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        ctl->abort = 0;
+    }
+    __syncthreads();
+    unsigned long long t_fill = 0;
+    auto half = [&](const TriArgs &a, unsigned par) {
+        return static_cast<T *>(a.mbox) + (par & 1u ? (size_t)a.nexp * a.mbox_stride : 0);
+    };
+    const DfPart<T> pl = df_part<T>(l, g, R, smem);
+    df_sweep<T, W, false, R1, false>(l, pl, R, half(l, ctl->epoch), &ctl->abort, t_fill, [&]() {
+        if (l.in_f64) df_fill_b<T, true, R1>(l, pl, R, static_cast<const double *>(l.bin));
+        else df_fill_b<T, true, R1>(l, pl, R, static_cast<const float *>(l.bin));
+        df_fill_lists(l, pl, R, half(l, ctl->epoch + 1u));
+    });
+    if (!ctl->abort) {
+        const DfPart<T> pu = df_part<T>(u, g, R, smem);
+        df_sweep<T, W, false, R1, false>(u, pu, R, half(u, ctl->epoch2), &ctl->abort, t_fill, [&]() {
+            df_fill_y<T, R1>(u, pu, R, pl.lo);
+            __syncthreads();
+            df_fill_lists(u, pu, R, half(u, ctl->epoch2 + 1u));
+        });
+        if (!ctl->abort) df_store(u, pu, R);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        if (ctl->abort == 2) {  // a wait gave up: tell the other workgroups, in either triangle
+            for (int *e : {l.err_dev, u.err_dev}) __hip_atomic_store(e, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            for (int *e : {l.err_host, u.err_host}) __hip_atomic_store(e, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        }
+        df_leave(l, ctl->epoch);
+        df_leave(u, ctl->epoch2);
+    }
 }
 
 }  // namespace hec

@@ -135,6 +135,13 @@ OwnerKernel df_f64_many_tr(int w, bool unit, bool tail);
 OwnerKernel df_f32_one_tr(int w, bool unit, bool tail);
 OwnerKernel df_f32_many_tr(int w, bool unit, bool tail);
 
+// Both triangles of an ILU application in one launch.
+using LuKernel = void (*)(TriArgs, TriArgs);
+LuKernel lu_f64_one(int w);
+LuKernel lu_f64_many(int w);
+LuKernel lu_f32_one(int w);
+LuKernel lu_f32_many(int w);
+
 // Polls of a bounded device-side wait before it is declared hung (a plan may
 // set its own, tri_plan_set_wait_limit); at most kMaxSpin so that the
 // sixteen-fold limit of LDS polls stays within 32 bits.
@@ -225,6 +232,12 @@ int32_t device_cus();
 // `xout` (type out_dt) through `scatter`.
 void launch_tri(DevTri &d, const void *bin, hec_dtype_t in_dt, const int32_t *gather, void *xw,
                 void *xout, hec_dtype_t out_dt, const int32_t *scatter, int32_t R, hipStream_t st);
+// L then U of an ILU application: one launch when the plans allow it
+// (lu_shared), else two with y in `y`, L's device order.  `qmap`: U device row
+// -> L device row; `uw`: U's own workspace.
+void launch_lu(DevTri &L, DevTri &U, bool lu_shared, const void *r, hec_dtype_t in_dt, const int32_t *gather_l, void *y,
+               const int32_t *qmap, void *uw, void *z, hec_dtype_t out_dt, const int32_t *scatter_u, int32_t R,
+               hipStream_t st);
 // Throws HEC_ERR_TIMEOUT if a persistent launch of this plan aborted a wait.
 void check_device_error(const DevTri &d);
 // Both plans of a preconditioner: clears both flags, throws once.

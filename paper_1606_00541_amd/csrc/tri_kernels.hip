@@ -1586,4 +1586,34 @@ void launch_tri(DevTri &d, const void *bin, hec_dtype_t in_dt, const int32_t *ga
     else launch_in<float>(d, a, in_dt, out_dt, st);
 }
 
+void launch_lu(DevTri &L, DevTri &U, bool lu_shared, const void *r, hec_dtype_t in_dt, const int32_t *gather_l, void *y,
+               const int32_t *qmap, void *uw, void *z, hec_dtype_t out_dt, const int32_t *scatter_u, int32_t R,
+               hipStream_t st)
+{
+    const int32_t most = lu_shared ? std::min(dataflow_columns(L), dataflow_columns(U)) : 0;
+    if (lu_shared && L.n > 0 && !L.trace && !U.trace && (R <= most || (R <= L.df_accept && R <= U.df_accept))) {
+        const bool f64 = L.dt == HEC_F64;
+        TriArgs a = tri_args(L, r, in_dt, gather_l, nullptr, nullptr, in_dt, nullptr, R);
+        TriArgs b = tri_args(U, nullptr, L.dt, qmap, nullptr, z, out_dt, scatter_u, R);
+        a.ldr = b.ldr = R;
+        for (int32_t k0 = 0; k0 < R; k0 += most) {
+            a.k0 = b.k0 = k0;
+            a.R = b.R = std::min(most, R - k0);
+            LuKernel k = a.R == 1 ? (f64 ? lu_f64_one : lu_f32_one)(L.w) : (f64 ? lu_f64_many : lu_f32_many)(L.w);
+            const size_t ts = f64 ? 8 : 4;
+            const size_t lds = std::max(dataflow_lds_bytes(L.df_rows, L.df_ints, a.R, ts),
+                                        dataflow_lds_bytes(U.df_rows, U.df_ints, a.R, ts));
+            a.lds_ctl = b.lds_ctl = (int32_t)lds - kDataflowCtlBytes;
+            const int block = 64 * L.df_waves + 128;
+            if (capacity_of((const void *)k, block, lds, true) < L.groups)
+                fail(HEC_ERR_CAPACITY, "dataflow grid exceeds the co-resident capacity");
+            hipLaunchKernelGGL(k, dim3(L.groups), dim3(block), lds, st, a, b);
+            hip_check(hipGetLastError(), "k_dataflow_lu launch");
+        }
+        return;
+    }
+    launch_tri(L, r, in_dt, gather_l, y, nullptr, in_dt, nullptr, R, st);
+    launch_tri(U, y, L.dt, qmap, uw, z, out_dt, scatter_u, R, st);
+}
+
 }  // namespace hec
