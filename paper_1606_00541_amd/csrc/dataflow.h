@@ -9,9 +9,8 @@
 //                  sentinel, so a row starts as soon as its own inputs exist.
 //                  Compute waves issue no global stores, so their waits cover
 //                  loads only.
-//   import wave    polls the mailbox slots this group reads (lane l takes
-//                  imports l, l+64, ... in order of first use) and copies
-//                  each value into LDS when it arrives;
+//   import waves   poll the mailbox slots this group reads, in order of first
+//                  use, and copy each value into LDS when it arrives;
 //   export wave    watches the group's exported rows in LDS and writes each
 //                  one to its mailbox slot as soon as it is solved.
 // Any row waits only on rows of lower levels, and every wave handles its
@@ -75,11 +74,13 @@ template <typename T, int W> struct DfRec {
     static constexpr int ND = 4 * CH + RE;
     static constexpr int LOADS = CH + (RE > 0 ? 1 : 0);
     // register sets in rotation: as many as the vector-memory counter (63
-    // outstanding loads) and about 144 registers hold, at most 16
+    // outstanding loads) and about 144 registers hold, at most 8 (4 sets made
+    // 128^3 ILU(0) 6% slower, 6 to 16 were equal, and 16 made ILU(1) with four
+    // right-hand sides 12% slower than 8)
     static constexpr int byreg = 144 / ND < 3 ? 3 : 144 / ND;
     static constexpr int bycnt = 60 / LOADS + 1;
     static constexpr int k0 = byreg < bycnt ? byreg : bycnt;
-    static constexpr int K = k0 < 16 ? k0 : 16;
+    static constexpr int K = k0 < 8 ? k0 : 8;
     static_assert(K <= kDataflowPad, "descriptors are read K steps ahead");
 };
 
@@ -228,6 +229,70 @@ __device__ __forceinline__ void df_fill_b(const TriArgs &a, const DfPart<T> &p, 
     }
 }
 
+// Import wave `w` of `nw`: the part's imports in level order are dealt to
+// LOOK * nw slots of 64 lanes; a slot polls its next item until it arrives,
+// copies it into LDS and goes to its next one.  All of a wave's slots have a
+// load in flight together.  What bounds a handoff (1.2-1.4 us) and the rate of
+// a stream of them is the round: an uncached round trip plus the
+// instructions between two, so addresses are kept in registers and computed
+// only on arrival (against slots that searched the list for their next items
+// every round: 128^3 ILU(0) 308 -> 264 us, 100^3 211 -> 183 us per L+U).  Two
+// waves with one slot beat one wave with two (259 us, 181 us; ILU(1) of
+// 47x41x37 with four right-hand sides 270 -> 239 us) but for wide rows, whose
+// compute waves keep the LDS busy (100^3 ILUT, width 10: 1386 against 1455
+// us; two waves of two slots 1631 us).  A slot past its last item polls that
+// again.
+template <typename T, int LOOK, bool R1>
+__device__ __forceinline__ void df_import(const TriArgs &a, const DfPart<T> &pt, int R, T *mrd, int *s_abort, int w, int nw)
+{
+    const int items = pt.nimp * R, lane = threadIdx.x & 63;
+    if (items <= 64 * w) return;
+    T *im = pt.xl + 2 * pt.win * R;
+    int idx[LOOK];
+    unsigned at[LOOK];
+    auto place = [&](int i) {
+        i = min(i, items - 1);
+        const int q = R1 ? i : i / R, k = R1 ? 0 : i - q * R;
+        return (unsigned)pt.isl[q] * (unsigned)a.mbox_stride + (unsigned)k;
+    };
+#pragma unroll
+    for (int u = 0; u < LOOK; ++u) {
+        idx[u] = lane + 64 * (u * nw + w);
+        at[u] = place(idx[u]);
+    }
+    unsigned quiet = 0;  // rounds since the last arrival
+    for (;;) {
+        T v[LOOK];
+#pragma unroll
+        for (int u = 0; u < LOOK; ++u) v[u] = __hip_atomic_load(mrd + at[u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        bool fresh = false;
+#pragma unroll
+        for (int u = 0; u < LOOK; ++u) {
+            if (!is_sentinel(v[u]) && idx[u] < items) {
+                lds_put(im + idx[u], v[u]);
+                idx[u] += 64 * LOOK * nw;
+                at[u] = place(idx[u]);
+                fresh = true;
+            }
+        }
+        if (__ballot(fresh) != 0) {
+            int left = idx[0];
+#pragma unroll
+            for (int u = 1; u < LOOK; ++u) left = min(left, idx[u]);
+            if (__ballot(left < items) == 0) break;
+            quiet = 0;
+            continue;
+        }
+        if (++quiet > a.spin) {
+            lds_put(s_abort, 2);
+        } else if ((quiet & 255u) == 0 &&
+                   __hip_atomic_load(a.err_dev, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
+            lds_put(s_abort, 1);  // another workgroup gave up
+        }
+        if (((quiet & 15u) == 0 || quiet > a.spin) && lds_get(s_abort)) break;
+    }
+}
+
 // One part of one triangle, from filled LDS to solved LDS.  `fill` puts the
 // part's right-hand side and lists into LDS; the compute wavefronts issue
 // their first matrix loads before it.
@@ -240,7 +305,7 @@ __device__ __forceinline__ void df_sweep(const TriArgs &a, const DfPart<T> &pt, 
     const int tid = threadIdx.x, nt = blockDim.x;
     const int lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int nwc = (nt >> 6) - 2;
+    const int nwc = (nt >> 6) - 1 - a.imp_waves;
     const int lo = pt.lo;
     T *xl = pt.xl;
     // the lane's row and right-hand side within any step (lanes past a
@@ -410,89 +475,41 @@ __device__ __forceinline__ void df_sweep(const TriArgs &a, const DfPart<T> &pt, 
             for (int p = 0; p < K - 1; ++p)
                 if (rest > p && __ballot(aborted) == 0) step(p, false);
         }
-    } else if (wv == nwc) {
-        // import wave: lane l owns items l, l+64, l+128, ... (level order).
-        // Each poll round reads those of the lane's next kLook items that have
-        // not arrived yet, copies every new arrival into LDS, and moves the
-        // lane past the delivered prefix.  One round trip thus delivers
-        // several levels' worth of a lane's items without re-reading any.
-        constexpr int kLook = 2;
-        const int items = pt.nimp * R;
-        const int xoff = 2 * pt.win * R;
-        int it = lane;
-        unsigned got = 0;  // bit u: item it + 64 u already delivered
-        unsigned idle = 0;
-        while (__ballot(it < items) != 0) {
-            if (it < items) {
-                T v[kLook];
-#pragma unroll
-                for (int u = 0; u < kLook; ++u) {
-                    const int i2 = it + 64 * u;
-                    v[u] = sentinel<T>();
-                    if (i2 < items && !((got >> u) & 1u)) {
-                        const int q = R1 ? i2 : i2 / R, k = R1 ? 0 : i2 - q * R;
-                        v[u] = __hip_atomic_load(mrd + (size_t)pt.isl[q] * a.mbox_stride + k, __ATOMIC_RELAXED,
-                                                 __HIP_MEMORY_SCOPE_AGENT);
-                    }
-                }
-                bool fresh = false;
-#pragma unroll
-                for (int u = 0; u < kLook; ++u) {
-                    if (!is_sentinel(v[u])) {
-                        lds_put(xl + xoff + it + 64 * u, v[u]);
-                        got |= 1u << u;
-                        fresh = true;
-                    }
-                }
-                while (got & 1u) {
-                    got >>= 1;
-                    it += 64;
-                }
-                if (fresh) {
-                    idle = 0;
-                } else if (++idle > a.spin) {
-                    lds_put(s_abort, 2);
-                    it = items;
-                } else if ((idle & 255u) == 0 &&
-                           __hip_atomic_load(a.err_dev, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
-                    lds_put(s_abort, 1);  // another workgroup gave up
-                    it = items;
-                }
-            }
-            if (lds_get(s_abort)) break;
-        }
+    } else if (wv < nwc + a.imp_waves) {
+        if (a.imp_waves == 2) df_import<T, 1, R1>(a, pt, R, mrd, s_abort, wv - nwc, 2);
+        else df_import<T, 2, R1>(a, pt, R, mrd, s_abort, 0, 1);
     } else {
         // export wave: each lane watches its next exported item; a round in
         // which no lane found a new value sleeps briefly, so the wave does
         // not take issue slots and LDS bandwidth from the compute waves
         const int items = pt.nex * R;
         int it = lane;
-        unsigned idle = 0, rounds = 0;
-        int q = R1 ? it : it / R, k = R1 ? 0 : it - q * R;
-        int row = it < items ? pt.erl[q] : 0;
+        unsigned off = 0, at = 0, rounds = 0;
+        auto place = [&](int i) {
+            const int q = R1 ? i : i / R, k = R1 ? 0 : i - q * R;
+            off = (unsigned)pt.erl[q] * rowb + (unsigned)k * (unsigned)sizeof(T);
+            at = (unsigned)(pt.e0 + q) * (unsigned)a.mbox_stride + (unsigned)k;
+        };
+        if (it < items) place(it);
         while (__ballot(it < items) != 0) {
             bool moved = false;
             if (it < items) {
-                const T v = lds_get(xl + row * R + k);
+                const T v = lds_at<T>(off);
                 if (!is_sentinel(v)) {
-                    __hip_atomic_store(mrd + (size_t)(pt.e0 + q) * a.mbox_stride + k, v, __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_AGENT);
+                    __hip_atomic_store(mrd + at, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     it += 64;
-                    idle = 0;
                     moved = true;
-                    if (it < items) {
-                        q = R1 ? it : it / R;
-                        k = R1 ? 0 : it - q * R;
-                        row = pt.erl[q];
-                    }
-                } else if (++idle > (a.spin << 4)) {
-                    lds_put(s_abort, 2);
-                    it = items;
+                    if (it < items) place(it);
                 }
             }
-            if (__ballot(moved) == 0) {
-                __builtin_amdgcn_s_sleep(1);
-                if ((++rounds & 15u) == 0 && lds_get(s_abort)) break;
+            if (__ballot(moved) != 0) {
+                rounds = 0;
+                continue;
+            }
+            __builtin_amdgcn_s_sleep(1);
+            if ((++rounds & 15u) == 0) {
+                if (rounds > (a.spin << 4)) lds_put(s_abort, 2);
+                if (lds_get(s_abort)) break;
             }
         }
     }

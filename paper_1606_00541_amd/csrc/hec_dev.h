@@ -83,6 +83,7 @@ constexpr unsigned int kSentinel32 = 0x7FA0BEEFu;
 // Kernel arguments of one triangular solve launch (passed by value).
 struct TriArgs {
     int32_t n, w, ld, R;
+    int32_t imp_waves;           // dataflow kernel: wavefronts that fetch imports
     int32_t ldr, k0;             // dataflow kernel: right-hand sides of a vector's row, the first of this launch
     const int32_t *ell_col;
     const void *ell_val;

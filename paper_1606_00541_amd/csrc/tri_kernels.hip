@@ -1258,6 +1258,13 @@ int32_t dataflow_columns(const DevTri &d)
     return r;
 }
 
+// Two import wavefronts, but one beside wide rows (see df_import) or where
+// the workgroup has no room for another.
+int32_t dataflow_import_waves(const DevTri &d)
+{
+    return d.w <= 8 && 64 * (d.df_waves + 3) <= dataflow_max_block(d.w) ? 2 : 1;
+}
+
 template <typename T> void launch_dataflow(DevTri &d, TriArgs a, hipStream_t st)
 {
     // the plan's columns name group-local imports: only this kernel reads them
@@ -1273,7 +1280,8 @@ template <typename T> void launch_dataflow(DevTri &d, TriArgs a, hipStream_t st)
     size_t lds = dataflow_lds_bytes(d.df_rows, d.df_ints, a.R, sizeof(T));
     if (a.trace) lds += 16 + 16 * (size_t)std::min(d.df_ints, a.trace_stride);  // per-step clocks
     a.lds_ctl = (int32_t)lds - kDataflowCtlBytes;
-    const int block = 64 * d.df_waves + 128;
+    a.imp_waves = dataflow_import_waves(d);
+    const int block = 64 * (d.df_waves + 1 + a.imp_waves);
     if (block > dataflow_max_block(d.w)) fail(HEC_ERR_INVALID_ARG, "dataflow kernel: block too large");
     if (lds > (size_t)device_max_lds())
         fail(HEC_ERR_CAPACITY, "dataflow kernel: LDS need exceeds the device limit at this nrhs");
@@ -1604,7 +1612,8 @@ void launch_lu(DevTri &L, DevTri &U, bool lu_shared, const void *r, hec_dtype_t 
             const size_t lds = std::max(dataflow_lds_bytes(L.df_rows, L.df_ints, a.R, ts),
                                         dataflow_lds_bytes(U.df_rows, U.df_ints, a.R, ts));
             a.lds_ctl = b.lds_ctl = (int32_t)lds - kDataflowCtlBytes;
-            const int block = 64 * L.df_waves + 128;
+            a.imp_waves = b.imp_waves = dataflow_import_waves(L);
+            const int block = 64 * (L.df_waves + 1 + a.imp_waves);
             if (capacity_of((const void *)k, block, lds, true) < L.groups)
                 fail(HEC_ERR_CAPACITY, "dataflow grid exceeds the co-resident capacity");
             hipLaunchKernelGGL(k, dim3(L.groups), dim3(block), lds, st, a, b);
