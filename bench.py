@@ -50,7 +50,7 @@ def kernel_source_hash():
     import hashlib
 
     h = hashlib.sha256()
-    for f in ("tri_kernels.hip", "dataflow.h", "tri_dev.h", "hec_dev.h"):
+    for f in ("tri_kernels.hip", "dataflow.h", "sysq.h", "row_record.h", "tri_dev.h", "hec_dev.h"):
         with open(os.path.join(ROOT, "paper_1606_00541_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]

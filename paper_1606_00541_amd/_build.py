@@ -20,15 +20,15 @@ ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
 HIPCC = os.path.join(ROCM, "bin", "hipcc")
 
 HOST_SRCS = ["analysis.cpp", "factor.cpp"]
-HIP_SRCS = ["tri_kernels.hip", "krylov.hip", "refactor.hip", "capi.hip", "dataflow_inst.hip"]
-HEADERS = ["hec_host.h", "hec_dev.h", "tri_dev.h", "dataflow.h"]
+HIP_SRCS = ["tri_kernels.hip", "krylov.hip", "refactor.hip", "capi.hip", "dataflow_inst.hip", "sysq_inst.hip"]
+HEADERS = ["hec_host.h", "hec_dev.h", "tri_dev.h", "row_record.h", "dataflow.h", "sysq.h"]
 
 
 def _hip_units():
     """(source, object name, defines) of every HIP compilation: the dataflow
-    kernels' instances are one source compiled per value type, right-hand-side
-    form and clock trace, side by side."""
-    units = [(f, f + ".o", []) for f in HIP_SRCS if f != "dataflow_inst.hip"]
+    kernels' and the system queue's instances are one source each, compiled
+    side by side per value type and form."""
+    units = [(f, f + ".o", []) for f in HIP_SRCS if not f.endswith("_inst.hip")]
     for t, typ in (("f64", "double"), ("f32", "float")):
         for r, one in (("one", "true"), ("many", "false")):
             for s, trace in (("", "false"), ("_tr", "true")):
@@ -39,6 +39,13 @@ def _hip_units():
             name = "lu_%s_%s" % (t, r)
             units.append(("dataflow_inst.hip", name + ".o",
                           ["-DHEC_DF_T=" + typ, "-DHEC_DF_R1=" + one, "-DHEC_DF_LU=1", "-DHEC_DF_NAME=" + name]))
+    for t, typ in (("f64", "double"), ("f32", "float")):
+        for mode, m in enumerate(("x", "d", "f")):
+            for columns in (1, 4):
+                name = "sq_%s_%s%d" % (t, m, columns)
+                units.append(("sysq_inst.hip", name + ".o",
+                              ["-DHEC_SQ_T=" + typ, "-DHEC_SQ_MODE=%d" % mode, "-DHEC_SQ_C=%d" % columns,
+                               "-DHEC_SQ_NAME=" + name]))
     return units
 
 COMMON = ["-O3", "-fPIC", "-std=c++17", "-Wall", "-I" + os.path.join(ROOT, "include"), "-I" + CSRC]

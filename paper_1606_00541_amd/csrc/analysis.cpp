@@ -586,7 +586,7 @@ size_t dataflow_lds_bytes(int32_t rows, int32_t ints, int32_t R, size_t tsize)
     return ((vals + 15) & ~(size_t)15) + (((size_t)ints * 4 + 15) & ~(size_t)15) + kDataflowCtlBytes;
 }
 
-DataflowRecord::DataflowRecord(int32_t w_, int32_t ld_, int32_t tsize_) : w(w_), ld(ld_), tsize(tsize_)
+RowRecord::RowRecord(int32_t w_, int32_t ld_, int32_t tsize_) : w(w_), ld(ld_), tsize(tsize_)
 {
     const int32_t nb = w * (tsize / 4) + (w + 1) / 2;
     chunks = nb / 4 + (nb % 4 == 3 ? 1 : 0);
@@ -960,6 +960,24 @@ void build_sysq(ExecHost &ex, const Levels &lv, const std::vector<int32_t> &sys,
             for (int32_t p = ex.tail_ptr[x]; p < ex.tail_ptr[x + 1]; ++p) f(ex.tail_col[p]);
     };
     const size_t cap = dev.lds > 0 ? (size_t)dev.lds : 163840;
+    s.sq_cols = std::min(R, kSysqColumns);
+    int64_t full_rows = 1;
+    const bool dense_far = ex.w < 1 || ex.w > 8 || !ex.tail_ptr.empty();  // not for the pipelined kernel
+    // two rows per thread if at least a quarter of the levels have more rows
+    // than the workgroup has threads (overlapping 64^3 subdomains of a 128^3
+    // grid, 1 -> 2 rows: 1228 -> 1192 us; always two rows: 256 ILU(1) systems
+    // of narrow levels 1195 -> 1574 us)
+    int64_t wider = 0;
+    for (int32_t l = 0; l < lvp[S]; ++l) wider += lvrow[l + 1] - lvrow[l] > kSysqThreads;
+    s.sq_rows = 4 * wider >= lvp[S] ? 2 : 1;
+    // levels a right-hand side (and a value older than the ring) is loaded
+    // ahead at most: kSysqAhead turns of the k wavefront groups that take a
+    // system's pieces of levels in turn (k_sysq_pipe)
+    auto ahead = [&](int32_t widest) {
+        int32_t wpg = 1;
+        while (wpg * 64 * s.sq_rows < widest && wpg < kSysqThreads / 64) wpg *= 2;
+        return kSysqAhead * (kSysqThreads / 64 / wpg);
+    };
     std::vector<int32_t> D(S, 0), W(S, 1);
     for (int32_t k = 0; k < S; ++k) {
         for (int32_t l = lvp[k]; l < lvp[k + 1]; ++l) W[k] = std::max(W[k], lvrow[l + 1] - lvrow[l]);
@@ -969,9 +987,19 @@ void build_sysq(ExecHost &ex, const Levels &lv, const std::vector<int32_t> &sys,
                     if (c < n) D[k] = std::max(D[k], lev_of[x] - lev_of[c]);
                 });
         // shrink the ring until it fits (global reads beyond it)
-        while (D[k] > 0 && ((size_t)(D[k] + 1) * W[k] + 1) * R * ts > cap) --D[k];
-        if (((size_t)(D[k] + 1) * W[k] + 1) * R * ts > cap) D[k] = -1;  // not even one level: all global
+        auto fit = [&](int32_t d, int32_t columns) {
+            while (d > 0 && ((size_t)(d + 1) * W[k] + 1) * columns * ts > cap) --d;
+            return ((size_t)(d + 1) * W[k] + 1) * columns * ts > cap ? -1 : d;  // -1: not even one level, all global
+        };
+        full_rows = std::max<int64_t>(full_rows, (int64_t)(fit(D[k], R) + 1) * W[k] + 1);
+        // a ring that does not hold every dependency leaves room for a
+        // second workgroup: the older values are loaded ahead of their use
+        const int32_t d = fit(D[k], s.sq_cols);
+        int32_t half = d;
+        while (half > ahead(W[k]) && ((size_t)(half + 1) * W[k] + 1) * s.sq_cols * ts > cap / 2 - 64) --half;
+        D[k] = d < D[k] && !dense_far ? half : d;
     }
+    s.sq_full_rows = (int32_t)full_rows;
     s.sq_global = false;
     int64_t lds_rows = 1;
     for (int32_t k = 0; k < S; ++k) {
@@ -1001,6 +1029,51 @@ void build_sysq(ExecHost &ex, const Levels &lv, const std::vector<int32_t> &sys,
         });
     }
     s.sq_lds_rows = (int32_t)lds_rows;
+    // Rows as records for the pipelined kernel: columns as 16-bit ring rows,
+    // padding as the system's zero row.
+    s.sq_packed = !dense_far && lds_rows < (int64_t)kSysqFar1 &&
+                  RowRecord(sysq_width(ex.w), ex.ld, (int32_t)ts).bytes() <= (size_t)UINT32_MAX;
+    for (int32_t k = 0; k < S; ++k) s.sq_packed = s.sq_packed && (s.sq_ring[2 * k] > 0 || lvp[k] == lvp[k + 1]);
+    if (s.sq_packed && s.sq_global) {
+        // at most two older values a row, stored before they are loaded
+        s.sq_far.assign(2 * (size_t)n, n);
+        for (int32_t x = 0; x < n && s.sq_packed; ++x) {
+            int32_t f = 0;
+            for (int32_t e = 0; e < ex.w; ++e) {
+                const int32_t c = ex.ell_col[(size_t)e * ex.ld + x];
+                if (c >= 0) continue;
+                if (f == 2 || D[sys_of[x]] < ahead(W[sys_of[x]])) {
+                    s.sq_packed = false;
+                    break;
+                }
+                s.sq_far[2 * (size_t)x + f++] = -2 - c;
+            }
+        }
+        if (!s.sq_packed) s.sq_far.clear();
+    }
+    if (s.sq_packed) {
+        s.sq_pcp.assign(1, 0);
+        for (int32_t k = 0; k < S; ++k) {
+            for (int32_t l = lvp[k]; l < lvp[k + 1]; ++l)
+                for (int32_t b = lvrow[l], m = s.sq_rows * kSysqThreads; b < lvrow[l + 1]; b += m) {
+                    const int32_t slot = (l - lvp[k]) % s.sq_ring[2 * k];
+                    s.sq_pc.insert(s.sq_pc.end(), {b, std::min(m, lvrow[l + 1] - b),
+                                                   slot * s.sq_ring[2 * k + 1] + (b - lvrow[l]), 0});
+                }
+            s.sq_pcp.push_back((int32_t)s.sq_pc.size() / 4);
+        }
+        s.sq_zero.resize(n);
+        for (int32_t x = 0; x < n; ++x) {
+            const int32_t k = sys_of[x], zrow = s.sq_ring[2 * k] * s.sq_ring[2 * k + 1];
+            int32_t f = 0;
+            for (int32_t e = 0; e < ex.w; ++e) {
+                int32_t &c = ex.ell_col[(size_t)e * ex.ld + x];
+                if (c == kSqPad) c = zrow;
+                else if (c < 0) c = (int32_t)(f++ == 0 ? kSysqFar0 : kSysqFar1);
+            }
+            s.sq_zero[x] = zrow;
+        }
+    }
     s.window.assign(2 * (size_t)S, 0);
     s.step_ptr.assign((size_t)S + 1, 0);
     s.exp_ptr.assign((size_t)S + 1, 0);
@@ -1333,7 +1406,7 @@ void build_exec(TriHost &t, const Csr &a, const Tune &tune, const DeviceShape &d
     if (want_df && dataflow_width(w) != w)
         fail(HEC_ERR_INVALID_ARG, "dataflow kernel: ELL width must be 1..8, 10, 12 or 16");
     if (want_df && R > 64) fail(HEC_ERR_INVALID_ARG, "dataflow kernel: max_nrhs above 64");
-    if (want_df && DataflowRecord(w, ld, t.dt == HEC_F64 ? 8 : 4).bytes() > (size_t)UINT32_MAX)
+    if (want_df && RowRecord(w, ld, t.dt == HEC_F64 ? 8 : 4).bytes() > (size_t)UINT32_MAX)
         fail(HEC_ERR_CAPACITY, "dataflow kernel: ELL part beyond 4 GiB (32-bit buffer offsets)");
     if (want_df && tune.block_threads > dataflow_max_block(w) - 128)
         fail(HEC_ERR_CAPACITY, "dataflow kernel: block_threads above " + std::to_string(dataflow_max_block(w) - 128) +
@@ -1457,19 +1530,33 @@ TriHost analyze(const Csr &a, bool upper, bool unit, hec_dtype_t dt, const Tune 
             }
         }
         // too large for LDS with enough independent systems to give every
-        // other compute unit one (a batch, RAS subdomains): the system
-        // queue, whose levels are separated by workgroup barriers with the
-        // last levels' values in LDS (256 systems of ILU(1), 8 RHS: 4.2 ms
-        // FP32 against 7.4 ms for the barrier-free kernel; 64 subdomains
-        // leave most of the GPU idle and stay on the barrier-free kernel)
+        // other compute unit one, or with more than eight right-hand sides
+        // enough columns of systems to give every one an item (a batch, RAS
+        // subdomains): the system queue, whose levels are separated by
+        // workgroup barriers with the last levels' values in LDS.  Both
+        // triangles, barrier-free kernel -> queue, 16 right-hand sides: 16
+        // subdomains of a 64^3 grid 395 -> 235 us, 64 of a 128^3 grid 1985 ->
+        // 1192; 16 systems of 48^3 rows 1049 -> 623, of 300^2 rows 1505 ->
+        // 709; two of 48^3 rows in FP64 423 -> 468.  With eight or fewer the
+        // line stays at half the compute units, also where the queue would
+        // win: such plans are often called with one or two right-hand sides,
+        // where long systems lose (16 systems of 48^3 rows in FP64, one
+        // right-hand side 392 -> 466; of 300^2 rows 1214 -> 569).
         const int32_t nsys = sys_ptr && sys_ptr->size() >= 2 ? (int32_t)sys_ptr->size() - 1 : 1;
-        if (auto_sched && nsys >= std::max(2, (dev.cus > 0 ? dev.cus : 256) / 2) && tu.max_nrhs <= 64) {
+        const int32_t cu = dev.cus > 0 ? dev.cus : 256;
+        const bool half = nsys >= cu / 2, columns = tu.max_nrhs > 8 && (int64_t)nsys * tu.max_nrhs >= cu;
+        if (auto_sched && nsys >= 2 && (half || columns) && tu.max_nrhs <= 64) {
             Tune q = tu;
             q.schedule = HEC_SCHED_LEVEL_PERSISTENT;
             q.variant = 7;
             t.variant = 7;
             attempt(q);
-            return t;
+            if (half) return t;
+            // by its columns only on the pipelined kernel; any number of
+            // right-hand sides, as on the kernel it takes the place of
+            t.ex.sched.sq_full_rows = 0;
+            if (t.ex.sched.sq_packed && ((size_t)a.n + 1) * tu.max_nrhs * 8 < kSysqDropped) return t;
+            t.variant = tu.variant;
         }
         if (auto_sched) {
             // too large for LDS: the barrier-free kernel (its per-level cost

@@ -82,6 +82,11 @@ void ensure_workspace(DevTri &d, int32_t R)
     d.ws_R = R;
 }
 
+static RowRecord row_record(const ExecHost &ex, hec_dtype_t dt)
+{
+    return RowRecord(ex.sched.dataflow ? ex.w : sysq_width(ex.w), ex.ld, (int32_t)vsize(dt));
+}
+
 void upload_tri(DevTri &d, const TriHost &t, int32_t max_nrhs)
 {
     hip_check(hipGetDevice(&d.device), "hipGetDevice");
@@ -94,27 +99,30 @@ void upload_tri(DevTri &d, const TriHost &t, int32_t max_nrhs)
     d.kind = ex.sched.kind;
     d.unit = t.unit;
     d.has_tail = !ex.tail_ptr.empty();
-    if (ex.sched.dataflow) {
-        // one record per row: values and 16-bit columns together
-        const DataflowRecord rec(ex.w, ex.ld, (int32_t)vsize(t.dt));
+    if (ex.sched.dataflow || ex.sched.sq_packed) {
+        // one record per row: values and 16-bit columns together; slots past
+        // the ELL width (system queue) hold 0 and the zero row's column
+        const RowRecord rec = row_record(ex, t.dt);
         std::vector<unsigned char> buf(rec.bytes(), 0);
-        for (int32_t e = 0; e < ex.w; ++e) {
+        for (int32_t e = 0; e < rec.w; ++e) {
             const int32_t dv = rec.value_dword(e), dc = rec.column_dword(e);
             unsigned char *pv = buf.data() + rec.first(dv), *pc = buf.data() + rec.first(dc) + 2 * (e & 1);
             const size_t sv = rec.stride(dv), sc = rec.stride(dc);
-            const double *v = ex.ell_val.data() + (size_t)e * ex.ld;
-            const int32_t *c = ex.ell_col.data() + (size_t)e * ex.ld;
+            const bool pad = e >= ex.w;
+            const double *v = ex.ell_val.data() + (size_t)(pad ? 0 : e) * ex.ld;
+            const int32_t *c = ex.ell_col.data() + (size_t)(pad ? 0 : e) * ex.ld;
             for (int32_t x = 0; x < ex.n; ++x, pv += sv, pc += sc) {
-                if (t.dt == HEC_F64) std::memcpy(pv, v + x, 8);
-                else {
+                if (!pad && t.dt == HEC_F64) std::memcpy(pv, v + x, 8);
+                if (!pad && t.dt == HEC_F32) {
                     const float f = (float)v[x];
                     std::memcpy(pv, &f, 4);
                 }
-                const uint16_t col = (uint16_t)c[x];
+                const uint16_t col = (uint16_t)(pad ? ex.sched.sq_zero[x] : c[x]);
                 std::memcpy(pc, &col, 2);
             }
         }
         upload(d.ell_val, buf);
+        d.w = rec.w;
     } else {
         upload(d.ell_col, ex.ell_col);
         upload_values(d.ell_val, ex.ell_val, t.dt);
@@ -170,18 +178,17 @@ void upload_tri(DevTri &d, const TriHost &t, int32_t max_nrhs)
             d.sysq = true;
             d.sq_global = s.sq_global;
             d.sq_lds_rows = s.sq_lds_rows;
-            d.sq_widths.clear();
-            for (size_t l = 0; l + 1 < s.sq_lvrow.size(); ++l) d.sq_widths.push_back(s.sq_lvrow[l + 1] - s.sq_lvrow[l]);
-            d.sq_median_rows = 0;
-            if (!d.sq_widths.empty()) {
-                std::vector<int32_t> w = d.sq_widths;
-                std::nth_element(w.begin(), w.begin() + w.size() / 2, w.end());
-                d.sq_median_rows = w[w.size() / 2];
-            }
+            d.sq_full_rows = s.sq_full_rows;
+            d.sq_packed = s.sq_packed;
+            d.sq_cols = s.sq_cols;
             upload(d.sq_lvp, s.sq_lvp);
             upload(d.sq_lvrow, s.sq_lvrow);
             upload(d.sq_ring, s.sq_ring);
             upload(d.sq_keep, s.sq_keep);
+            upload(d.sq_far, s.sq_far);
+            upload(d.sq_pcp, s.sq_pcp);
+            upload(d.sq_pc, s.sq_pc);
+            d.sq_rows = s.sq_rows;
         }
     }
     // epoch, workgroups done, work counter (part queue / chunk batches)
@@ -468,7 +475,7 @@ void build_refactor(ilu_s &f, const int32_t *rowptr, const int32_t *col)
     // plan positions: the off-diagonals of a row keep their order in both layouts
     auto place = [&f](const ExecHost &ex, int32_t x, int32_t e) -> int32_t {
         if (e >= ex.w) return -1 - (ex.tail_ptr[x] + (e - ex.w));
-        if (ex.sched.dataflow) return (int32_t)DataflowRecord(ex.w, ex.ld, (int32_t)vsize(f.fdt)).value(x, e);
+        if (ex.sched.dataflow || ex.sched.sq_packed) return (int32_t)row_record(ex, f.fdt).value(x, e);
         return e * ex.ld + x;
     };
     std::vector<int32_t> l_src, l_dst, u_src, u_dst, u_diag, d_src(n);

@@ -35,7 +35,7 @@
 // three factors in turn), 100^3 ILUT(1e-3, 10) FP32 1910 -> 1395 us.
 #pragma once
 
-#include "tri_dev.h"
+#include "row_record.h"
 
 namespace hec {
 
@@ -48,71 +48,17 @@ template <typename T> __device__ __forceinline__ void lds_put(T *p, T v)
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-// A value of the LDS value area by its byte offset.  The kernels of this file
-// have no static LDS, so their dynamic LDS, which starts with the value area,
-// starts at LDS address 0 (checked at launch): an offset is an address, with
-// no base to add on the dependency chain.
-template <typename T> using LdsPtr = __attribute__((address_space(3))) T *;
-template <typename T> __device__ __forceinline__ T lds_at(unsigned off)
+// Register sets in rotation: as many as the vector-memory counter (63
+// outstanding loads) and about 144 registers hold, at most 8 (4 sets made
+// 128^3 ILU(0) 6% slower, 6 to 16 were equal, and 16 made ILU(1) with four
+// right-hand sides 12% slower than 8).
+template <typename T, int W> constexpr int df_sets()
 {
-    return __hip_atomic_load((LdsPtr<T>)(uintptr_t)off, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-template <typename T> __device__ __forceinline__ void lds_set(unsigned off, T v)
-{
-    __hip_atomic_store((LdsPtr<T>)(uintptr_t)off, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-
-// A row as the kernel loads it: W values, then W 16-bit LDS value rows (own
-// rows, imports, the zero row of ELL padding), in 16-byte chunks and a
-// remainder of 0..2 dwords, each chunk an array over the rows.  Three
-// dwords are padded to a chunk.  (dataflow_record on the host.)
-template <typename T, int W> struct DfRec {
-    static constexpr int V = W * (int)sizeof(T) / 4;  // dwords of values
-    static constexpr int NB = V + (W + 1) / 2;
-    static constexpr int CH = NB / 4 + (NB % 4 == 3 ? 1 : 0);
-    static constexpr int RE = NB % 4 == 3 ? 0 : NB % 4;
-    static constexpr int ND = 4 * CH + RE;
-    static constexpr int LOADS = CH + (RE > 0 ? 1 : 0);
-    // register sets in rotation: as many as the vector-memory counter (63
-    // outstanding loads) and about 144 registers hold, at most 8 (4 sets made
-    // 128^3 ILU(0) 6% slower, 6 to 16 were equal, and 16 made ILU(1) with four
-    // right-hand sides 12% slower than 8)
-    static constexpr int byreg = 144 / ND < 3 ? 3 : 144 / ND;
-    static constexpr int bycnt = 60 / LOADS + 1;
-    static constexpr int k0 = byreg < bycnt ? byreg : bycnt;
-    static constexpr int K = k0 < 8 ? k0 : 8;
-    static_assert(K <= kDataflowPad, "descriptors are read K steps ahead");
-};
-
-template <int ND> struct DfSet {
-    uint32_t d[ND];
-};
-
-template <typename T, int W> __device__ __forceinline__ T df_val(const DfSet<DfRec<T, W>::ND> &u, int e)
-{
-    if constexpr (sizeof(T) == 8)
-        return __builtin_bit_cast(T, (unsigned long long)u.d[2 * e] | ((unsigned long long)u.d[2 * e + 1] << 32));
-    else
-        return __builtin_bit_cast(T, u.d[e]);
-}
-// LDS byte offset of ELL slot e: its value row times the bytes of a row, plus
-// the lane's right-hand side.  One multiply-add on a half of the packed dword.
-template <typename T, int W, bool R1>
-__device__ __forceinline__ unsigned df_off(const DfSet<DfRec<T, W>::ND> &u, int e, unsigned rowbytes, unsigned kbytes)
-{
-    const unsigned d = u.d[DfRec<T, W>::V + e / 2];
-    unsigned r;
-    if constexpr (R1 && sizeof(T) == 8) {
-        if (e & 1) asm volatile("v_mad_u32_u16 %0, %1, 8, 0 op_sel:[1,0,0,0]" : "=v"(r) : "v"(d));
-        else asm volatile("v_mad_u32_u16 %0, %1, 8, 0" : "=v"(r) : "v"(d));
-    } else if constexpr (R1) {
-        if (e & 1) asm volatile("v_mad_u32_u16 %0, %1, 4, 0 op_sel:[1,0,0,0]" : "=v"(r) : "v"(d));
-        else asm volatile("v_mad_u32_u16 %0, %1, 4, 0" : "=v"(r) : "v"(d));
-    } else {
-        if (e & 1) asm volatile("v_mad_u32_u16 %0, %1, %2, %3 op_sel:[1,0,0,0]" : "=v"(r) : "v"(d), "s"(rowbytes), "v"(kbytes));
-        else asm volatile("v_mad_u32_u16 %0, %1, %2, %3" : "=v"(r) : "v"(d), "s"(rowbytes), "v"(kbytes));
-    }
-    return r;
+    using Rec = RowRec<T, W>;
+    constexpr int byreg = 144 / Rec::ND < 3 ? 3 : 144 / Rec::ND, bycnt = 60 / Rec::LOADS + 1;
+    constexpr int k = byreg < bycnt ? byreg : bycnt, sets = k < 8 ? k : 8;
+    static_assert(sets <= kDataflowPad, "descriptors are read that many steps ahead");
+    return sets;
 }
 
 // A workgroup's part of one triangle and its place in LDS: x [win][R], b
@@ -300,8 +246,8 @@ template <typename T, int W, bool TAIL, bool R1, bool TRACE, typename Fill>
 __device__ __forceinline__ void df_sweep(const TriArgs &a, const DfPart<T> &pt, int R, T *mrd, int *s_abort,
                                          unsigned long long &t_fill, Fill fill)
 {
-    using Rec = DfRec<T, W>;
-    constexpr int K = Rec::K;
+    using Rec = RowRec<T, W>;
+    constexpr int K = df_sets<T, W>();
     const int tid = threadIdx.x, nt = blockDim.x;
     const int lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -316,34 +262,20 @@ __device__ __forceinline__ void df_sweep(const TriArgs &a, const DfPart<T> &pt, 
     const unsigned kb = R1 ? 0u : (lane - q0 * R) * (unsigned)sizeof(T);
     const unsigned bofs = (unsigned)(reinterpret_cast<unsigned char *>(pt.bl) - reinterpret_cast<unsigned char *>(xl));
     const unsigned long long nbytes = (unsigned long long)Rec::ND * 4u * (unsigned)a.ld;
-    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
+    const BufRsrc rsrc = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<void *>(a.ell_val), 0, (int)(unsigned)(nbytes > 0xffffffffull ? 0xffffffffull : nbytes), 0x00020000);
     // the part's rows begin at lo: chunk c of its row r is 16 bytes at
     // (lo + c * ld + r) * 16, the remainder behind all chunks
     const unsigned ld = (unsigned)a.ld, base = (unsigned)lo * 16u, rbase = Rec::CH * ld * 16u + (unsigned)lo * (Rec::RE * 4u);
-    DfSet<Rec::ND> S[K];
+    uint32_t S[K][Rec::ND];
     unsigned xo[K];  // LDS byte offset of the item's value
     // Loads of the step with descriptor dsc into set i.  All of it is vector
     // work on a descriptor every lane holds: no scalar register is written by
     // a vector instruction, which would cost wait states before its use.
     auto load = [&](int i, unsigned dsc) {
-        DfSet<Rec::ND> &u = S[i];
         unsigned vo;
         asm("v_mad_u32_u16 %0, %1, 16, %2" : "=v"(vo) : "v"(dsc), "v"(min(q16, dsc >> 16)));
-#pragma unroll
-        for (int c = 0; c < Rec::CH; ++c) {
-            auto v = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)vo, (int)(base + c * ld * 16u), 0);
-            u.d[4 * c] = v[0];
-            u.d[4 * c + 1] = v[1];
-            u.d[4 * c + 2] = v[2];
-            u.d[4 * c + 3] = v[3];
-        }
-        if constexpr (Rec::RE == 1) u.d[4 * Rec::CH] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, (int)(vo / 4u), (int)rbase, 0);
-        if constexpr (Rec::RE == 2) {
-            auto v = __builtin_amdgcn_raw_buffer_load_b64(rsrc, (int)(vo / 2u), (int)rbase, 0);
-            u.d[4 * Rec::CH] = v[0];
-            u.d[4 * Rec::CH + 1] = v[1];
-        }
+        row_load<T, W>(S[i], rsrc, ld, base, rbase, vo);
         xo[i] = R1 ? vo / (16u / (unsigned)sizeof(T)) : (vo / 16u) * rowb + kb;
         asm volatile("" : "+v"(xo[i]));  // here, not on the dependency chain
     };
@@ -374,16 +306,20 @@ __device__ __forceinline__ void df_sweep(const TriArgs &a, const DfPart<T> &pt, 
         unsigned stp = 0;  // LDS address of descriptor j
         unsigned on[W];  // LDS byte offsets of the next step's inputs
         auto rhs = [&](int i) { bv[i] = *(LdsPtr<T>)(uintptr_t)(xo[i] + bofs); };
-        auto offsets = [&](const DfSet<Rec::ND> &u) {
+        auto offset = [&](const uint32_t (&u)[Rec::ND], int e) {
+            if constexpr (R1) return row_off<T, W, (unsigned)sizeof(T)>(u, e);
+            else return row_off<T, W>(u, e, rowb, kb);
+        };
+        auto offsets = [&](const uint32_t (&u)[Rec::ND]) {
 #pragma unroll
-            for (int e = 0; e < W; ++e) on[e] = df_off<T, W, R1>(u, e, rowb, kb);
+            for (int e = 0; e < W; ++e) on[e] = offset(u, e);
         };
         auto read = [&](const unsigned *o) {
 #pragma unroll
             for (int e = 0; e < W; ++e) dep[e] = lds_at<T>(o[e]);
         };
         auto step = [&](int p, bool more) {  // more: also issue the loads of step p + K - 1
-            const DfSet<Rec::ND> &u = S[p];
+            const uint32_t (&u)[Rec::ND] = S[p];
             if (TRACE && j + p < ntr && lane == 0) pt.ltr[2 * (j + p)] = __builtin_amdgcn_s_memrealtime();
             if (more) {
                 load((p + K - 1) % K, dsc);
@@ -394,12 +330,12 @@ __device__ __forceinline__ void df_sweep(const TriArgs &a, const DfPart<T> &pt, 
             __builtin_amdgcn_sched_barrier(0);
             T acc = bv[p];
 #pragma unroll
-            for (int e = 0; e < W; ++e) acc -= df_val<T, W>(u, e) * dep[e];
+            for (int e = 0; e < W; ++e) acc -= row_val<T, W>(u, e) * dep[e];
             if (__builtin_expect(__ballot(acc != acc) != 0, 0)) {
                 bool pend = false;
                 unsigned oc[W];
 #pragma unroll
-                for (int e = 0; e < W; ++e) oc[e] = df_off<T, W, R1>(u, e, rowb, kb);
+                for (int e = 0; e < W; ++e) oc[e] = offset(u, e);
 #pragma unroll
                 for (int e = 0; e < W; ++e) pend |= is_sentinel(dep[e]);
                 unsigned spins = 0;
@@ -422,7 +358,7 @@ __device__ __forceinline__ void df_sweep(const TriArgs &a, const DfPart<T> &pt, 
                 }
                 acc = bv[p];
 #pragma unroll
-                for (int e = 0; e < W; ++e) acc -= df_val<T, W>(u, e) * dep[e];
+                for (int e = 0; e < W; ++e) acc -= row_val<T, W>(u, e) * dep[e];
             }
             if (TAIL) {
                 const unsigned x = lo + (R1 ? xo[p] / (unsigned)sizeof(T) : (xo[p] - kb) / rowb);

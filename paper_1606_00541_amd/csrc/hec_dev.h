@@ -84,7 +84,10 @@ constexpr unsigned int kSentinel32 = 0x7FA0BEEFu;
 struct TriArgs {
     int32_t n, w, ld, R;
     int32_t imp_waves;           // dataflow kernel: wavefronts that fetch imports
-    int32_t ldr, k0;             // dataflow kernel: right-hand sides of a vector's row, the first of this launch
+    int32_t ldr, k0;             // right-hand sides of a vector's row, the first of this launch (R: of this launch)
+    int32_t cgroups;             // system queue: groups of R columns a system's columns are cut into
+    int32_t rec_chunks, rec_rest;  // system queue: 16-byte chunks and remaining dwords of a packed row (-1: not packed)
+    int32_t xw_grouped, bin_grouped;  // system queue: xw / bin hold the groups one after the other
     const int32_t *ell_col;
     const void *ell_val;
     const int32_t *tail_ptr, *tail_col;
@@ -116,11 +119,12 @@ struct TriArgs {
     int32_t trace_stride;
     unsigned spin;               // polls before a bounded wait gives up
     const int32_t *step_pack;    // dataflow kernel: per step its first window row | 16 (rows - 1) << 16
-    int32_t lds_ctl;             // dataflow kernel: LDS offset of the control words
+    int32_t lds_ctl;             // dataflow kernels, pipelined system queue: LDS offset of the control words
     int32_t nparts;              // dataflow kernel: parts of the plan; system queue: systems
     int32_t queue;               // dataflow kernel: workgroups take parts from a counter (epoch[2])
     const int32_t *sq_lvp, *sq_lvrow, *sq_ring;  // system queue: levels per system, level rows, rings
     const int8_t *sq_keep;                        // system queue: rows also stored to xw (read beyond a ring)
+    const int32_t *sq_far;                        // packed rows: the two rows read beyond the ring (n: none)
 };
 
 // Kernels of one launch per triangle that take nothing but TriArgs.
@@ -142,6 +146,22 @@ LuKernel lu_f64_one(int w);
 LuKernel lu_f64_many(int w);
 LuKernel lu_f32_one(int w);
 LuKernel lu_f32_many(int w);
+
+// Pipelined system queue by record width: value type and output (_x: the
+// workspace, _d / _f: the caller's FP64 / FP32 vector).
+using SysqKernel = void (*)(TriArgs, const int32_t *, const int4 *, const int32_t *);
+SysqKernel sq_f64_x1(int w, bool in_f64, int rows, bool far);
+SysqKernel sq_f64_x4(int w, bool in_f64, int rows, bool far);
+SysqKernel sq_f64_d1(int w, bool in_f64, int rows, bool far);
+SysqKernel sq_f64_d4(int w, bool in_f64, int rows, bool far);
+SysqKernel sq_f64_f1(int w, bool in_f64, int rows, bool far);
+SysqKernel sq_f64_f4(int w, bool in_f64, int rows, bool far);
+SysqKernel sq_f32_x1(int w, bool in_f64, int rows, bool far);
+SysqKernel sq_f32_x4(int w, bool in_f64, int rows, bool far);
+SysqKernel sq_f32_d1(int w, bool in_f64, int rows, bool far);
+SysqKernel sq_f32_d4(int w, bool in_f64, int rows, bool far);
+SysqKernel sq_f32_f1(int w, bool in_f64, int rows, bool far);
+SysqKernel sq_f32_f4(int w, bool in_f64, int rows, bool far);
 
 // Polls of a bounded device-side wait before it is declared hung (a plan may
 // set its own, tri_plan_set_wait_limit); at most kMaxSpin so that the
@@ -170,10 +190,9 @@ struct DevTri {
     int32_t df_accept = 0;         // right-hand sides taken in groups of columns
     bool queue = false;            // dataflow parts taken from a counter (more parts than workgroups)
     bool sysq = false, sq_global = false;  // system queue kernel; some dependencies read from xw
-    int32_t sq_lds_rows = 0;
-    std::vector<int32_t> sq_widths;  // rows of every level of every system
-    int32_t sq_median_rows = 0;      // their median
-    DevMem sq_lvp, sq_lvrow, sq_ring, sq_keep;
+    bool sq_packed = false;        // rows as records (w: their slots)
+    int32_t sq_lds_rows = 0, sq_full_rows = 0, sq_cols = 1, sq_rows = 1;  // as in Schedule
+    DevMem sq_lvp, sq_lvrow, sq_ring, sq_keep, sq_far, sq_pcp, sq_pc;
     int32_t chunk_rows = 0;
     bool max_lanes_one = true;     // every step runs one thread per (row, rhs)
     DevMem epoch, err, mbox;

@@ -103,8 +103,15 @@ struct Schedule {
     // its LDS ring has sq_ring[2k] slots of sq_ring[2k+1] rows
     bool sysq = false;
     bool sq_global = false;          // some dependency is read from the global workspace
+    int32_t sq_cols = 1;             // columns the rings are sized for
     int32_t sq_lds_rows = 0;         // largest ring plus the zero row, in rows
+    bool sq_packed = false;          // rows as records (pipelined kernel): columns are ring rows, padding the zero row
+    int32_t sq_full_rows = 0;        // the same if rings were sized for all max_nrhs columns (0: no limit on the right-hand sides)
     std::vector<int32_t> sq_lvp, sq_lvrow, sq_ring;
+    int32_t sq_rows = 1;             // packed rows: rows of a piece per thread
+    std::vector<int32_t> sq_pcp, sq_pc;  // packed rows: pieces of each system; first row, rows, first ring row (and 0) of each
+    std::vector<int32_t> sq_far;     // packed rows: two device rows read beyond the ring (n: none)
+    std::vector<int32_t> sq_zero;    // packed rows: zero row of the row's ring
     std::vector<int8_t> sq_keep;     // rows read back from the global workspace
     int32_t nsteps() const { return (int32_t)step_lanes.size(); }
 };
@@ -167,20 +174,27 @@ struct Tune {
 // window and imports) of R right-hand sides, then `ints` int32 entries
 // (import slots, export rows, step descriptors) and the control words.
 constexpr int32_t kDataflowCtlBytes = 16;
+constexpr int32_t kSysqColumns = 4;     // columns of one item of the system queue
+constexpr int32_t kSysqThreads = 512;   // threads of its pipelined kernel
+constexpr int32_t kSysqAhead = 2;       // turns its right-hand sides are loaded ahead
+constexpr uint32_t kSysqFar0 = 0xffff, kSysqFar1 = 0xfffe;  // packed columns: the row's first, second value beyond the ring
+constexpr uint32_t kSysqDropped = 0xf0000000u;  // byte offset past every output vector of its kernel
+// ELL slots of a row record of the pipelined system queue for ELL width w.
+inline int32_t sysq_width(int32_t w) { return w <= 2 ? 2 : (w <= 4 ? w : (w <= 6 ? 6 : 8)); }
 constexpr int32_t kDataflowPad = 16;  // descriptors the kernel may read past a part's last step
 size_t dataflow_lds_bytes(int32_t rows, int32_t ints, int32_t R, size_t tsize);
 // Smallest ELL width >= w the dataflow kernel is built for (1..8, 10, 12,
 // 16), or -1 above 16; and its largest workgroup (threads) at that width.
 int32_t dataflow_width(int32_t w);
 int32_t dataflow_max_block(int32_t w);
-// Record of a row as the dataflow kernel loads it: w values, then w 16-bit LDS
-// value rows, cut into 16-byte chunks (each chunk an array over the ld rows)
+// Record of a row as the dataflow kernel and the pipelined system queue load
+// it: w values, then w 16-bit LDS value rows, cut into 16-byte chunks (each chunk an array over the ld rows)
 // and a remainder of 0..2 dwords behind them (three dwords fill a chunk).
-struct DataflowRecord {
+struct RowRecord {
     int32_t w, ld;
     int32_t chunks, rest;  // 16-byte chunks, dwords of the remainder
     int32_t tsize;         // bytes of a value
-    DataflowRecord(int32_t w_, int32_t ld_, int32_t tsize_);
+    RowRecord(int32_t w_, int32_t ld_, int32_t tsize_);
     size_t bytes() const { return (size_t)ld * (16 * (size_t)chunks + 4 * (size_t)rest); }
     // byte offset of a dword of row x: first(dword) + x * stride(dword)
     size_t first(int32_t dword) const

@@ -878,6 +878,13 @@ __global__ void __launch_bounds__(256) k_syncfree(TriArgs a, int waves)
     }
 }
 
+// Address of a dword of a packed row (RowRecord::first and stride).
+__device__ __forceinline__ const unsigned char *rec_dword(const TriArgs &a, const unsigned char *p, int x, int dw)
+{
+    if (dw < 4 * a.rec_chunks) return p + ((size_t)(dw / 4) * a.ld + x) * 16 + 4 * (dw % 4);
+    return p + (size_t)a.rec_chunks * a.ld * 16 + ((size_t)x * a.rec_rest + (dw - 4 * a.rec_chunks)) * 4;
+}
+
 // System queue: every workgroup takes whole independent systems from a
 // counter (largest first) and solves one system's levels in order, all of a
 // level's (row, rhs) items spread over the workgroup, with a workgroup
@@ -888,6 +895,8 @@ __global__ void __launch_bounds__(256) k_syncfree(TriArgs a, int waves)
 // co-residency.  Rows are computed exactly as in k_level (ELL slots in order,
 // then the CSR tail; ELL padding reads a zero row of the ring and subtracts
 // 0 * 0), so results are bit-identical to it.
+// With several right-hand sides an item of the queue is a system and a group
+// of at most a.R of its columns (see k_sysq_pipe).
 template <typename T, typename TIn, typename TOut>
 __global__ void __launch_bounds__(1024) k_sysq(TriArgs a)
 {
@@ -896,7 +905,7 @@ __global__ void __launch_bounds__(1024) k_sysq(TriArgs a)
     __shared__ unsigned s_epoch;
     T *ring = reinterpret_cast<T *>(smem);
     const int tid = threadIdx.x, nt = blockDim.x;
-    const int R = a.R;
+    const long ldr = a.ldr;
     const T *ev = static_cast<const T *>(a.ell_val);
     const T *tv = static_cast<const T *>(a.tail_val);
     T *xw = static_cast<T *>(a.xw);
@@ -905,8 +914,9 @@ __global__ void __launch_bounds__(1024) k_sysq(TriArgs a)
         if (tid == 0)
             s_q = (int)__hip_atomic_fetch_add(&a.epoch[2], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __syncthreads();
-        const int q = s_q;
-        if (q >= a.nparts) break;
+        const int item = s_q;
+        if (item >= a.nparts * a.cgroups) break;
+        const int q = item / a.cgroups, g0 = (item - q * a.cgroups) * a.R, R = min(a.R, a.ldr - g0);
         const int slots = a.sq_ring[2 * q], W = a.sq_ring[2 * q + 1];
         const int zrow = slots * W;
         for (int t = tid; t < R; t += nt) ring[(size_t)zrow * R + t] = T(0);
@@ -919,13 +929,22 @@ __global__ void __launch_bounds__(1024) k_sysq(TriArgs a)
             for (int t = tid; t < items; t += nt) {
                 const int i = t / R, k = t - i * R;
                 const int x = rb + i;
-                T sv = canon(static_cast<T>(static_cast<const TIn *>(a.bin)[(size_t)a.gather[x] * R + k]));
+                T sv = canon(static_cast<T>(static_cast<const TIn *>(a.bin)[(size_t)a.gather[x] * ldr + g0 + k]));
                 if (a.dinv) sv = scale_rhs(sv, static_cast<const T *>(a.dinv)[x]);
                 for (int e = 0; e < a.w; ++e) {
-                    const int c = a.ell_col[(size_t)e * a.ld + x];
-                    const T v = ev[(size_t)e * a.ld + x];
+                    int c;
+                    T v;
+                    if (a.rec_chunks >= 0) {  // packed rows
+                        const unsigned char *p = static_cast<const unsigned char *>(a.ell_val);
+                        v = *reinterpret_cast<const T *>(rec_dword(a, p, x, e * (int)(sizeof(T) / 4)));
+                        c = reinterpret_cast<const uint16_t *>(rec_dword(a, p, x, a.w * (int)(sizeof(T) / 4) + e / 2))[e & 1];
+                        if (a.sq_far && c >= (int)kSysqFar1) c = -2 - a.sq_far[2 * (size_t)x + (c == (int)kSysqFar1 ? 1 : 0)];
+                    } else {
+                        c = a.ell_col[(size_t)e * a.ld + x];
+                        v = ev[(size_t)e * a.ld + x];
+                    }
                     const T dep = c >= 0 ? ring[(size_t)min(c, zrow) * R + k]
-                                         : __hip_atomic_load(xw + (size_t)(-2 - c) * R + k, __ATOMIC_RELAXED,
+                                         : __hip_atomic_load(xw + (size_t)(-2 - c) * ldr + g0 + k, __ATOMIC_RELAXED,
                                                              __HIP_MEMORY_SCOPE_WORKGROUP);
                     sv -= v * dep;
                 }
@@ -933,265 +952,21 @@ __global__ void __launch_bounds__(1024) k_sysq(TriArgs a)
                     for (int p = a.tail_ptr[x]; p < a.tail_ptr[x + 1]; ++p) {
                         const int c = a.tail_col[p];
                         const T dep = c >= 0 ? ring[(size_t)min(c, zrow) * R + k]
-                                             : __hip_atomic_load(xw + (size_t)(-2 - c) * R + k, __ATOMIC_RELAXED,
+                                             : __hip_atomic_load(xw + (size_t)(-2 - c) * ldr + g0 + k, __ATOMIC_RELAXED,
                                                                  __HIP_MEMORY_SCOPE_WORKGROUP);
                         sv -= tv[p] * dep;
                     }
                 }
                 if (slots) ring[(size_t)(base + i) * R + k] = sv;
                 if (a.write_xw)
-                    __hip_atomic_store(xw + (size_t)x * R + k, sv, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                    __hip_atomic_store(xw + (size_t)x * ldr + g0 + k, sv, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
                 if (a.xout) {
                     const int d = a.scatter[x];
-                    if (d >= 0) static_cast<TOut *>(a.xout)[(size_t)d * R + k] = static_cast<TOut>(sv);
+                    if (d >= 0) static_cast<TOut *>(a.xout)[(size_t)d * ldr + g0 + k] = static_cast<TOut>(sv);
                 }
             }
             __syncthreads();
         }
-    }
-    if (tid == 0) {
-        const unsigned done = __hip_atomic_fetch_add(&a.epoch[1], 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
-        if (done == gridDim.x - 1) {
-            // last workgroup out: every claim is over; reset the queue
-            __hip_atomic_store(&a.epoch[2], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(&a.epoch[1], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(&a.epoch[0], s_epoch + 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-        }
-    }
-}
-
-// One item of the pipelined system queue: a row's G right-hand sides, with
-// the row's data loaded P levels before its level is solved and its
-// right-hand sides H levels before.
-template <typename T, typename TIn, int G, int MW> struct SqItem {
-    // integers, not bools: a bool becomes a lane mask as soon as it is
-    // formed, which would wait for the load it comes from
-    int ok;        // a real row of the level (else loads of a clamped row, unused)
-    int keep;      // also stored to xw (read beyond a ring)
-    int x, gi, dst;
-    int c[MW];
-    T v[MW];
-    T d;
-    TIn b[G];
-};
-
-// Row data of local row i of level lf (clamped into the system's levels and
-// into the level, so that every load stays inside the plan's arrays).
-template <typename T, typename TIn, int G, int MW>
-__device__ __forceinline__ void sq_rows(const TriArgs &a, const int32_t *__restrict__ lvrow,
-                                       SqItem<T, TIn, G, MW> &u, int lf, int l1, int i)
-{
-    const int lc = min(lf, l1 - 1);
-    const int rb = lvrow[lc], re = lvrow[lc + 1];
-    u.ok = lf < l1 && rb + i < re;
-    const int x = max(0, min(rb + i, re - 1));
-    u.x = x;
-    u.gi = a.gather[x];
-    const T *ev = static_cast<const T *>(a.ell_val);
-#pragma unroll
-    for (int e = 0; e < MW; ++e) {
-        const size_t o = (size_t)min(e, a.w - 1) * a.ld + x;
-        u.c[e] = a.ell_col[o];
-        u.v[e] = ev[o];
-    }
-    // unconditional loads (from a stand-in array when there is no diagonal
-    // or scatter), so that every set issues the same number of loads and
-    // the compiler's memory counters wait only for the set being solved
-    u.d = (a.dinv ? static_cast<const T *>(a.dinv) : ev)[x];
-    u.dst = (a.xout ? a.scatter : a.gather)[x];
-    u.keep = a.sq_keep[x];
-}
-
-template <typename T, typename TIn, int G, int MW>
-__device__ __forceinline__ void sq_rhs(const TriArgs &a, SqItem<T, TIn, G, MW> &u, int g0)
-{
-    const TIn *src = static_cast<const TIn *>(a.bin) + (size_t)u.gi * a.R + g0;
-#pragma unroll
-    for (int g = 0; g < G; ++g) u.b[g] = src[g];
-}
-
-// The row's value for its G right-hand sides, computed as k_level does
-// (right-hand side, scaled by the reciprocal diagonal if any, then the ELL
-// slots in order; padding reads the ring's zero row, a dependency beyond the
-// ring the workspace, which this workgroup wrote before an earlier barrier).
-template <typename T, typename TIn, int G, int MW>
-__device__ __forceinline__ void sq_solve(const TriArgs &a, const SqItem<T, TIn, G, MW> &u, T *ring, int zrow,
-                                         int slots, int slotrow, int g0)
-{
-    if (!u.ok) return;
-    const int R = a.R;
-    T s[G];
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-        T sv = canon(static_cast<T>(u.b[g]));
-        if (a.dinv) sv = scale_rhs(sv, u.d);
-        s[g] = sv;
-    }
-    const int dst = a.xout ? u.dst : -1;
-#pragma unroll
-    for (int e = 0; e < MW; ++e) {
-        if (e < a.w) {
-            const int c = u.c[e];
-            const T v = u.v[e];
-            if (c >= 0) {
-                const T *dp = ring + (size_t)min(c, zrow) * R + g0;
-#pragma unroll
-                for (int g = 0; g < G; ++g) s[g] -= v * dp[g];
-            } else {
-                const T *dp = static_cast<const T *>(a.xw) + (size_t)(-2 - c) * R + g0;
-#pragma unroll
-                for (int g = 0; g < G; ++g) s[g] -= v * dp[g];
-            }
-        }
-    }
-    if (slots) {
-        T *o = ring + (size_t)slotrow * R + g0;
-#pragma unroll
-        for (int g = 0; g < G; ++g) o[g] = s[g];
-    }
-    if (a.write_xw || u.keep) {
-        T *w = static_cast<T *>(a.xw) + (size_t)u.x * R + g0;
-#pragma unroll
-        for (int g = 0; g < G; ++g) w[g] = s[g];
-    }
-    if (dst >= 0) {  // the output type is a launch argument (one instance serves both)
-        if (a.out_f64) {
-            double *w = static_cast<double *>(a.xout) + (size_t)dst * R + g0;
-#pragma unroll
-            for (int g = 0; g < G; ++g) w[g] = static_cast<double>(s[g]);
-        } else {
-            float *w = static_cast<float *>(a.xout) + (size_t)dst * R + g0;
-#pragma unroll
-            for (int g = 0; g < G; ++g) w[g] = static_cast<float>(s[g]);
-        }
-    }
-}
-
-// System queue with software pipelining: the same work and results as
-// k_sysq (workgroups take whole systems from a counter, a workgroup barrier
-// between levels, the last levels' values in an LDS ring), but the
-// wavefronts form k groups that take a system's levels in turn, and each
-// thread owns M items of its group's levels (item t = thread in group +
-// m * group size, G right-hand sides of one row), held in P register sets:
-// a set's row data is loaded P turns (P * k levels) before its level is
-// solved and its right-hand sides (whose address needs the row's gather
-// index) H = P / 2 turns before, so that the barrier-separated levels do
-// not wait on memory.  k is as large as the system's widest level allows.
-// Items beyond M * group size of a wide level are solved directly.  Needs no
-// CSR tail, ELL width 1..MW and R a multiple of G (checked by the host); rows
-// read beyond a ring are also stored to xw.  The level tables come as
-// separate restrict arguments, so that their uniform reads are scalar loads
-// (a vector load waited for inside a level would also wait for every
-// prefetch issued before it).
-template <typename T, typename TIn, int G, int MW, int M, int P>
-__global__ void __launch_bounds__(512) k_sysq_pipe(TriArgs a, const int32_t *__restrict__ lvp,
-                                                   const int32_t *__restrict__ lvrow,
-                                                   const int32_t *__restrict__ rings)
-{
-    constexpr int H = P / 2;
-    extern __shared__ __align__(16) unsigned char smem[];
-    __shared__ int s_q;
-    __shared__ unsigned s_epoch;
-    T *ring = reinterpret_cast<T *>(smem);
-    const int tid = threadIdx.x, nt = blockDim.x;
-    // the wavefront index as a uniform value: level numbers derived from it
-    // stay scalar, so the level table reads remain scalar loads
-    const int nw = nt >> 6, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int R = a.R, NG = R / G;
-    SqItem<T, TIn, G, MW> S[P][M];
-    if (tid == 0) s_epoch = __hip_atomic_load(a.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    for (;;) {
-        if (tid == 0)
-            s_q = (int)__hip_atomic_fetch_add(&a.epoch[2], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __syncthreads();
-        const int q = s_q;
-        if (q >= a.nparts) break;
-        const int slots = rings[2 * q], W = rings[2 * q + 1];
-        const int zrow = slots * W;
-        // optional clocks per system: start, end
-        if (a.trace && tid == 0 && a.trace_stride > 0)
-            a.trace[2 * (size_t)q * a.trace_stride] = __builtin_amdgcn_s_memrealtime();
-        for (int t = tid; t < R; t += nt) ring[(size_t)zrow * R + t] = T(0);
-        const int l0 = lvp[q], l1 = lvp[q + 1];
-        // a Krylov solve's mask of unfinished (system, rhs) problems: a
-        // system whose right-hand sides have all finished is skipped (its
-        // rows feed only its own problems)
-        if (a.act && l1 > l0) {
-            const int sys = a.seg ? a.seg[lvrow[l0]] : 0;
-            int live = 0;
-            for (int k2 = 0; k2 < R; ++k2) live |= a.act[(size_t)sys * R + k2];
-            if (!live) {
-                __syncthreads();  // every thread has read s_q before it is reused
-                continue;
-            }
-        }
-        // wavefront groups: the system's widest level needs `need`
-        // wavefronts (M items per thread); k = nw / wpg groups take the
-        // levels in turn (group g solves levels l0 + g, l0 + g + k, ...), so
-        // a wavefront's P register sets reach P * k levels ahead
-        const int need = (W * NG + 64 * M - 1) / (64 * M);
-        int wpg = 1;
-        while (wpg < need && wpg < nw) wpg *= 2;
-        const int k = nw / wpg, grp = wave / wpg, ng = wpg * 64, tl = tid - grp * ng;
-        int im[M], gm[M];
-#pragma unroll
-        for (int m = 0; m < M; ++m) {
-            const int t = tl + m * ng;
-            im[m] = t / NG;
-            gm[m] = (t - im[m] * NG) * G;
-        }
-        if (l1 > l0) {
-            // each set's right-hand sides right after its row data, so that
-            // (as in the steady state) many loads follow them: the counter
-            // wait before the first level then covers that set alone
-#pragma unroll
-            for (int p = 0; p < P; ++p) {
-#pragma unroll
-                for (int m = 0; m < M; ++m) sq_rows(a, lvrow, S[p][m], l0 + grp + p * k, l1, im[m]);
-                if (p < H) {
-#pragma unroll
-                    for (int m = 0; m < M; ++m) sq_rhs(a, S[p][m], gm[m]);
-                }
-            }
-        }
-        __syncthreads();
-        // one barrier per level, for every wavefront: the levels of the
-        // other groups before and after this group's level of the round
-        const int nr = (l1 - l0 + k - 1) / k;
-        for (int r0 = 0; r0 < nr; r0 += P) {
-#pragma unroll
-            for (int p = 0; p < P; ++p) {
-                const int r = r0 + p;
-                if (r >= nr) break;
-                const int nlr = min(k, l1 - l0 - r * k);  // levels in this round
-                for (int g = 0; g < min(grp, nlr); ++g) __syncthreads();
-                // this group's level (past the system's end in a short last
-                // round: nothing is solved there, the loads are clamped)
-                const int l = l0 + r * k + grp;
-#pragma unroll
-                for (int m = 0; m < M; ++m) sq_rhs(a, S[(p + H) % P][m], gm[m]);
-                const int base = slots ? ((l - l0) % slots) * W : 0;
-#pragma unroll
-                for (int m = 0; m < M; ++m)
-                    sq_solve<T, TIn, G, MW>(a, S[p][m], ring, zrow, slots, base + im[m], gm[m]);
-                // items beyond the pipeline (two at a time per thread
-                // measured slower: more registers)
-                const int items = l < l1 ? (lvrow[l + 1] - lvrow[l]) * NG : 0;
-                for (int t = tl + M * ng; t < items; t += ng) {
-                    SqItem<T, TIn, G, MW> u;
-                    const int i = t / NG;
-                    sq_rows(a, lvrow, u, l, l1, i);
-                    sq_rhs(a, u, (t - i * NG) * G);
-                    sq_solve<T, TIn, G, MW>(a, u, ring, zrow, slots, base + i, (t - i * NG) * G);
-                }
-#pragma unroll
-                for (int m = 0; m < M; ++m) sq_rows(a, lvrow, S[p][m], l + P * k, l1, im[m]);
-                if (grp < nlr) __syncthreads();
-                for (int g = grp + 1; g < nlr; ++g) __syncthreads();
-            }
-        }
-        if (a.trace && tid == 0 && a.trace_stride > 0)
-            a.trace[2 * (size_t)q * a.trace_stride + 1] = __builtin_amdgcn_s_memrealtime();
     }
     if (tid == 0) {
         const unsigned done = __hip_atomic_fetch_add(&a.epoch[1], 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
@@ -1212,40 +987,42 @@ __global__ void __launch_bounds__(256) k_fill_sentinel(T *p, size_t count, unsig
     if (counter && i == 0) *counter = 0u;  // the next launch's chunk counter
 }
 
-using SqKernel = void (*)(TriArgs, const int32_t *, const int32_t *, const int32_t *);
-
-// Pipelined system-queue instance for ELL width w: one item per thread
-// (wider levels solve their items beyond 512 directly), or, when at least a
-// quarter of the levels hold more than 512 items, two items per thread; two
-// register sets either way (four sets measured 7% slower on 256 batched
-// systems: more loads in flight per wavefront; more items per thread spill
-// registers).
-template <typename T, typename TIn, int G, int MW>
-SqKernel sysq_pipe_width(bool wide)
+// Columns of one item of the system queue: those the rings were sized for, or
+// fewer right-hand sides if the call has fewer.
+int32_t sysq_columns(const DevTri &d, int32_t R)
 {
-    if (!wide) return k_sysq_pipe<T, TIn, G, MW, 1, 2>;
-    return k_sysq_pipe<T, TIn, G, MW, 2, 2>;
+    const size_t row = (size_t)std::max(1, d.sq_lds_rows) * (d.dt == HEC_F64 ? 8 : 4);
+    int32_t c = std::min(R, std::max(d.sq_cols, kSysqColumns));
+    while (c > 1 && row * c > (size_t)device_max_lds()) --c;
+    return c;
 }
 
-// Right-hand sides per thread: 4 (pairs of lanes share a row, so a
-// wavefront's right-hand-side loads and result stores touch half as many
-// scattered cache lines as with 8) when the median level then still fits one
-// item per thread, else 8.
-inline int sysq_group(int R, int median_rows)
+// Columns of one item of the pipelined kernel (0: not for it, which needs
+// packed rows and vectors within 32-bit buffer offsets).  Four load a row's
+// data once for them, one gives more and shorter items; both triangles, four ->
+// one: 64 overlapping subdomains of a 128^3 grid with 4 / 8 / 16 right-hand
+// sides 1083 -> 712 / 1092 -> 1237 / 1195 -> 1938 us, 256 ILU(1) systems in
+// FP64 with 4 / 8 / 16 1541 -> 1074 / 1582 -> 2075 / 1788 -> 4160 us.  So four
+// from 8 right-hand sides on, unless items of one all run at once.
+int32_t sysq_pipe_columns(const DevTri &d, int32_t R)
 {
-    if (R % 4 == 0 && (R % 8 != 0 || (int64_t)median_rows * (R / 4) <= 512)) return 4;
-    return 8;
+    if (!d.sysq || !d.sq_packed || ((size_t)d.n + 1) * R * 8 >= kSysqDropped) return 0;
+    auto fits = [&](int32_t c) {
+        return (size_t)std::max(1, d.sq_lds_rows) * c * (d.dt == HEC_F64 ? 8 : 4) + 32 <= (size_t)device_max_lds();
+    };
+    if (R >= 2 * kSysqColumns && R % kSysqColumns == 0 && (int64_t)d.groups * R >= 2 * device_cus() && fits(kSysqColumns))
+        return kSysqColumns;
+    return fits(1) ? 1 : 0;
 }
 
-template <typename T, typename TIn>
-SqKernel sysq_pipe_kernel(int w, const std::vector<int32_t> &widths, int G, int R)
+SysqKernel sysq_pipe_kernel(const DevTri &d, const TriArgs &a, int32_t columns)
 {
-    const int groups = R / G;
-    size_t wide = 0;
-    for (const int32_t r : widths) wide += (size_t)r * groups > 512;
-    const bool many = 4 * wide >= widths.size();
-    if (G == 4) return w <= 4 ? sysq_pipe_width<T, TIn, 4, 4>(many) : sysq_pipe_width<T, TIn, 4, 8>(many);
-    return w <= 4 ? sysq_pipe_width<T, TIn, 8, 4>(many) : sysq_pipe_width<T, TIn, 8, 8>(many);
+    const bool in = a.in_f64 != 0, far = d.sq_global, f64 = d.dt == HEC_F64;
+    const int out = !a.xout ? 0 : (a.out_f64 ? 1 : 2);
+    using Select = SysqKernel (*)(int, bool, int, bool);
+    static constexpr Select one[2][3] = {{sq_f32_x1, sq_f32_d1, sq_f32_f1}, {sq_f64_x1, sq_f64_d1, sq_f64_f1}};
+    static constexpr Select four[2][3] = {{sq_f32_x4, sq_f32_d4, sq_f32_f4}, {sq_f64_x4, sq_f64_d4, sq_f64_f4}};
+    return (columns == 1 ? one : four)[f64][out](d.w, in, d.sq_rows, far);
 }
 
 // Right-hand sides one launch of a dataflow plan holds: a wavefront covers the
@@ -1326,26 +1103,31 @@ void launch_typed(DevTri &d, TriArgs a, hipStream_t st)
         return;
     }
     if (d.sysq) {
-        const size_t lds = (size_t)std::max(1, d.sq_lds_rows) * a.R * sizeof(T);
-        if (lds > (size_t)device_max_lds())
+        if ((size_t)d.sq_full_rows * a.R * sizeof(T) > (size_t)device_max_lds())
             fail(HEC_ERR_CAPACITY, "system queue: the LDS ring exceeds the device limit at this nrhs");
         a.nparts = d.groups;
-        // no CSR tail, ELL width 1..8 and right-hand sides in groups of
-        // 4 or 8: the pipelined kernel
-        if (!d.has_tail && d.w >= 1 && d.w <= 8 && a.R % 4 == 0) {
-            const SqKernel k =
-                sysq_pipe_kernel<T, TIn>(d.w, d.sq_widths, sysq_group(a.R, d.sq_median_rows), a.R);
-            const int32_t cap = capacity_of((const void *)k, 512, lds);
-            const int grid = std::max(1, std::min(d.groups, cap));
-            hipLaunchKernelGGL(k, dim3(grid), dim3(512), lds, st, a, a.sq_lvp, a.sq_lvrow, a.sq_ring);
+        a.ldr = a.R;
+        const int32_t piped = sysq_pipe_columns(d, a.ldr);
+        a.R = piped ? piped : sysq_columns(d, a.ldr);
+        a.cgroups = (a.ldr + a.R - 1) / a.R;
+        const int items = d.groups * a.cgroups;
+        const size_t lds = (size_t)std::max(1, d.sq_lds_rows) * a.R * sizeof(T);
+        if (piped) {
+            const SysqKernel k = sysq_pipe_kernel(d, a, piped);
+            if (!k) fail(HEC_ERR_INVALID_ARG, "internal: system queue with an unsupported record width");
+            const size_t all = ((lds + 15) & ~(size_t)15) + 16;
+            a.lds_ctl = (int32_t)all - 16;
+            const int32_t cap = capacity_of((const void *)k, kSysqThreads, all, true);
+            const int grid = std::max(1, std::min(items, cap));
+            hipLaunchKernelGGL(k, dim3(grid), dim3(kSysqThreads), all, st, a, d.sq_pcp.as<int32_t>(), d.sq_pc.as<int4>(),
+                               a.sq_ring);
             hip_check(hipGetLastError(), "k_sysq_pipe launch");
             return;
         }
         const int block = std::max(64, std::min(1024, d.block));
         const int32_t cap = capacity_of((const void *)k_sysq<T, TIn, TOut>, block, lds);
-        a.nparts = d.groups;
         if (d.sq_global) a.write_xw = 1;  // dependencies beyond the ring are read back from xw
-        const int grid = std::max(1, std::min(d.groups, cap));
+        const int grid = std::max(1, std::min(items, cap));
         hipLaunchKernelGGL((k_sysq<T, TIn, TOut>), dim3(grid), dim3(block), lds, st, a);
         hip_check(hipGetLastError(), "k_sysq launch");
         return;
@@ -1579,9 +1361,22 @@ TriArgs tri_args(const DevTri &d, const void *bin, hec_dtype_t in_dt, const int3
     a.sq_lvrow = d.sq_lvrow.as<int32_t>();
     a.sq_ring = d.sq_ring.as<int32_t>();
     a.sq_keep = d.sq_keep.as<int8_t>();
+    a.sq_far = d.sq_far.as<int32_t>();
+    a.rec_chunks = -1;
+    if (d.sysq && d.sq_packed) {
+        const RowRecord rec(d.w, d.ld, d.dt == HEC_F64 ? 8 : 4);
+        a.rec_chunks = rec.chunks;
+        a.rec_rest = rec.rest;
+    }
     a.in_f64 = in_dt == HEC_F64 ? 1 : 0;
     a.out_f64 = out_dt == HEC_F64 ? 1 : 0;
     return a;
+}
+
+void launch_any(DevTri &d, const TriArgs &a, hec_dtype_t in_dt, hec_dtype_t out_dt, hipStream_t st)
+{
+    if (d.dt == HEC_F64) launch_in<double>(d, a, in_dt, out_dt, st);
+    else launch_in<float>(d, a, in_dt, out_dt, st);
 }
 
 }  // namespace
@@ -1589,9 +1384,7 @@ TriArgs tri_args(const DevTri &d, const void *bin, hec_dtype_t in_dt, const int3
 void launch_tri(DevTri &d, const void *bin, hec_dtype_t in_dt, const int32_t *gather, void *xw, void *xout,
                 hec_dtype_t out_dt, const int32_t *scatter, int32_t R, hipStream_t st)
 {
-    const TriArgs a = tri_args(d, bin, in_dt, gather, xw, xout, out_dt, scatter, R);
-    if (d.dt == HEC_F64) launch_in<double>(d, a, in_dt, out_dt, st);
-    else launch_in<float>(d, a, in_dt, out_dt, st);
+    launch_any(d, tri_args(d, bin, in_dt, gather, xw, xout, out_dt, scatter, R), in_dt, out_dt, st);
 }
 
 void launch_lu(DevTri &L, DevTri &U, bool lu_shared, const void *r, hec_dtype_t in_dt, const int32_t *gather_l, void *y,
@@ -1621,8 +1414,14 @@ void launch_lu(DevTri &L, DevTri &U, bool lu_shared, const void *r, hec_dtype_t 
         }
         return;
     }
-    launch_tri(L, r, in_dt, gather_l, y, nullptr, in_dt, nullptr, R, st);
-    launch_tri(U, y, L.dt, qmap, uw, z, out_dt, scatter_u, R, st);
+    // two system queues: y is stored group of columns by group of columns, so
+    // that an item writes and reads whole cache lines of it
+    const bool grouped = L.dt == U.dt && sysq_pipe_columns(L, R) > 0 && sysq_pipe_columns(L, R) == sysq_pipe_columns(U, R);
+    TriArgs a = tri_args(L, r, in_dt, gather_l, y, nullptr, in_dt, nullptr, R);
+    TriArgs b = tri_args(U, y, L.dt, qmap, uw, z, out_dt, scatter_u, R);
+    a.xw_grouped = b.bin_grouped = grouped ? 1 : 0;
+    launch_any(L, a, in_dt, in_dt, st);
+    launch_any(U, b, L.dt, out_dt, st);
 }
 
 }  // namespace hec

@@ -1,0 +1,110 @@
+"""The system queue at the edges of its ranges, bit for bit against one launch
+per level (the same summation order): levels of one row to more than two pieces,
+values read beyond the LDS ring, and columns in and out of whole groups."""
+import numpy as np
+import pytest
+
+from synth import CSR
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+import paper_1606_00541_amd as H  # noqa: E402
+
+# rows of a level, levels, levels back to the oldest value read.  FP64 rings of
+# four columns hold 5119 rows, and half of that where values are read beyond
+# them: the third to last systems read beyond theirs.
+SYSTEMS = [(1, 1, 1), (1, 9, 3), (30, 110, 100), (100, 70, 45), (600, 30, 20), (1100, 12, 9)]
+
+
+def banded(systems, symmetric):
+    """Independent systems whose levels hold m rows each: a row reads the row
+    above it, its neighbour, and two rows `back` levels away."""
+    rows, base = [], 0
+    for m, nlev, back in systems:
+        for i in range(m * nlev):
+            c = {i - m, i - m - 1, i - m * back, i - m * back - 2} if i >= m else set()
+            c = {j for j in c if 0 <= j and j // m < i // m}
+            if symmetric:
+                up = {i + m, i + m + 1, i + m * back, i + m * back + 2}
+                c |= {j for j in up if j < m * nlev}
+            rows.append(sorted(base + j for j in c | {i}))
+        base += m * nlev
+    rp = np.cumsum([0] + [len(r) for r in rows]).astype(np.int32)
+    ci = np.concatenate([np.asarray(r) for r in rows]).astype(np.int32)
+    rng = np.random.default_rng(base)
+    v = rng.uniform(-0.2, 0.2, ci.size)
+    v[ci == np.repeat(np.arange(base), np.diff(rp))] = rng.uniform(1.5, 2.5, base)
+    return CSR(base, rp, ci, v)
+
+
+QUEUE = dict(schedule="level_persistent", kernel_variant=7)
+
+
+@pytest.mark.parametrize("vec", ["f64", "f32"])
+@pytest.mark.parametrize("dt", ["f64", "f32"])
+@pytest.mark.parametrize("system", SYSTEMS)
+def test_one_system(system, dt, vec):
+    L = banded([system], False)
+    rng = np.random.default_rng(3)
+    vt = torch.float64 if vec == "f64" else torch.float32
+    for nrhs in (1, 4, 6, 8):
+        b = torch.from_numpy(rng.standard_normal((L.n, nrhs))).to(vt).cuda()
+        out = []
+        for t in (dict(schedule="level_launch"), dict(QUEUE, max_nrhs=nrhs)):
+            p = H.tri_analyze(L, "lower", dtype=dt, tune=H.tune_default(**t))
+            x = torch.empty_like(b)
+            for _ in range(2):
+                x.fill_(float("nan"))
+                H.tri_solve_lower(p, b, x)
+            torch.cuda.synchronize()
+            H.tri_plan_check(p)
+            out.append(x)
+        assert H.tri_plan_stats(p)["sysq"] == 1
+        assert torch.equal(out[0], out[1]), nrhs
+
+
+@pytest.mark.parametrize("nrhs,most", [(4, 4), (16, 16), (8, 16), (5, 8), (16, 8)])
+@pytest.mark.parametrize("dt", ["f64", "f32"])
+def test_batched_factors(dt, nrhs, most):
+    # both triangles through the workspace between them; more systems than one
+    # so that items of different widths follow each other in a workgroup
+    systems = SYSTEMS + SYSTEMS[:4]
+    A = banded(systems, True)
+    ptr = np.cumsum([0] + [m * nlev for m, nlev, _ in systems]).astype(np.int32)
+    r = torch.from_numpy(np.random.default_rng(5).standard_normal((A.n, nrhs))).cuda()
+    out = []
+    for t in (dict(schedule="level_launch"), dict(QUEUE, max_nrhs=most)):
+        f = H.batch_setup(A, ptr, "ilu0", factor_dtype=dt, tune=H.tune_default(**t))
+        z = torch.full_like(r, float("nan"))
+        if nrhs > most and "max_nrhs" in t:  # the rings that max_nrhs columns fill do not take twice as many
+            with pytest.raises(H.HecError, match="LDS ring exceeds"):
+                H.ilu_apply(f, r, z)
+            return
+        for _ in range(2):
+            H.ilu_apply(f, r, z)
+        torch.cuda.synchronize()
+        out.append(z)
+    assert torch.equal(out[0], out[1])
+
+
+def test_automatic_choice_by_columns():
+    # too few systems for half the compute units, enough with their columns;
+    # any number of right-hand sides is accepted
+    import scipy.sparse as sp
+    import synth
+
+    P = synth.poisson3d(32)
+    m = sp.block_diag([P.to_scipy()] * 16).tocsr()
+    m.sort_indices()
+    A = CSR(m.shape[0], m.indptr.astype(np.int32), m.indices.astype(np.int32), m.data.copy())
+    ptr = (np.arange(17) * P.n).astype(np.int32)
+    fs = [H.batch_setup(A, ptr, "ilu0", tune=H.tune_default(**t)) for t in (dict(schedule="level_launch"), dict(max_nrhs=16))]
+    assert H.tri_plan_stats(H.ilu_plans(fs[1])[0])["sysq"] == 1
+    for nrhs in (1, 5, 16, 48):
+        r = torch.from_numpy(np.random.default_rng(nrhs).standard_normal((A.n, nrhs))).cuda()
+        z = [torch.full_like(r, float("nan")) for _ in fs]
+        for f, x in zip(fs, z):
+            H.ilu_apply(f, r, x)
+        torch.cuda.synchronize()
+        assert torch.equal(z[0], z[1]), nrhs
