@@ -84,7 +84,9 @@ typedef struct hec_tune {
                                rows having more than w off-diagonals */
     int32_t schedule;       /* hec_schedule_t */
     int32_t num_groups;     /* persistent workgroups; 0 = one per compute unit (at most the
-                               co-resident capacity; larger requests fail with CAPACITY) */
+                               co-resident capacity; larger requests fail with CAPACITY);
+                               the dataflow kernel then takes as many parts as an estimate of
+                               the solve finds best, and U the parts of its L */
     int32_t merge_rows;     /* level-merge threshold: a level with fewer rows than this
                                is not split across workgroups */
     int32_t group_lanes;    /* lanes cooperating on one row when a step holds long
@@ -94,7 +96,10 @@ typedef struct hec_tune {
     int32_t part_rows;      /* owner schedule: target rows per owned part (0 = auto) */
     int32_t host_only;      /* 1 = build the host plan only (no device upload) */
     int32_t max_nrhs;       /* workspace is allocated for up to this many RHS (grows on demand);
-                               plans run by the dataflow kernel accept at most this many */
+                               plans run by the dataflow kernel with an explicit num_groups
+                               accept at most this many (if a step then fills a wavefront),
+                               others take as many as one workgroup per compute unit would,
+                               in groups of columns */
     int32_t block_threads;  /* threads per workgroup (64..1024, multiple of 64) */
     int32_t chunk_rows;     /* owner schedule: rows of matrix data staged in LDS per chunk
                                (1, 2 or 4 times block_threads; 0 = the smallest of
@@ -129,12 +134,15 @@ typedef struct hec_tune {
                                barrier between levels, the last levels of the system held in
                                an LDS ring (no co-residency needed).  Without a CSR tail, with
                                ELL width 1..8 (the automatic width covers the longest row up
-                               to 8) and a multiple of 4 right-hand sides, a pipelined kernel of 512
-                               threads prefetches each level's rows several levels ahead;
+                               to 8) and at most two values a row older than the ring, a
+                               pipelined kernel of 512 threads loads each level's rows several
+                               levels ahead and takes one or four columns of a system at a time;
                                otherwise block_threads sets the workgroup.
                                Schedule AUTO picks the dataflow kernel when its LDS holds
                                every part, else 7 for at least half as many independent
-                               systems as compute units, else 5 unless the levels are very
+                               systems as compute units or, with max_nrhs above 8 and where the
+                               pipelined kernel takes it, at least as many columns of systems
+                               (nsys * max_nrhs) as compute units, else 5 unless the levels are very
                                wide (2^20 (row, rhs) items per level on average or more),
                                else one launch per level */
 } hec_tune_t;

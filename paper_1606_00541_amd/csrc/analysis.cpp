@@ -605,7 +605,7 @@ void make_dataflow(Schedule &s, ExecHost &ex, const std::vector<int32_t> &xlev,
                    const std::vector<std::vector<int32_t>> &run_wave, int32_t waves)
 {
     const int32_t G = s.groups, n = ex.n;
-    auto each_col = [&](int32_t x, const std::function<void(int32_t &)> &f) {
+    auto each_col = [&](int32_t x, auto &&f) {
         for (int32_t e = 0; e < ex.w; ++e) f(ex.ell_col[(size_t)e * ex.ld + x]);
         if (!ex.tail_ptr.empty())
             for (int32_t p = ex.tail_ptr[x]; p < ex.tail_ptr[x + 1]; ++p) f(ex.tail_col[p]);
@@ -954,7 +954,7 @@ void build_sysq(ExecHost &ex, const Levels &lv, const std::vector<int32_t> &sys,
                 lev_of[x] = l - lvp[k];
                 sys_of[x] = k;
             }
-    auto each_col = [&](int32_t x, const std::function<void(int32_t &)> &f) {
+    auto each_col = [&](int32_t x, auto &&f) {
         for (int32_t e = 0; e < ex.w; ++e) f(ex.ell_col[(size_t)e * ex.ld + x]);
         if (!ex.tail_ptr.empty())
             for (int32_t p = ex.tail_ptr[x]; p < ex.tail_ptr[x + 1]; ++p) f(ex.tail_col[p]);
@@ -1518,7 +1518,13 @@ TriHost analyze(const Csr &a, bool upper, bool unit, hec_dtype_t dt, const Tune 
         Tune d = tu;
         d.variant = 4;
         d.choose_parts = auto_sched;
-        const bool df_ok = d.block_threads <= 384 && d.max_nrhs <= 64 && d.ell_width <= 16;
+        // right-hand sides and solutions beyond the LDS of all workgroups: not
+        // tried (setup of 16 systems of 48^3 rows, 16 right-hand sides, on the
+        // host 2.23 -> 0.99 s)
+        const int64_t groups_most = d.num_groups > 0 ? d.num_groups : (dev.cus > 0 ? dev.cus : 256);
+        const bool beyond = auto_sched && 2 * (int64_t)a.n * std::max(1, d.max_nrhs) * (dt == HEC_F64 ? 8 : 4) >
+                                              groups_most * (int64_t)(dev.lds > 0 ? dev.lds : 163840);
+        const bool df_ok = !beyond && d.block_threads <= 384 && d.max_nrhs <= 64 && d.ell_width <= 16;
         // the parts of the other triangle first, if there is one
         for (int pass = d.share_part && auto_sched ? 0 : 1; df_ok && pass < 2; ++pass) {
             if (pass == 1) d.share_part = nullptr;
