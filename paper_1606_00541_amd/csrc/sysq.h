@@ -257,7 +257,7 @@ __global__ void __launch_bounds__(512) k_sysq_pipe(TriArgs a, const int32_t *__r
         }
         __syncthreads();
         // one barrier per piece, for every wavefront: the pieces of the other
-        // groups before and after this group's piece of the round.  Whole
+        // groups before and after this group's piece of the turn.  Whole
         // rotations: turns past the last piece have no rows, no barrier and
         // nothing to store (leaving early would cost the exact counts)
         const int nr = (l1 - l0 + k - 1) / k;
@@ -265,7 +265,7 @@ __global__ void __launch_bounds__(512) k_sysq_pipe(TriArgs a, const int32_t *__r
 #pragma unroll
             for (int p = 0; p < P; ++p) {
                 const int r = r0 + p;
-                const int nlr = min(k, l1 - l0 - r * k);  // pieces in this round
+                const int nlr = min(k, l1 - l0 - r * k);  // pieces in this turn of the groups
                 for (int g = 0; g < min(grp, nlr); ++g) __syncthreads();
                 const int4 next = bounds(l0 + (r + P) * k + grp);
                 rhs(S[(p + H) % P]);
