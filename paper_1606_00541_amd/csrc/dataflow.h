@@ -124,9 +124,18 @@ __device__ __forceinline__ void df_copy_ints(int *dst, const int32_t *src, int c
     }
 }
 
-// Everything but the right-hand side: sentinels, the zero row, index lists,
-// and this part's slots of the mailbox's other half for the next launch.
-template <typename T> __device__ __forceinline__ void df_fill_lists(const TriArgs &a, const DfPart<T> &p, int R, T *other)
+// Empty the mailbox half the next launch reads, each workgroup its share.
+// Every workgroup does it before its first wait, for all plans of the launch:
+// a launch whose waits give up still advances the epochs, so a slot left out
+// would offer the next launch the value of the one before.
+template <typename T> __device__ __forceinline__ void df_clear(const TriArgs &a, T *other)
+{
+    const size_t count = (size_t)a.nexp * a.mbox_stride, step = (size_t)gridDim.x * blockDim.x;
+    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < count; i += step) other[i] = sentinel<T>();
+}
+
+// Everything but the right-hand side: sentinels, the zero row and index lists.
+template <typename T> __device__ __forceinline__ void df_fill_lists(const TriArgs &a, const DfPart<T> &p, int R)
 {
     const int tid = threadIdx.x, nt = blockDim.x;
     for (int t = tid; t < p.win * R; t += nt) p.xl[t] = sentinel<T>();
@@ -135,10 +144,6 @@ template <typename T> __device__ __forceinline__ void df_fill_lists(const TriArg
     df_copy_ints(p.erl, a.exp_row + p.e0, p.nex, -p.lo);
     df_copy_ints(p.stl, a.step_pack + p.s0, p.ns, 0);
     if (tid < kDataflowPad) p.stl[p.ns + tid] = 0;
-    if (a.nexp > 0) {
-        const size_t m0 = (size_t)p.e0 * a.mbox_stride, m1 = (size_t)(p.e0 + p.nex) * a.mbox_stride;
-        for (size_t i = m0 + tid; i < m1; i += nt) other[i] = sentinel<T>();
-    }
 }
 
 // The right-hand side, gathered and scaled.  The gather indices of a round
@@ -517,13 +522,17 @@ __global__ void __launch_bounds__(512) k_dataflow(TriArgs a)
             break;
         }
         const int g = a.queue ? ctl->part : (int)blockIdx.x;
-        if (g >= a.nparts) break;
+        if (g >= a.nparts) {
+            if (round == 0) df_clear(a, other);
+            break;
+        }
         const DfPart<T> pt = df_part<T>(a, g, R, smem);
         unsigned long long t_fill = 0;
         df_sweep<T, W, TAIL, R1, TRACE>(a, pt, R, mrd, &ctl->abort, t_fill, [&]() {
             if (a.in_f64) df_fill_b<T, UNIT, R1>(a, pt, R, static_cast<const double *>(a.bin));
             else df_fill_b<T, UNIT, R1>(a, pt, R, static_cast<const float *>(a.bin));
-            df_fill_lists(a, pt, R, other);
+            df_fill_lists(a, pt, R);
+            if (round == 0) df_clear(a, other);
         });
         const unsigned long long t_done = TRACE ? __builtin_amdgcn_s_memrealtime() : 0ull;
         df_report(a, ctl);
@@ -593,14 +602,16 @@ __global__ void __launch_bounds__(512) k_dataflow_lu(TriArgs l, TriArgs u)
     df_sweep<T, W, false, R1, false>(l, pl, R, half(l, ctl->epoch), &ctl->abort, t_fill, [&]() {
         if (l.in_f64) df_fill_b<T, true, R1>(l, pl, R, static_cast<const double *>(l.bin));
         else df_fill_b<T, true, R1>(l, pl, R, static_cast<const float *>(l.bin));
-        df_fill_lists(l, pl, R, half(l, ctl->epoch + 1u));
+        df_fill_lists(l, pl, R);
+        df_clear(l, half(l, ctl->epoch + 1u));
+        df_clear(u, half(u, ctl->epoch2 + 1u));
     });
     if (!ctl->abort) {
         const DfPart<T> pu = df_part<T>(u, g, R, smem);
         df_sweep<T, W, false, R1, false>(u, pu, R, half(u, ctl->epoch2), &ctl->abort, t_fill, [&]() {
             df_fill_y<T, R1>(u, pu, R, pl.lo);
             __syncthreads();
-            df_fill_lists(u, pu, R, half(u, ctl->epoch2 + 1u));
+            df_fill_lists(u, pu, R);
         });
         if (!ctl->abort) df_store(u, pu, R);
     }
