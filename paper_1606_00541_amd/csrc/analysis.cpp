@@ -894,6 +894,13 @@ PartEstimate estimate_parts(const Csr &a, bool upper, const Levels &lv, const st
     return out;
 }
 
+// The automatic schedule chooses the parts, unless the caller asks for their
+// number or shape: then every triangle is cut as asked, also U of an ILU.
+bool parts_open(const Tune &t)
+{
+    return t.choose_parts && t.partition == 0 && t.part_rows == 0 && t.num_groups == 0;
+}
+
 // Contiguous ranges of about n / P rows that end at block boundaries where
 // they can: a block of up to 5/4 of that stays whole, longer ones are cut
 // evenly.  Returns the number of parts.
@@ -1200,7 +1207,8 @@ void build_exec(TriHost &t, const Csr &a, const Tune &tune, const DeviceShape &d
         parts = std::max(1, std::min(parts, std::max(1, n)));
         std::vector<int32_t> part_of;
         int32_t gx = 0, gy = 0, gz = 0;
-        const bool shared = tune.choose_parts && tune.share_part;
+        const bool choose = want_df && !queue && parts_open(tune);
+        const bool shared = choose && tune.share_part;
         const bool grid = !queue && !shared && (tune.partition == 0 || tune.partition == 3) && detect_grid(a, gx, gy, gz);
         auto contiguous = [&](int32_t count) {
             std::vector<int32_t> po(n);
@@ -1222,14 +1230,12 @@ void build_exec(TriHost &t, const Csr &a, const Tune &tune, const DeviceShape &d
             }
             return po;
         };
-        const bool choose = tune.choose_parts && want_df && !queue && tune.partition == 0 && tune.part_rows == 0 &&
-                            tune.num_groups == 0;
         const size_t ts = t.dt == HEC_F64 ? 8 : 4;
         const size_t lds_cap = dev.lds > 0 ? (size_t)dev.lds : 163840;
         const bool blocks = sys_ptr && sys_ptr->size() > 2;
         if (queue) {
             part_of = queue_parts(a, t.upper, lv, sys_ptr, tune, dev, t.dt, parts);
-        } else if (choose && tune.share_part) {
+        } else if (shared) {
             part_of = *tune.share_part;
             parts = tune.share_parts;
             accept = tune.share_accept;
@@ -1526,7 +1532,7 @@ TriHost analyze(const Csr &a, bool upper, bool unit, hec_dtype_t dt, const Tune 
                                               groups_most * (int64_t)(dev.lds > 0 ? dev.lds : 163840);
         const bool df_ok = !beyond && d.block_threads <= 384 && d.max_nrhs <= 64 && d.ell_width <= 16;
         // the parts of the other triangle first, if there is one
-        for (int pass = d.share_part && auto_sched ? 0 : 1; df_ok && pass < 2; ++pass) {
+        for (int pass = d.share_part && parts_open(d) ? 0 : 1; df_ok && pass < 2; ++pass) {
             if (pass == 1) d.share_part = nullptr;
             try {
                 attempt(d);
