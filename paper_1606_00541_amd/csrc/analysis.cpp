@@ -1268,7 +1268,12 @@ void build_exec(TriHost &t, const Csr &a, const Tune &tune, const DeviceShape &d
                 if (grid) consider(grid_parts(n, gx, gy, gz, c), c);
                 consider(contiguous(c), c);
             }
-            if (best_parts == 0) fail(HEC_ERR_CAPACITY, "dataflow kernel: no parts fit the LDS");
+            if (best_parts == 0) {
+                // imports can outweigh the rows (16 entries a row anywhere
+                // before it): one part per compute unit holds the fewest
+                part_of = full_set();
+                best_parts = parts;
+            }
             if (best_parts < parts) {
                 // calls with more right-hand sides than max_nrhs run in
                 // groups of columns as far as one part per compute unit

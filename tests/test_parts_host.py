@@ -1,5 +1,6 @@
 """Host-only checks of the parts the automatic schedule gives the dataflow
 kernel (no GPU is touched)."""
+import numpy as np
 import pytest
 
 import synth
@@ -23,3 +24,19 @@ def test_u_of_an_ilu_is_cut_like_a_triangle_of_its_own(tune):
     assert u["dataflow"] == alone["dataflow"] == 1
     for key in ("num_groups", "nexport", "nremote", "crit_hops"):
         assert u[key] == alone[key], key
+
+
+def test_parts_with_many_imports_fall_back_to_the_full_set():
+    # 16 entries a row anywhere before it: a part of few large ones reads most
+    # of the solution, which the LDS holds only beside small parts
+    n, w = 81920, 16
+    rng = np.random.default_rng(1)
+    i = np.arange(n)[:, None]
+    j = np.sort(np.floor(rng.uniform(0.0, 1.0, (n, w)) * i).astype(np.int64), axis=1)
+    ok = j < i
+    ok[:, 1:] &= j[:, 1:] != j[:, :-1]
+    keep = np.concatenate([ok, np.ones((n, 1), bool)], axis=1)
+    rp = np.concatenate([[0], np.cumsum(keep.sum(axis=1))]).astype(np.int32)
+    col = np.concatenate([j, i], axis=1)[keep].astype(np.int32)
+    st = H.tri_plan_stats(H.tri_analyze(CSR(n, rp, col, np.ones(col.size)), "lower", tune=H.tune_default(host_only=1)))
+    assert st["dataflow"] == 1 and st["num_groups"] == 256
