@@ -586,6 +586,13 @@ size_t dataflow_lds_bytes(int32_t rows, int32_t ints, int32_t R, size_t tsize)
     return ((vals + 15) & ~(size_t)15) + (((size_t)ints * 4 + 15) & ~(size_t)15) + kDataflowCtlBytes;
 }
 
+int32_t dataflow_columns(int32_t rows, int32_t ints, int32_t longest, size_t tsize, size_t lds)
+{
+    int32_t r = std::max(1, 64 / std::max(1, longest));
+    while (r > 1 && dataflow_lds_bytes(rows, ints, r, tsize) > lds) --r;
+    return r;
+}
+
 RowRecord::RowRecord(int32_t w_, int32_t ld_, int32_t tsize_) : w(w_), ld(ld_), tsize(tsize_)
 {
     const int32_t nb = w * (tsize / 4) + (w + 1) / 2;
@@ -689,9 +696,11 @@ void make_dataflow(Schedule &s, ExecHost &ex, const std::vector<int32_t> &xlev,
     // 5. step descriptors (a step has 1..64 rows, a window fewer than 2^16)
     s.step_pack.resize((size_t)s.nsteps());
     for (int32_t g = 0; g < G; ++g)
-        for (int32_t q = s.step_ptr[g]; q < s.step_ptr[g + 1]; ++q)
-            s.step_pack[q] = (s.step_row[2 * q] - s.window[2 * g]) |
-                             (s.step_row[2 * q + 1] - s.step_row[2 * q] - 1) * 16 << 16;
+        for (int32_t q = s.step_ptr[g]; q < s.step_ptr[g + 1]; ++q) {
+            const int32_t rows = s.step_row[2 * q + 1] - s.step_row[2 * q];
+            s.step_pack[q] = (s.step_row[2 * q] - s.window[2 * g]) | (rows - 1) * 16 << 16;
+            s.df_step_rows = std::max(s.df_step_rows, rows);
+        }
     s.dataflow = true;
 }
 
@@ -1209,7 +1218,7 @@ void build_exec(TriHost &t, const Csr &a, const Tune &tune, const DeviceShape &d
         int32_t gx = 0, gy = 0, gz = 0;
         const bool choose = want_df && !queue && parts_open(tune);
         const bool shared = choose && tune.share_part;
-        const bool grid = !queue && !shared && (tune.partition == 0 || tune.partition == 3) && detect_grid(a, gx, gy, gz);
+        bool grid = !queue && !shared && (tune.partition == 0 || tune.partition == 3) && detect_grid(a, gx, gy, gz);
         auto contiguous = [&](int32_t count) {
             std::vector<int32_t> po(n);
             for (int32_t g = 0; g < count; ++g) {
@@ -1233,18 +1242,34 @@ void build_exec(TriHost &t, const Csr &a, const Tune &tune, const DeviceShape &d
         const size_t ts = t.dt == HEC_F64 ? 8 : 4;
         const size_t lds_cap = dev.lds > 0 ? (size_t)dev.lds : 163840;
         const bool blocks = sys_ptr && sys_ptr->size() > 2;
+        auto estimate = [&](const std::vector<int32_t> &po, int32_t count, size_t lds, double limit) {
+            return estimate_parts(a, t.upper, lv, po, count, df_waves, w0, R, ts, lds, limit);
+        };
+        // Right-hand sides the plan takes in groups of columns: as many as the
+        // full set of parts would at once, or any number where that set does
+        // not fit and a kernel without a limit would run (0: no more than the
+        // parts themselves hold).
+        auto accepted = [&](const std::vector<int32_t> &po) {
+            const std::vector<int32_t> full = full_set();
+            if (po == full) return 0;
+            const PartEstimate e = estimate(full, parts, SIZE_MAX, INFINITY);
+            if (dataflow_lds_bytes(e.rows, e.ints, R, ts) > lds_cap) return INT32_MAX;
+            return std::max(R, dataflow_columns(e.rows, e.ints, e.longest, ts, lds_cap));
+        };
         if (queue) {
             part_of = queue_parts(a, t.upper, lv, sys_ptr, tune, dev, t.dt, parts);
         } else if (shared) {
+            // no less than L takes, and no less than a plan of its own would
             part_of = *tune.share_part;
+            grid = detect_grid(a, gx, gy, gz);
+            accept = std::max(tune.share_accept, accepted(part_of));
             parts = tune.share_parts;
-            accept = tune.share_accept;
         } else if (choose && n > 0 && n <= kEstimateRows) {
             double best = INFINITY;
             int32_t best_parts = 0;
             auto consider = [&](std::vector<int32_t> &&po, int32_t count) {
                 if (count < 1 || count > parts) return;
-                const PartEstimate e = estimate_parts(a, t.upper, lv, po, count, df_waves, w0, R, ts, lds_cap, best);
+                const PartEstimate e = estimate(po, count, lds_cap, best);
                 if (e.us < best) {
                     best = e.us;
                     best_parts = count;
@@ -1274,15 +1299,7 @@ void build_exec(TriHost &t, const Csr &a, const Tune &tune, const DeviceShape &d
                 part_of = full_set();
                 best_parts = parts;
             }
-            if (best_parts < parts) {
-                // calls with more right-hand sides than max_nrhs run in
-                // groups of columns as far as one part per compute unit
-                // would take them at once
-                const PartEstimate e = estimate_parts(a, t.upper, lv, full_set(), parts, df_waves, w0, R, ts, SIZE_MAX, INFINITY);
-                int32_t r = 64 / std::max(1, e.longest);
-                while (r > R && dataflow_lds_bytes(e.rows, e.ints, r, ts) > lds_cap) --r;
-                accept = r;
-            }
+            accept = accepted(part_of);
             parts = best_parts;
         } else if (grid) {
             part_of = full_set();
@@ -1294,7 +1311,8 @@ void build_exec(TriHost &t, const Csr &a, const Tune &tune, const DeviceShape &d
                 std::vector<int32_t> po;
                 const int32_t k = block_parts(n, *sys_ptr, parts, po);
                 if (k <= parts && critical_hops(a, t.upper, po) < critical_hops(a, t.upper, part_of) &&
-                    estimate_parts(a, t.upper, lv, po, k, df_waves, w0, R, ts, lds_cap, INFINITY).us < INFINITY) {
+                    estimate(po, k, lds_cap, INFINITY).us < INFINITY) {
+                    accept = accepted(po);
                     part_of.swap(po);
                     parts = k;
                 }

@@ -169,9 +169,7 @@ void upload_tri(DevTri &d, const TriHost &t, int32_t max_nrhs)
             d.queue = s.queue;
             upload(d.wave_ptr, s.wave_ptr);
             upload(d.step_pack, s.step_pack);
-            d.df_step_rows = 0;
-            for (int32_t q = 0; q < s.nsteps(); ++q)
-                d.df_step_rows = std::max(d.df_step_rows, s.step_row[2 * q + 1] - s.step_row[2 * q]);
+            d.df_step_rows = s.df_step_rows;
         }
         d.max_lanes_one = std::all_of(s.step_lanes.begin(), s.step_lanes.end(), [](int32_t v) { return v == 1; });
         if (s.sysq) {
@@ -398,7 +396,9 @@ void build_ilu(ilu_s &f, const Csr &L, const Csr &U, hec_dtype_t fdt, const Tune
         // U on L's parts: both then finish and start a part on the same workgroup
         tun.share_part = &f.L.h.ex.part;
         tun.share_parts = f.L.h.ex.parts;
-        tun.share_accept = f.L.h.ex.sched.df_accept;
+        const Schedule &s = f.L.h.ex.sched;
+        tun.share_accept = std::max(s.df_accept, dataflow_columns(s.df_rows, s.df_ints, s.df_step_rows, vsize(fdt),
+                                                                  tu.host_only ? 163840 : device_max_lds()));
     }
     build_plan(f.U, U, true, false, fdt, tun, blocks);
     if (!tu.host_only) {

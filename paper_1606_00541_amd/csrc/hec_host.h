@@ -92,6 +92,7 @@ struct Schedule {
     int32_t df_ints = 0;             // max over groups of imports + exports + steps + kDataflowPad
     std::vector<int32_t> step_pack;  // per step: first window row | 16 (rows - 1) << 16
     int32_t df_waves = 0;            // compute wavefronts per group
+    int32_t df_step_rows = 0;        // rows of the longest step
     int32_t df_accept = 0;           // right-hand sides accepted in groups of columns beyond what fits at once
     std::vector<int32_t> wave_ptr;   // [groups*df_waves+1]: steps of wavefront w of group g
     // queue mode: `groups` parts, more than the workgroups that run them; the
@@ -183,6 +184,9 @@ constexpr uint32_t kSysqDropped = 0xf0000000u;  // byte offset past every output
 inline int32_t sysq_width(int32_t w) { return w <= 2 ? 2 : (w <= 4 ? w : (w <= 6 ? 6 : 8)); }
 constexpr int32_t kDataflowPad = 16;  // descriptors the kernel may read past a part's last step
 size_t dataflow_lds_bytes(int32_t rows, int32_t ints, int32_t R, size_t tsize);
+// Right-hand sides one launch holds: a wavefront covers the longest step, the
+// LDS (of `lds` bytes) every part.
+int32_t dataflow_columns(int32_t rows, int32_t ints, int32_t longest, size_t tsize, size_t lds);
 // Smallest ELL width >= w the dataflow kernel is built for (1..8, 10, 12,
 // 16), or -1 above 16; and its largest workgroup (threads) at that width.
 int32_t dataflow_width(int32_t w);

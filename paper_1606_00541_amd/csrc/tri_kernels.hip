@@ -1025,14 +1025,10 @@ SysqKernel sysq_pipe_kernel(const DevTri &d, const TriArgs &a, int32_t columns)
     return (columns == 1 ? one : four)[f64][out](d.w, in, d.sq_rows, far);
 }
 
-// Right-hand sides one launch of a dataflow plan holds: a wavefront covers the
-// longest step, the LDS every part.
+// Right-hand sides one launch of a dataflow plan holds.
 int32_t dataflow_columns(const DevTri &d)
 {
-    const size_t ts = d.dt == HEC_F64 ? 8 : 4;
-    int32_t r = std::max(1, 64 / std::max(1, d.df_step_rows));
-    while (r > 1 && dataflow_lds_bytes(d.df_rows, d.df_ints, r, ts) > (size_t)device_max_lds()) --r;
-    return r;
+    return hec::dataflow_columns(d.df_rows, d.df_ints, d.df_step_rows, d.dt == HEC_F64 ? 8 : 4, (size_t)device_max_lds());
 }
 
 // Two import wavefronts, but one beside wide rows (see df_import) or where
