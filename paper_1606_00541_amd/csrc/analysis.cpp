@@ -1245,16 +1245,34 @@ void build_exec(TriHost &t, const Csr &a, const Tune &tune, const DeviceShape &d
         auto estimate = [&](const std::vector<int32_t> &po, int32_t count, size_t lds, double limit) {
             return estimate_parts(a, t.upper, lv, po, count, df_waves, w0, R, ts, lds, limit);
         };
-        // Right-hand sides the plan takes in groups of columns: as many as the
-        // full set of parts would at once, or any number where that set does
-        // not fit and a kernel without a limit would run (0: no more than the
-        // parts themselves hold).
+        // The full set of parts, with what it would take in one launch.  Plans
+        // on other parts take as many right-hand sides in groups of columns,
+        // and any number where the full set does not fit and a kernel without
+        // a limit would run (0: no more than the parts themselves hold).
+        std::vector<int32_t> full;
+        PartEstimate full_est;
+        auto full_needed = [&]() {
+            if (!full.empty() || n == 0) return;
+            full = full_set();
+            full_est = estimate(full, parts, SIZE_MAX, INFINITY);
+        };
         auto accepted = [&](const std::vector<int32_t> &po) {
-            const std::vector<int32_t> full = full_set();
+            full_needed();
             if (po == full) return 0;
-            const PartEstimate e = estimate(full, parts, SIZE_MAX, INFINITY);
-            if (dataflow_lds_bytes(e.rows, e.ints, R, ts) > lds_cap) return INT32_MAX;
-            return std::max(R, dataflow_columns(e.rows, e.ints, e.longest, ts, lds_cap));
+            if (dataflow_lds_bytes(full_est.rows, full_est.ints, R, ts) > lds_cap) return INT32_MAX;
+            return std::max(R, dataflow_columns(full_est.rows, full_est.ints, full_est.longest, ts, lds_cap));
+        };
+        // Calls that the full set takes in one launch may need two on other
+        // parts, whose groups of columns run side by side as far as the compute
+        // units go: with one group to a launch parts that hold one column made
+        // 32^3 ILU(0) with 16 right-hand sides 3.5 times slower than the full
+        // set.  Two launches are the most that never lost to what one part per
+        // compute unit took when this was chosen (700^2, 64 parts: 279 us, five
+        // right-hand sides 623 us in two launches, on 256 parts 317 and 340
+        // us, 420 and 1050 with the kernel of then).
+        auto weighed = [&](const std::vector<int32_t> &po, int32_t count, const PartEstimate &e) {
+            const int64_t most = accepted(po), have = dataflow_columns(e.rows, e.ints, e.longest, ts, lds_cap);
+            return most == INT32_MAX || (most + have - 1) / have <= 2 * std::max(1, parts / count);
         };
         if (queue) {
             part_of = queue_parts(a, t.upper, lv, sys_ptr, tune, dev, t.dt, parts);
@@ -1270,7 +1288,7 @@ void build_exec(TriHost &t, const Csr &a, const Tune &tune, const DeviceShape &d
             auto consider = [&](std::vector<int32_t> &&po, int32_t count) {
                 if (count < 1 || count > parts) return;
                 const PartEstimate e = estimate(po, count, lds_cap, best);
-                if (e.us < best) {
+                if (e.us < best && weighed(po, count, e)) {
                     best = e.us;
                     best_parts = count;
                     part_of.swap(po);
@@ -1310,11 +1328,13 @@ void build_exec(TriHost &t, const Csr &a, const Tune &tune, const DeviceShape &d
                 // blocks fit; taken when they fit the LDS as well
                 std::vector<int32_t> po;
                 const int32_t k = block_parts(n, *sys_ptr, parts, po);
-                if (k <= parts && critical_hops(a, t.upper, po) < critical_hops(a, t.upper, part_of) &&
-                    estimate(po, k, lds_cap, INFINITY).us < INFINITY) {
-                    accept = accepted(po);
-                    part_of.swap(po);
-                    parts = k;
+                if (k <= parts && critical_hops(a, t.upper, po) < critical_hops(a, t.upper, part_of)) {
+                    const PartEstimate e = estimate(po, k, lds_cap, INFINITY);
+                    if (e.us < INFINITY && weighed(po, k, e)) {
+                        accept = accepted(po);
+                        part_of.swap(po);
+                        parts = k;
+                    }
                 }
             }
         } else {

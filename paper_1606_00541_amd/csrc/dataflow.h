@@ -16,6 +16,11 @@
 // Any row waits only on rows of lower levels, and every wave handles its
 // items in level order, so the row of lowest level not yet solved can always
 // proceed: the grid drains as long as all workgroups are co-resident.
+// Right-hand sides beyond what a part's LDS and wavefronts hold are groups of
+// columns, each solved by its own workgroups (grid y) beside the others: they
+// share nothing but the mailbox, where every column has its place.  One launch
+// per group instead: 32^3 ILU(0) with 16 right-hand sides, planned for one,
+// 737 us; one part per compute unit in their place 209 us.
 // The summation order (ELL slots, then the CSR tail, on a right-hand side
 // scaled by the reciprocal diagonal) is the one of k_level, so results are
 // bit-identical to it.
@@ -61,18 +66,18 @@ template <typename T, int W> constexpr int df_sets()
     return sets;
 }
 
-// A workgroup's part of one triangle and its place in LDS: x [win][R], b
+// A workgroup's part of one triangle, its columns (R from k0) and its place in LDS: x [win][R], b
 // [win][R], imports [nimp][R], one zero row (the target of ELL padding), then
 // import slots, export rows (window offsets) and step descriptors (first
 // window row | 16 (number of rows - 1) << 16) with kDataflowPad zeros behind.
 template <typename T> struct DfPart {
-    int g, lo, win, i0, nimp, e0, nex, s0, ns;
+    int g, lo, win, i0, nimp, e0, nex, s0, ns, k0;
     T *xl, *bl, *im;
     int *isl, *erl, *stl;
     unsigned long long *ltr;
 };
 
-template <typename T> __device__ __forceinline__ DfPart<T> df_part(const TriArgs &a, int g, int R, unsigned char *smem)
+template <typename T> __device__ __forceinline__ DfPart<T> df_part(const TriArgs &a, int g, int k0, int R, unsigned char *smem)
 {
     // uniform values as scalars: behind a store the compiler reads them with
     // vector loads, and a buffer load whose offset it cannot prove uniform
@@ -80,6 +85,7 @@ template <typename T> __device__ __forceinline__ DfPart<T> df_part(const TriArgs
     auto uni = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
     DfPart<T> p;
     p.g = uni(g);
+    p.k0 = k0;
     p.lo = uni(a.window[2 * g]);
     p.win = uni(a.window[2 * g + 1]) - p.lo;
     p.i0 = uni(a.imp_ptr[g]);
@@ -130,8 +136,9 @@ __device__ __forceinline__ void df_copy_ints(int *dst, const int32_t *src, int c
 // would offer the next launch the value of the one before.
 template <typename T> __device__ __forceinline__ void df_clear(const TriArgs &a, T *other)
 {
-    const size_t count = (size_t)a.nexp * a.mbox_stride, step = (size_t)gridDim.x * blockDim.x;
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < count; i += step) other[i] = sentinel<T>();
+    const size_t count = (size_t)a.nexp * a.mbox_stride, step = (size_t)gridDim.x * gridDim.y * blockDim.x;
+    const size_t block = (size_t)blockIdx.y * gridDim.x + blockIdx.x;
+    for (size_t i = block * blockDim.x + threadIdx.x; i < count; i += step) other[i] = sentinel<T>();
 }
 
 // Everything but the right-hand side: sentinels, the zero row and index lists.
@@ -167,7 +174,7 @@ __device__ __forceinline__ void df_fill_b(const TriArgs &a, const DfPart<T> &p, 
 #pragma unroll
         for (int u = 0; u < kDfFill; ++u) {
             const int t = min(t0 + u * nt, cnt - 1);
-            bv[u] = bin[(size_t)gi[u] * a.ldr + (a.k0 + (R1 ? 0 : t % R))];
+            bv[u] = bin[(size_t)gi[u] * a.ldr + (p.k0 + (R1 ? 0 : t % R))];
             if (!UNIT) dd[u] = static_cast<const T *>(a.dinv)[p.lo + (R1 ? t : t / R)];
         }
         if (t0 + kDfFill * nt < cnt) index(t0 + kDfFill * nt);
@@ -465,11 +472,11 @@ template <typename T> __device__ __forceinline__ void df_store(const TriArgs &a,
         const int q = t / R, k = t - q * R;
         const int x = p.lo + q;
         const T v = p.xl[t];
-        if (a.write_xw) static_cast<T *>(a.xw)[(size_t)x * a.ldr + a.k0 + k] = v;
+        if (a.write_xw) static_cast<T *>(a.xw)[(size_t)x * a.ldr + p.k0 + k] = v;
         if (a.xout) {
             const int d = a.scatter[x];  // negative: the row is not written (RAS overlap rows)
             if (d >= 0) {
-                const size_t dst = (size_t)d * a.ldr + a.k0 + k;
+                const size_t dst = (size_t)d * a.ldr + p.k0 + k;
                 if (a.out_f64) static_cast<double *>(a.xout)[dst] = static_cast<double>(v);
                 else static_cast<float *>(a.xout)[dst] = static_cast<float>(v);
             }
@@ -491,7 +498,7 @@ __device__ __forceinline__ void df_report(const TriArgs &a, DfCtl *ctl)
 __device__ __forceinline__ void df_leave(const TriArgs &a, unsigned epoch)
 {
     const unsigned done = __hip_atomic_fetch_add(&a.epoch[1], 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
-    if (done == gridDim.x - 1) {
+    if (done == gridDim.x * gridDim.y - 1) {
         __hip_atomic_store(&a.epoch[2], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __hip_atomic_store(&a.epoch[1], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __hip_atomic_store(&a.epoch[0], epoch + 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
@@ -504,7 +511,7 @@ __global__ void __launch_bounds__(512) k_dataflow(TriArgs a)
     extern __shared__ __align__(16) unsigned char smem[];
     DfCtl *ctl = reinterpret_cast<DfCtl *>(smem + a.lds_ctl);
     const int tid = threadIdx.x;
-    const int R = R1 ? 1 : a.R;
+    const int k0 = a.k0 + (int)blockIdx.y * a.R, R = R1 ? 1 : min(a.R, a.ldr - k0);
     if (tid == 0) {
         ctl->epoch = __hip_atomic_load(a.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         ctl->abort = 0;
@@ -513,7 +520,7 @@ __global__ void __launch_bounds__(512) k_dataflow(TriArgs a)
     const unsigned par = ctl->epoch & 1u;
     T *mbox = static_cast<T *>(a.mbox);
     const size_t half = (size_t)a.nexp * a.mbox_stride;
-    T *mrd = mbox + (par ? half : 0), *other = mbox + (par ? 0 : half);
+    T *mrd = mbox + (par ? half : 0) + k0, *other = mbox + (par ? 0 : half);
     for (int round = 0;; ++round) {
         if (a.queue) {
             if (tid == 0) ctl->part = (int)__hip_atomic_fetch_add(&a.epoch[2], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -526,7 +533,7 @@ __global__ void __launch_bounds__(512) k_dataflow(TriArgs a)
             if (round == 0) df_clear(a, other);
             break;
         }
-        const DfPart<T> pt = df_part<T>(a, g, R, smem);
+        const DfPart<T> pt = df_part<T>(a, g, k0, R, smem);
         unsigned long long t_fill = 0;
         df_sweep<T, W, TAIL, R1, TRACE>(a, pt, R, mrd, &ctl->abort, t_fill, [&]() {
             if (a.in_f64) df_fill_b<T, UNIT, R1>(a, pt, R, static_cast<const double *>(a.bin));
@@ -536,7 +543,7 @@ __global__ void __launch_bounds__(512) k_dataflow(TriArgs a)
         });
         const unsigned long long t_done = TRACE ? __builtin_amdgcn_s_memrealtime() : 0ull;
         df_report(a, ctl);
-        if (TRACE) {
+        if (TRACE && blockIdx.y == 0) {
             const int ntr = min(pt.ns, a.trace_stride - 1);
             for (int t = tid; t < 2 * ntr; t += blockDim.x) a.trace[2 * (size_t)g * a.trace_stride + t] = pt.ltr[t];
             if (tid == 0) {
@@ -587,7 +594,7 @@ __global__ void __launch_bounds__(512) k_dataflow_lu(TriArgs l, TriArgs u)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     DfCtl *ctl = reinterpret_cast<DfCtl *>(smem + l.lds_ctl);
-    const int R = R1 ? 1 : l.R, g = blockIdx.x;
+    const int k0 = l.k0 + (int)blockIdx.y * l.R, R = R1 ? 1 : min(l.R, l.ldr - k0), g = blockIdx.x;
     if (threadIdx.x == 0) {
         ctl->epoch = __hip_atomic_load(l.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         ctl->epoch2 = __hip_atomic_load(u.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -598,8 +605,8 @@ __global__ void __launch_bounds__(512) k_dataflow_lu(TriArgs l, TriArgs u)
     auto half = [&](const TriArgs &a, unsigned par) {
         return static_cast<T *>(a.mbox) + (par & 1u ? (size_t)a.nexp * a.mbox_stride : 0);
     };
-    const DfPart<T> pl = df_part<T>(l, g, R, smem);
-    df_sweep<T, W, false, R1, false>(l, pl, R, half(l, ctl->epoch), &ctl->abort, t_fill, [&]() {
+    const DfPart<T> pl = df_part<T>(l, g, k0, R, smem);
+    df_sweep<T, W, false, R1, false>(l, pl, R, half(l, ctl->epoch) + k0, &ctl->abort, t_fill, [&]() {
         if (l.in_f64) df_fill_b<T, true, R1>(l, pl, R, static_cast<const double *>(l.bin));
         else df_fill_b<T, true, R1>(l, pl, R, static_cast<const float *>(l.bin));
         df_fill_lists(l, pl, R);
@@ -607,8 +614,8 @@ __global__ void __launch_bounds__(512) k_dataflow_lu(TriArgs l, TriArgs u)
         df_clear(u, half(u, ctl->epoch2 + 1u));
     });
     if (!ctl->abort) {
-        const DfPart<T> pu = df_part<T>(u, g, R, smem);
-        df_sweep<T, W, false, R1, false>(u, pu, R, half(u, ctl->epoch2), &ctl->abort, t_fill, [&]() {
+        const DfPart<T> pu = df_part<T>(u, g, k0, R, smem);
+        df_sweep<T, W, false, R1, false>(u, pu, R, half(u, ctl->epoch2) + k0, &ctl->abort, t_fill, [&]() {
             df_fill_y<T, R1>(u, pu, R, pl.lo);
             __syncthreads();
             df_fill_lists(u, pu, R);

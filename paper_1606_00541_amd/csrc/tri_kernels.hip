@@ -1031,6 +1031,23 @@ int32_t dataflow_columns(const DevTri &d)
     return hec::dataflow_columns(d.df_rows, d.df_ints, d.df_step_rows, d.dt == HEC_F64 ? 8 : 4, (size_t)device_max_lds());
 }
 
+// A call's R right-hand sides as even groups of at most `most` columns, and the
+// groups of one launch: no more than have a compute unit for each workgroup.
+struct DataflowSplit {
+    int32_t columns, groups;
+    static int32_t even(int32_t R, int32_t most)
+    {
+        const int32_t all = (R + most - 1) / most;
+        return (R + all - 1) / all;
+    }
+    DataflowSplit(int32_t R, int32_t most, int32_t parts, int32_t cap) : columns(even(R, most))
+    {
+        groups = std::max(1, std::min((R + columns - 1) / columns, std::min(cap, device_cus()) / std::max(1, parts)));
+    }
+    // groups of the launch that starts at column k0
+    int32_t at(int32_t k0, int32_t R) const { return std::min(groups, (R - k0 + columns - 1) / columns); }
+};
+
 // Two import wavefronts, but one beside wide rows (see df_import) or where
 // the workgroup has no room for another.
 int32_t dataflow_import_waves(const DevTri &d)
@@ -1040,7 +1057,17 @@ int32_t dataflow_import_waves(const DevTri &d)
 
 template <typename T> void launch_dataflow(DevTri &d, TriArgs a, hipStream_t st)
 {
-    // the plan's columns name group-local imports: only this kernel reads them
+    // the plan's columns name group-local imports: only this kernel reads them.
+    // One launch, or (a plan whose parts hold fewer right-hand sides than one
+    // part per compute unit would) groups of columns
+    a.ldr = a.R;
+    const int32_t all = a.R, most = dataflow_columns(d);
+    if (all > most && all > d.df_accept) {
+        if ((int64_t)d.df_step_rows * all > 64)
+            fail(HEC_ERR_INVALID_ARG, "dataflow plan: nrhs exceeds the plan's max_nrhs (steps are sized for it)");
+        fail(HEC_ERR_CAPACITY, "dataflow kernel: LDS need exceeds the device limit at this nrhs");
+    }
+    a.R = DataflowSplit::even(all, most);
     const bool one = a.R == 1, f64 = sizeof(T) == 8;
     OwnerKernel k = nullptr;
     if (a.trace)
@@ -1069,8 +1096,11 @@ template <typename T> void launch_dataflow(DevTri &d, TriArgs a, hipStream_t st)
     } else if (cap < d.groups) {
         fail(HEC_ERR_CAPACITY, "dataflow grid exceeds the co-resident capacity");
     }
-    hipLaunchKernelGGL(k, dim3(grid), dim3(block), lds, st, a);
-    hip_check(hipGetLastError(), "k_dataflow launch");
+    const DataflowSplit split(all, most, d.groups, cap);
+    for (a.k0 = 0; a.k0 < all; a.k0 += split.groups * split.columns) {
+        hipLaunchKernelGGL(k, dim3(grid, split.at(a.k0, all)), dim3(block), lds, st, a);
+        hip_check(hipGetLastError(), "k_dataflow launch");
+    }
 }
 
 template <typename T, typename TIn, typename TOut>
@@ -1140,20 +1170,7 @@ void launch_typed(DevTri &d, TriArgs a, hipStream_t st)
         return;
     }
     if (d.dataflow) {
-        // the plan's columns name group-local imports: only this kernel reads them
-        // one launch, or (a plan whose automatic parts hold fewer right-hand
-        // sides than one part per compute unit would) one per group of columns
-        a.ldr = a.R;
-        const int32_t all = a.R, most = dataflow_columns(d);
-        if (all > most && all > d.df_accept) {
-            if ((int64_t)d.df_step_rows * all > 64)
-                fail(HEC_ERR_INVALID_ARG, "dataflow plan: nrhs exceeds the plan's max_nrhs (steps are sized for it)");
-            fail(HEC_ERR_CAPACITY, "dataflow kernel: LDS need exceeds the device limit at this nrhs");
-        }
-        for (a.k0 = 0; a.k0 < all; a.k0 += a.R) {
-            a.R = std::min(most, all - a.k0);
-            launch_dataflow<T>(d, a, st);
-        }
+        launch_dataflow<T>(d, a, st);
         return;
     }
     if (d.kind == HEC_SCHED_OWNER_PERSISTENT && d.variant == 3 && a.R == 1 && !d.has_tail && d.max_lanes_one &&
@@ -1393,19 +1410,20 @@ void launch_lu(DevTri &L, DevTri &U, bool lu_shared, const void *r, hec_dtype_t 
         TriArgs a = tri_args(L, r, in_dt, gather_l, nullptr, nullptr, in_dt, nullptr, R);
         TriArgs b = tri_args(U, nullptr, L.dt, qmap, nullptr, z, out_dt, scatter_u, R);
         a.ldr = b.ldr = R;
-        for (int32_t k0 = 0; k0 < R; k0 += most) {
+        a.R = b.R = DataflowSplit::even(R, most);
+        LuKernel k = a.R == 1 ? (f64 ? lu_f64_one : lu_f32_one)(L.w) : (f64 ? lu_f64_many : lu_f32_many)(L.w);
+        const size_t ts = f64 ? 8 : 4;
+        const size_t lds = std::max(dataflow_lds_bytes(L.df_rows, L.df_ints, a.R, ts),
+                                    dataflow_lds_bytes(U.df_rows, U.df_ints, a.R, ts));
+        a.lds_ctl = b.lds_ctl = (int32_t)lds - kDataflowCtlBytes;
+        a.imp_waves = b.imp_waves = dataflow_import_waves(L);
+        const int block = 64 * (L.df_waves + 1 + a.imp_waves);
+        const int32_t cap = capacity_of((const void *)k, block, lds, true);
+        if (cap < L.groups) fail(HEC_ERR_CAPACITY, "dataflow grid exceeds the co-resident capacity");
+        const DataflowSplit split(R, most, L.groups, cap);
+        for (int32_t k0 = 0; k0 < R; k0 += split.groups * split.columns) {
             a.k0 = b.k0 = k0;
-            a.R = b.R = std::min(most, R - k0);
-            LuKernel k = a.R == 1 ? (f64 ? lu_f64_one : lu_f32_one)(L.w) : (f64 ? lu_f64_many : lu_f32_many)(L.w);
-            const size_t ts = f64 ? 8 : 4;
-            const size_t lds = std::max(dataflow_lds_bytes(L.df_rows, L.df_ints, a.R, ts),
-                                        dataflow_lds_bytes(U.df_rows, U.df_ints, a.R, ts));
-            a.lds_ctl = b.lds_ctl = (int32_t)lds - kDataflowCtlBytes;
-            a.imp_waves = b.imp_waves = dataflow_import_waves(L);
-            const int block = 64 * (L.df_waves + 1 + a.imp_waves);
-            if (capacity_of((const void *)k, block, lds, true) < L.groups)
-                fail(HEC_ERR_CAPACITY, "dataflow grid exceeds the co-resident capacity");
-            hipLaunchKernelGGL(k, dim3(L.groups), dim3(block), lds, st, a, b);
+            hipLaunchKernelGGL(k, dim3(L.groups, split.at(k0, R)), dim3(block), lds, st, a, b);
             hip_check(hipGetLastError(), "k_dataflow_lu launch");
         }
         return;

@@ -37,3 +37,56 @@ def test_parts_that_end_with_the_systems_take_what_even_parts_take():
         out.append(z)
     assert H.tri_plan_stats(H.ilu_plans(f)[0])["dataflow"] == 1
     assert torch.equal(out[0], out[1])
+
+
+@pytest.mark.parametrize("dt", ["f64", "f32"])
+@pytest.mark.parametrize("shape,counts", [((32, 32, 32), (2, 3, 5, 16)), ((64, 64, 1), (4, 5, 7, 31)), ((200, 200, 1), (3, 6)),
+                                          ((64, 64, 64), (2, 4)), ((700, 700, 1), (2, 5))])
+def test_groups_side_by_side(shape, counts, dt):
+    # default plans (made for one right-hand side) of several parts, in place
+    # as well: one group, uneven groups, more groups than one launch runs
+    A = synth.poisson3d(*shape)
+    ref = H.ilu_setup(A, "ilu0", factor_dtype=dt, tune=H.tune_default(schedule="level_launch"))
+    f = H.ilu_setup(A, "ilu0", factor_dtype=dt)
+    pl, pu = H.ilu_plans(f)
+    st = H.tri_plan_stats(pl)
+    assert st["dataflow"] and st["num_groups"] > 1 and st["nexport"] > 0
+    for nrhs in counts + (1,):
+        r = torch.from_numpy(np.random.default_rng(nrhs).standard_normal((A.n, nrhs))).cuda()
+        want = torch.empty_like(r)
+        H.ilu_apply(ref, r, want)
+        for _ in range(3):  # both mailbox halves
+            z = torch.empty_like(r)
+            H.ilu_apply(f, r, z)
+            assert torch.equal(z, want), nrhs
+        z = r.clone()
+        H.ilu_apply(f, z, z)
+        assert torch.equal(z, want), nrhs
+        H.tri_solve_lower(pl, r, z)
+        H.tri_solve_upper(pu, z, z)
+        assert torch.equal(z, want), nrhs
+        for p in (pl, pu):
+            H.tri_plan_check(p)
+
+
+@pytest.mark.parametrize("shape,nrhs", [((32, 32, 32), 16), ((64, 64, 1), 16), ((300, 300, 1), 8)])
+def test_more_columns_than_planned_cost_less_than_a_solve_each(shape, nrhs):
+    # a quarter of it is the line: side by side they take little more than one
+    A = synth.poisson3d(*shape)
+    f = H.ilu_setup(A, "ilu0")
+    times = []
+    for k in (1, nrhs):
+        r = torch.zeros(A.n, k, dtype=torch.float64, device="cuda")
+        z = torch.empty_like(r)
+        H.ilu_apply(f, r, z)
+        laps = []
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(20):
+                H.ilu_apply(f, r, z)
+            b.record()
+            b.synchronize()
+            laps.append(a.elapsed_time(b))
+        times.append(min(laps))
+    assert times[1] < times[0] * nrhs / 4, times
