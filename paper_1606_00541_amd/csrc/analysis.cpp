@@ -463,19 +463,12 @@ bool detect_grid(const Csr &a, int32_t &nx, int32_t &ny, int32_t &nz)
     if (n < 64) return false;
     std::vector<std::pair<int64_t, int32_t>> cnt;  // offset -> count (sparse)
     {
-        std::vector<int32_t> offs;
-        offs.reserve(a.nnz());
+        std::vector<int32_t> hist(n, 0);
         for (int32_t i = 0; i < n; ++i)
-            for (int32_t p = a.rp[i]; p < a.rp[i + 1]; ++p)
-                if (a.ci[p] != i) offs.push_back(std::abs(a.ci[p] - i));
-        if (offs.empty()) return false;
-        std::sort(offs.begin(), offs.end());
-        for (size_t k = 0; k < offs.size();) {
-            size_t e = k;
-            while (e < offs.size() && offs[e] == offs[k]) ++e;
-            cnt.push_back({offs[k], (int32_t)(e - k)});
-            k = e;
-        }
+            for (int32_t p = a.rp[i]; p < a.rp[i + 1]; ++p) hist[std::abs(a.ci[p] - i)] += 1;
+        for (int32_t o = 1; o < n; ++o)
+            if (hist[o] > 0) cnt.push_back({o, hist[o]});
+        if (cnt.empty()) return false;
     }
     auto freq = [&](int64_t o) {
         for (auto &c : cnt)
@@ -540,12 +533,14 @@ std::vector<int32_t> grid_parts(int32_t n, int32_t nx, int32_t ny, int32_t nz, i
         return part;
     }
     const int32_t px = best[0], py = best[1], pz = best[2];
-    for (int32_t i = 0; i < n; ++i) {
-        const int32_t x = i % nx, y = (i / nx) % ny, z = i / (nx * ny);
-        const int32_t bx = (int32_t)((int64_t)x * px / nx), by = (int32_t)((int64_t)y * py / ny),
-                      bz = (int32_t)((int64_t)z * pz / nz);
-        part[i] = bx + px * (by + py * bz);
-    }
+    std::vector<int32_t> bx(nx);
+    for (int32_t x = 0; x < nx; ++x) bx[x] = (int32_t)((int64_t)x * px / nx);
+    int32_t i = 0;
+    for (int32_t z = 0; i < n; ++z)
+        for (int32_t y = 0; y < ny && i < n; ++y) {
+            const int32_t by = (int32_t)((int64_t)y * py / ny), bz = (int32_t)((int64_t)z * pz / nz);
+            for (int32_t x = 0; x < nx && i < n; ++x) part[i++] = bx[x] + px * (by + py * bz);
+        }
     return part;
 }
 
@@ -804,104 +799,166 @@ struct PartModel {
     static constexpr double wave = 0.05, hop = 1.2, kvalue = 0.8;
 };
 
-// LDS bytes the dataflow kernel needs for these parts (as make_dataflow and
-// dataflow_lds_bytes count them), and the estimated time of the solve, given
-// up (infinite) once it exceeds `limit`.
-struct PartEstimate {
-    int32_t rows = 0, ints = 0;   // as Schedule::df_rows, df_ints
-    int32_t longest = 0;          // rows of the longest step
-    double us = 0.0;              // infinite when over the limit or the LDS
-};
+// A cut of the rows into parts: what it needs of the LDS (as make_dataflow and
+// dataflow_lds_bytes count it) and the estimated time of the solve.  Each
+// question costs a pass over the rows or the matrix, so a cut that cannot win
+// is dropped as early as it shows: by its rows and levels alone, within the
+// walk over the levels, by its imports.
+class PartCut {
+public:
+    int32_t rows = 0, ints = 0;  // as Schedule::df_rows, df_ints (lists)
+    int32_t longest = 0;         // rows of the longest step (steps, time)
 
-PartEstimate estimate_parts(const Csr &a, bool upper, const Levels &lv, const std::vector<int32_t> &part, int32_t P,
-                            int32_t waves, int32_t w, int32_t R, size_t ts, size_t cap, double limit)
-{
-    const int32_t n = a.n;
-    PartEstimate out;
-    // rows of each part in problem order, and the wavefront piece of each row
-    std::vector<int32_t> size((size_t)P + 1, 0), piece(n);
-    for (int32_t i = 0; i < n; ++i) size[part[i] + 1] += 1;
-    std::vector<int32_t> start(size);
-    for (int32_t g = 0; g < P; ++g) start[g + 1] += start[g];
-    std::vector<int32_t> rows(n), cur(start.begin(), start.end() - 1);
-    for (int32_t q = 0; q < n; ++q) {
-        const int32_t i = upper ? n - 1 - q : q;
-        rows[cur[part[i]]++] = i;
+    PartCut(const Csr &a_, bool upper_, const Levels &lv_, int32_t waves_, int32_t w, int32_t R)
+        : a(a_), lv(lv_), upper(upper_), waves(waves_), per(std::max(1, 64 / R)), step_us(PartModel::step(w)),
+          value_us(1e-3 * PartModel::kvalue * R), at(a_.n)
+    {
     }
-    int64_t widest = 0;
-    for (int32_t g = 0; g < P; ++g) {
-        const int64_t m = start[g + 1] - start[g];
-        widest = std::max(widest, m);
-        for (int32_t w2 = 0; w2 < waves; ++w2)
-            for (int64_t u = m * w2 / waves; u < m * (w2 + 1) / waves; ++u) piece[rows[start[g] + u]] = g * waves + w2;
+
+    void set(const std::vector<int32_t> &part_, int32_t P)
+    {
+        part = part_.data();
+        size.assign(P, 0);
+        for (int32_t i = 0; i < a.n; ++i) size[part[i]] += 1;
+        widest = *std::max_element(size.begin(), size.end());
+        longest = 0;
+        nsteps.assign(P, 0);
     }
-    // imports and exports
-    std::vector<int32_t> stamp(n, -1);
-    std::vector<int32_t> exported((size_t)P, 0);
-    std::vector<char> is_exp(n, 0);
-    std::vector<int32_t> imports((size_t)P, 0);
-    for (int32_t g = 0; g < P; ++g)
-        for (int32_t k = start[g]; k < start[g + 1]; ++k)
-            for (int32_t p = a.rp[rows[k]]; p < a.rp[rows[k] + 1]; ++p) {
-                const int32_t j = a.ci[p];
-                if (part[j] == g || stamp[j] == g) continue;
-                stamp[j] = g;
-                imports[g] += 1;
-                if (!is_exp[j]) {
-                    is_exp[j] = 1;
-                    exported[part[j]] += 1;
-                }
-            }
-    // steps and finish times, level by level
-    const int32_t per = std::max(1, 64 / R);
-    const double ts_us = PartModel::step(w), fixed = 1e-3 * PartModel::kvalue * (double)widest * R;
-    std::vector<double> clock((size_t)P * waves, 0.0), ready((size_t)P * waves, 0.0), finish;
-    std::vector<int32_t> count((size_t)P * waves, 0), open((size_t)P * waves, -1), nsteps((size_t)P, 0), step(n), touched;
-    finish.reserve((size_t)n / 16 + 64);
-    for (int32_t l = 0; l < lv.nlev; ++l) {
-        touched.clear();
+    int32_t largest() const { return widest; }
+    // no estimate is below it
+    double least() const { return lv.nlev * step_us + value_us * widest; }
+
+    // Steps of every part: the rows of a wavefront's piece in level order.
+    void steps()
+    {
+        pieces();
+        for (int32_t l = 0; l < lv.nlev; ++l) {
+            for (int32_t r = lv.levelptr[l]; r < lv.levelptr[l + 1]; ++r) step(at[lv.perm[r]]);
+            for (int32_t c : touched) count[c] = 0;
+            touched.clear();
+        }
+    }
+
+    // The same with the estimated time of the solve, infinite once it reaches `limit`.
+    double time(double limit)
+    {
+        pieces();
+        clock.assign(count.size(), 0.0);
+        ready.assign(count.size(), 0.0);
+        open.assign(count.size(), -1);
+        finish.clear();
+        const double fixed = value_us * widest;
+        double us = 0.0;
         auto close = [&](int32_t c) {
-            clock[c] = std::max(clock[c], ready[c]) + ts_us;
+            clock[c] = std::max(clock[c], ready[c]) + step_us;
             finish[open[c]] = clock[c];
         };
-        for (int32_t r = lv.levelptr[l]; r < lv.levelptr[l + 1]; ++r) {
-            const int32_t i = lv.perm[r], c = piece[i];
-            if (count[c] == 0) touched.push_back(c);
-            if (count[c] % per == 0) {
-                if (count[c] > 0) close(c);
-                open[c] = (int32_t)finish.size();
-                finish.push_back(0.0);
-                nsteps[part[i]] += 1;
-                ready[c] = 0.0;
+        for (int32_t l = 0; l < lv.nlev; ++l) {
+            for (int32_t r = lv.levelptr[l]; r < lv.levelptr[l + 1]; ++r) {
+                const int32_t i = lv.perm[r];
+                At &x = at[i];
+                const int32_t c = x.piece;
+                const bool more = count[c] > 0;
+                if (step(x)) {
+                    if (more) close(c);
+                    open[c] = (int32_t)finish.size();
+                    finish.push_back(0.0);
+                    ready[c] = 0.0;
+                }
+                x.step = open[c];
+                for (int32_t p = a.rp[i]; p < a.rp[i + 1]; ++p) {
+                    const int32_t j = a.ci[p];
+                    if (j == i) continue;
+                    const At y = at[j];
+                    ready[c] = std::max(ready[c], finish[y.step] + (y.piece == c        ? 0.0
+                                                                    : y.part == x.part ? PartModel::wave
+                                                                                       : PartModel::hop));
+                }
             }
-            count[c] += 1;
-            out.longest = std::max(out.longest, std::min(count[c], per));
-            step[i] = open[c];
-            for (int32_t p = a.rp[i]; p < a.rp[i + 1]; ++p) {
-                const int32_t j = a.ci[p];
-                if (j == i) continue;
-                const double t = finish[step[j]] + (piece[j] == c ? 0.0 : part[j] == part[i] ? PartModel::wave : PartModel::hop);
-                ready[c] = std::max(ready[c], t);
+            for (int32_t c : touched) {
+                close(c);
+                count[c] = 0;
+                us = std::max(us, clock[c]);
             }
+            touched.clear();
+            if (us + fixed >= limit) return INFINITY;
         }
-        for (int32_t c : touched) {
-            close(c);
-            count[c] = 0;
-            out.us = std::max(out.us, clock[c]);
-        }
-        if (out.us + fixed > limit) {
-            out.us = INFINITY;
-            return out;
+        return us + fixed;
+    }
+
+    // Imports and exports, and with them (after steps or time) the lists.
+    void lists()
+    {
+        const int32_t P = (int32_t)size.size();
+        std::vector<int32_t> start((size_t)P + 1, 0), imports(P, 0), exported(P, 0), row(a.n), stamp(a.n, -1);
+        for (int32_t g = 0; g < P; ++g) start[g + 1] = start[g] + size[g];
+        std::vector<int32_t> cur(start.begin(), start.end() - 1);
+        for (int32_t i = 0; i < a.n; ++i) row[cur[part[i]]++] = i;
+        for (int32_t g = 0; g < P; ++g)
+            for (int32_t k = start[g]; k < start[g + 1]; ++k)
+                for (int32_t p = a.rp[row[k]]; p < a.rp[row[k] + 1]; ++p) {
+                    const int32_t j = a.ci[p];
+                    if (part[j] == g || stamp[j] == g) continue;
+                    imports[g] += 1;
+                    if (stamp[j] < 0) exported[part[j]] += 1;
+                    stamp[j] = g;
+                }
+        rows = ints = 0;
+        for (int32_t g = 0; g < P; ++g) {
+            rows = std::max(rows, 2 * size[g] + imports[g] + 1);
+            ints = std::max(ints, imports[g] + exported[g] + nsteps[g] + kDataflowPad);
         }
     }
-    out.us += fixed;
-    for (int32_t g = 0; g < P; ++g) {
-        out.rows = std::max(out.rows, 2 * (start[g + 1] - start[g]) + imports[g] + 1);
-        out.ints = std::max(out.ints, imports[g] + exported[g] + nsteps[g] + kDataflowPad);
+
+private:
+    struct At {
+        int32_t step;
+        uint16_t piece, part;
+    };
+    void pieces()
+    {
+        struct Piece {
+            int32_t next, bound, w;  // rank of the next row, first rank of the next piece, this piece
+        };
+        const int32_t P = (int32_t)size.size();
+        std::vector<Piece> cur(P);
+        auto bound = [&](int32_t g, int32_t w) { return (int32_t)((int64_t)size[g] * w / waves); };
+        for (int32_t g = 0; g < P; ++g) cur[g] = {0, bound(g, 1), 0};
+        for (int32_t q = 0; q < a.n; ++q) {
+            const int32_t i = upper ? a.n - 1 - q : q, g = part[i];
+            Piece &c = cur[g];
+            while (c.next >= c.bound) c.bound = bound(g, ++c.w + 1);
+            c.next += 1;
+            at[i].piece = (uint16_t)(g * waves + c.w);
+            at[i].part = (uint16_t)g;
+        }
+        count.assign((size_t)P * waves, 0);
+        touched.clear();
+        longest = 0;
+        nsteps.assign(P, 0);
     }
-    if (dataflow_lds_bytes(out.rows, out.ints, R, ts) > cap) out.us = INFINITY;
-    return out;
-}
+    // the next row of a level: true if it opens a step
+    bool step(const At &x)
+    {
+        int32_t &k = count[x.piece];
+        if (k == 0) touched.push_back(x.piece);
+        const bool first = k % per == 0;
+        if (first) nsteps[x.part] += 1;
+        k += 1;
+        longest = std::max(longest, std::min(k, per));
+        return first;
+    }
+    const Csr &a;
+    const Levels &lv;
+    const bool upper;
+    const int32_t waves, per;  // per: rows of a step
+    const double step_us, value_us;
+    int32_t widest = 0;  // rows of the largest part
+    const int32_t *part = nullptr;
+    std::vector<int32_t> size, nsteps, count, open, touched;
+    std::vector<At> at;
+    std::vector<double> clock, ready, finish;
+};
 
 // The automatic schedule chooses the parts, unless the caller asks for their
 // number or shape: then every triangle is cut as asked, also U of an ILU.
@@ -1218,7 +1275,7 @@ void build_exec(TriHost &t, const Csr &a, const Tune &tune, const DeviceShape &d
         int32_t gx = 0, gy = 0, gz = 0;
         const bool choose = want_df && !queue && parts_open(tune);
         const bool shared = choose && tune.share_part;
-        bool grid = !queue && !shared && (tune.partition == 0 || tune.partition == 3) && detect_grid(a, gx, gy, gz);
+        const bool grid = !queue && !shared && (tune.partition == 0 || tune.partition == 3) && detect_grid(a, gx, gy, gz);
         auto contiguous = [&](int32_t count) {
             std::vector<int32_t> po(n);
             for (int32_t g = 0; g < count; ++g) {
@@ -1242,25 +1299,24 @@ void build_exec(TriHost &t, const Csr &a, const Tune &tune, const DeviceShape &d
         const size_t ts = t.dt == HEC_F64 ? 8 : 4;
         const size_t lds_cap = dev.lds > 0 ? (size_t)dev.lds : 163840;
         const bool blocks = sys_ptr && sys_ptr->size() > 2;
-        auto estimate = [&](const std::vector<int32_t> &po, int32_t count, size_t lds, double limit) {
-            return estimate_parts(a, t.upper, lv, po, count, df_waves, w0, R, ts, lds, limit);
-        };
-        // The full set of parts, with what it would take in one launch.  Plans
-        // on other parts take as many right-hand sides in groups of columns,
-        // and any number where the full set does not fit and a kernel without
-        // a limit would run (0: no more than the parts themselves hold).
+        auto fits = [&](const PartCut &c) { return dataflow_lds_bytes(c.rows, c.ints, R, ts) <= lds_cap; };
+        auto columns = [&](const PartCut &c) { return dataflow_columns(c.rows, c.ints, c.longest, ts, lds_cap); };
+        // The full set of parts, and the right-hand sides it takes in one
+        // launch: plans on other parts take as many in groups of columns, and
+        // any number where the full set does not fit and a kernel without a
+        // limit would run (0: no more than the parts themselves hold).
         std::vector<int32_t> full;
-        PartEstimate full_est;
-        auto full_needed = [&]() {
-            if (!full.empty() || n == 0) return;
-            full = full_set();
-            full_est = estimate(full, parts, SIZE_MAX, INFINITY);
-        };
+        int32_t full_accept = -1;
         auto accepted = [&](const std::vector<int32_t> &po) {
-            full_needed();
-            if (po == full) return 0;
-            if (dataflow_lds_bytes(full_est.rows, full_est.ints, R, ts) > lds_cap) return INT32_MAX;
-            return std::max(R, dataflow_columns(full_est.rows, full_est.ints, full_est.longest, ts, lds_cap));
+            if (full_accept < 0) {
+                full = full_set();
+                PartCut c(a, t.upper, lv, df_waves, w0, R);
+                c.set(full, parts);
+                c.steps();
+                c.lists();
+                full_accept = fits(c) ? std::max(R, columns(c)) : INT32_MAX;
+            }
+            return po == full ? 0 : full_accept;
         };
         // Calls that the full set takes in one launch may need two on other
         // parts, whose groups of columns run side by side as far as the compute
@@ -1270,29 +1326,45 @@ void build_exec(TriHost &t, const Csr &a, const Tune &tune, const DeviceShape &d
         // compute unit took when this was chosen (700^2, 64 parts: 279 us, five
         // right-hand sides 623 us in two launches, on 256 parts 317 and 340
         // us, 420 and 1050 with the kernel of then).
-        auto weighed = [&](const std::vector<int32_t> &po, int32_t count, const PartEstimate &e) {
-            const int64_t most = accepted(po), have = dataflow_columns(e.rows, e.ints, e.longest, ts, lds_cap);
+        auto weighed = [&](const std::vector<int32_t> &po, int32_t count, const PartCut &c) {
+            const int64_t most = accepted(po), have = columns(c);
             return most == INT32_MAX || (most + have - 1) / have <= 2 * std::max(1, parts / count);
         };
         if (queue) {
             part_of = queue_parts(a, t.upper, lv, sys_ptr, tune, dev, t.dt, parts);
         } else if (shared) {
-            // no less than L takes, and no less than a plan of its own would
             part_of = *tune.share_part;
-            grid = detect_grid(a, gx, gy, gz);
-            accept = std::max(tune.share_accept, accepted(part_of));
             parts = tune.share_parts;
+            accept = tune.share_accept;  // what L takes
         } else if (choose && n > 0 && n <= kEstimateRows) {
             double best = INFINITY;
             int32_t best_parts = 0;
-            auto consider = [&](std::vector<int32_t> &&po, int32_t count) {
+            PartCut cut(a, t.upper, lv, df_waves, w0, R);
+            // twice the parts make more handoffs and smaller parts: a shape
+            // that loses twice in a row is not cut further
+            enum { kBlocks, kGrid, kContiguous };
+            int32_t left[3] = {2, 2, 2};
+            bool doubled = false;
+            auto consider = [&](int shape, std::vector<int32_t> &&po, int32_t count) {
                 if (count < 1 || count > parts) return;
-                const PartEstimate e = estimate(po, count, lds_cap, best);
-                if (e.us < best && weighed(po, count, e)) {
-                    best = e.us;
-                    best_parts = count;
-                    part_of.swap(po);
+                if (doubled) left[shape] -= 1;
+                cut.set(po, count);
+                if (cut.least() >= best) return;
+                // parts that fill most of the LDS: their imports come first
+                const bool tight = 2 * (size_t)cut.largest() * R * ts > lds_cap - lds_cap / 8;
+                if (tight) cut.lists();
+                if (tight && !fits(cut)) {
+                    if (doubled) left[shape] += 1;  // says nothing about its time
+                    return;
                 }
+                const double us = cut.time(best);
+                if (us == INFINITY) return;
+                cut.lists();
+                left[shape] = 2;
+                if (!fits(cut) || !weighed(po, count, cut)) return;
+                best = us;
+                best_parts = count;
+                part_of.swap(po);
             };
             const int64_t least = std::max<int64_t>(1, (int64_t)((2 * (size_t)n * R * ts + lds_cap - 1) / lds_cap));
             std::vector<int32_t> counts;
@@ -1304,12 +1376,13 @@ void build_exec(TriHost &t, const Csr &a, const Tune &tune, const DeviceShape &d
             if (8 * p2 >= parts) counts.push_back(parts);
             std::vector<int32_t> po;
             for (int32_t c : counts) {
-                if (blocks) {
+                doubled = c >= p2;
+                if (blocks && left[kBlocks] > 0) {
                     const int32_t k = block_parts(n, *sys_ptr, c, po);
-                    consider(std::move(po), k);
+                    consider(kBlocks, std::move(po), k);
                 }
-                if (grid) consider(grid_parts(n, gx, gy, gz, c), c);
-                consider(contiguous(c), c);
+                if (grid && left[kGrid] > 0) consider(kGrid, grid_parts(n, gx, gy, gz, c), c);
+                if (left[kContiguous] > 0) consider(kContiguous, contiguous(c), c);
             }
             if (best_parts == 0) {
                 // imports can outweigh the rows (16 entries a row anywhere
@@ -1329,8 +1402,11 @@ void build_exec(TriHost &t, const Csr &a, const Tune &tune, const DeviceShape &d
                 std::vector<int32_t> po;
                 const int32_t k = block_parts(n, *sys_ptr, parts, po);
                 if (k <= parts && critical_hops(a, t.upper, po) < critical_hops(a, t.upper, part_of)) {
-                    const PartEstimate e = estimate(po, k, lds_cap, INFINITY);
-                    if (e.us < INFINITY && weighed(po, k, e)) {
+                    PartCut cut(a, t.upper, lv, df_waves, w0, R);
+                    cut.set(po, k);
+                    cut.steps();
+                    cut.lists();
+                    if (fits(cut) && weighed(po, k, cut)) {
                         accept = accepted(po);
                         part_of.swap(po);
                         parts = k;

@@ -1,5 +1,7 @@
 """Host-only checks of the parts the automatic schedule gives the dataflow
 kernel (no GPU is touched)."""
+import time
+
 import numpy as np
 import pytest
 
@@ -40,3 +42,14 @@ def test_parts_with_many_imports_fall_back_to_the_full_set():
     col = np.concatenate([j, i], axis=1)[keep].astype(np.int32)
     st = H.tri_plan_stats(H.tri_analyze(CSR(n, rp, col, np.ones(col.size)), "lower", tune=H.tune_default(host_only=1)))
     assert st["dataflow"] == 1 and st["num_groups"] == 256
+
+
+def test_choosing_the_parts_costs_less_than_half_of_the_rest_of_the_setup():
+    A = synth.poisson3d(64)
+    best = [1e9, 1e9]
+    for _ in range(5):
+        for k, tune in enumerate((dict(num_groups=256), dict())):
+            t = time.perf_counter()
+            plans(A, **tune)
+            best[k] = min(best[k], time.perf_counter() - t)
+    assert best[1] < 1.5 * best[0], best
