@@ -136,7 +136,7 @@ typedef struct hec_tune {
                                ELL width 1..8 (the automatic width covers the longest row up
                                to 8) and at most two values a row older than the ring, a
                                pipelined kernel of 512 threads loads each level's rows several
-                               levels ahead and takes one or four columns of a system at a time;
+                               levels ahead and takes 1 to 16 columns of a system at a time;
                                otherwise block_threads sets the workgroup.
                                Schedule AUTO picks the dataflow kernel when its LDS holds
                                every part, else 7 for at least half as many independent

@@ -1040,15 +1040,17 @@ void build_sysq(ExecHost &ex, const Levels &lv, const std::vector<int32_t> &sys,
     // than the workgroup has threads (overlapping 64^3 subdomains of a 128^3
     // grid, 1 -> 2 rows: 1228 -> 1192 us; always two rows: 256 ILU(1) systems
     // of narrow levels 1195 -> 1574 us)
-    int64_t wider = 0;
-    for (int32_t l = 0; l < lvp[S]; ++l) wider += lvrow[l + 1] - lvrow[l] > kSysqThreads;
-    s.sq_rows = 4 * wider >= lvp[S] ? 2 : 1;
+    for (int32_t c = 0; c < kSysqShifts; ++c) {
+        int64_t wider = 0;
+        for (int32_t l = 0; l < lvp[S]; ++l) wider += lvrow[l + 1] - lvrow[l] > kSysqThreads >> c;
+        s.sq_rows[c] = 4 * wider >= lvp[S] ? 2 : 1;
+    }
     // levels a right-hand side (and a value older than the ring) is loaded
     // ahead at most: kSysqAhead turns of the k wavefront groups that take a
     // system's pieces of levels in turn (k_sysq_pipe)
     auto ahead = [&](int32_t widest) {
         int32_t wpg = 1;
-        while (wpg * 64 * s.sq_rows < widest && wpg < kSysqThreads / 64) wpg *= 2;
+        while (wpg * 64 * s.sq_rows[0] < widest && wpg < kSysqThreads / 64) wpg *= 2;
         return kSysqAhead * (kSysqThreads / 64 / wpg);
     };
     std::vector<int32_t> D(S, 0), W(S, 1);
@@ -1125,16 +1127,28 @@ void build_sysq(ExecHost &ex, const Levels &lv, const std::vector<int32_t> &sys,
         if (!s.sq_packed) s.sq_far.clear();
     }
     if (s.sq_packed) {
-        s.sq_pcp.assign(1, 0);
-        for (int32_t k = 0; k < S; ++k) {
-            for (int32_t l = lvp[k]; l < lvp[k + 1]; ++l)
-                for (int32_t b = lvrow[l], m = s.sq_rows * kSysqThreads; b < lvrow[l + 1]; b += m) {
-                    const int32_t slot = (l - lvp[k]) % s.sq_ring[2 * k];
-                    s.sq_pc.insert(s.sq_pc.end(), {b, std::min(m, lvrow[l + 1] - b),
-                                                   slot * s.sq_ring[2 * k + 1] + (b - lvrow[l]), 0});
-                }
-            s.sq_pcp.push_back((int32_t)s.sq_pc.size() / 4);
+        for (int32_t c = 0; c < (s.sq_global ? 1 : kSysqShifts); ++c) {
+            const int32_t m = s.sq_rows[c] * kSysqThreads >> c;
+            s.sq_pcp[c].assign(1, 0);
+            for (int32_t k = 0; k < S; ++k) {
+                for (int32_t l = lvp[k]; l < lvp[k + 1]; ++l)
+                    for (int32_t b = lvrow[l]; b < lvrow[l + 1]; b += m) {
+                        const int32_t slot = (l - lvp[k]) % s.sq_ring[2 * k];
+                        s.sq_pc[c].insert(s.sq_pc[c].end(), {b, std::min(m, lvrow[l + 1] - b),
+                                                             slot * s.sq_ring[2 * k + 1] + (b - lvrow[l]), 0});
+                    }
+                s.sq_pcp[c].push_back((int32_t)s.sq_pc[c].size() / 4);
+            }
         }
+        // a level costs as much as 128 of its rows (fitted to one column of
+        // systems of 87 to 348 rows a level)
+        double all = 0.0, most = 1.0;
+        for (int32_t k = 0; k < S; ++k) {
+            const double work = lvp[k + 1] - lvp[k] + (lvrow[lvp[k + 1]] - lvrow[lvp[k]]) / 128.0;
+            all += work;
+            most = std::max(most, work);
+        }
+        s.sq_balance = all / most;
         s.sq_zero.resize(n);
         for (int32_t x = 0; x < n; ++x) {
             const int32_t k = sys_of[x], zrow = s.sq_ring[2 * k] * s.sq_ring[2 * k + 1];

@@ -184,9 +184,12 @@ void upload_tri(DevTri &d, const TriHost &t, int32_t max_nrhs)
             upload(d.sq_ring, s.sq_ring);
             upload(d.sq_keep, s.sq_keep);
             upload(d.sq_far, s.sq_far);
-            upload(d.sq_pcp, s.sq_pcp);
-            upload(d.sq_pc, s.sq_pc);
-            d.sq_rows = s.sq_rows;
+            for (int32_t c = 0; c < kSysqShifts; ++c) {
+                upload(d.sq_pcp[c], s.sq_pcp[c]);
+                upload(d.sq_pc[c], s.sq_pc[c]);
+                d.sq_rows[c] = s.sq_rows[c];
+            }
+            d.sq_balance = s.sq_balance;
         }
     }
     // epoch, workgroups done, work counter (part queue / chunk batches)

@@ -86,6 +86,7 @@ struct TriArgs {
     int32_t imp_waves;           // dataflow kernel: wavefronts that fetch imports
     int32_t ldr, k0;             // right-hand sides of a vector's row, the first of this launch (R: of this launch)
     int32_t cgroups;             // system queue: groups of R columns a system's columns are cut into
+    int32_t cshift;              // system queue: log2 of the threads that share an item's row, each with its columns
     int32_t rec_chunks, rec_rest;  // system queue: 16-byte chunks and remaining dwords of a packed row (-1: not packed)
     int32_t xw_grouped, bin_grouped;  // system queue: xw / bin hold the groups one after the other
     const int32_t *ell_col;
@@ -191,8 +192,9 @@ struct DevTri {
     bool queue = false;            // dataflow parts taken from a counter (more parts than workgroups)
     bool sysq = false, sq_global = false;  // system queue kernel; some dependencies read from xw
     bool sq_packed = false;        // rows as records (w: their slots)
-    int32_t sq_lds_rows = 0, sq_full_rows = 0, sq_cols = 1, sq_rows = 1;  // as in Schedule
-    DevMem sq_lvp, sq_lvrow, sq_ring, sq_keep, sq_far, sq_pcp, sq_pc;
+    int32_t sq_lds_rows = 0, sq_full_rows = 0, sq_cols = 1, sq_rows[kSysqShifts] = {1, 1, 1};  // as in Schedule
+    double sq_balance = 1.0;
+    DevMem sq_lvp, sq_lvrow, sq_ring, sq_keep, sq_far, sq_pcp[kSysqShifts], sq_pc[kSysqShifts];
     int32_t chunk_rows = 0;
     bool max_lanes_one = true;     // every step runs one thread per (row, rhs)
     DevMem epoch, err, mbox;

@@ -55,6 +55,8 @@ struct HecHost {
 // chunk of one).  Rows read by a workgroup other than their owner are
 // "exported": their values also travel through a double-buffered mailbox
 // whose slots consumers poll until the value has arrived.
+constexpr int32_t kSysqShifts = 3;      // system queue: 1, 2 or 4 threads to a row of an item
+
 struct Schedule {
     int32_t kind = HEC_SCHED_LEVEL_PERSISTENT;
     int32_t groups = 0;
@@ -109,8 +111,11 @@ struct Schedule {
     bool sq_packed = false;          // rows as records (pipelined kernel): columns are ring rows, padding the zero row
     int32_t sq_full_rows = 0;        // the same if rings were sized for all max_nrhs columns (0: no limit on the right-hand sides)
     std::vector<int32_t> sq_lvp, sq_lvrow, sq_ring;
-    int32_t sq_rows = 1;             // packed rows: rows of a piece per thread
-    std::vector<int32_t> sq_pcp, sq_pc;  // packed rows: pieces of each system; first row, rows, first ring row (and 0) of each
+    // packed rows, for 1 << c threads to a row of an item: rows of a piece per
+    // thread; pieces of each system; first row, rows, first ring row (and 0) of each
+    int32_t sq_rows[kSysqShifts] = {1, 1, 1};
+    std::vector<int32_t> sq_pcp[kSysqShifts], sq_pc[kSysqShifts];
+    double sq_balance = 1.0;         // all systems' work over the largest one's
     std::vector<int32_t> sq_far;     // packed rows: two device rows read beyond the ring (n: none)
     std::vector<int32_t> sq_zero;    // packed rows: zero row of the row's ring
     std::vector<int8_t> sq_keep;     // rows read back from the global workspace

@@ -16,8 +16,10 @@ namespace hec {
 // conditional stores each level also waited for the stores of the level
 // before.)
 //
-// The workgroups take items, a system and a group of C (one or four) of its
-// columns, from a counter (largest system first).  Levels are cut into pieces
+// The workgroups take items, a system and a group of its columns, from a
+// counter (largest system first).  A thread has C (one or four) columns of a
+// row; 1 << cshift threads share a row of an item, neighbours in a wavefront, so
+// that a row's record is fetched once for them.  Levels are cut into pieces
 // of at most M rows per thread.  The wavefronts form
 // k groups that take a system's pieces in turn (k as large as its widest
 // piece allows); a turn's row data is loaded P turns ahead and its right-hand
@@ -37,7 +39,7 @@ namespace hec {
 // (items of one column), 2750 -> 1070 and 18240 -> 1310 us.  Column groups
 // alone gave 1537 and 2375.  P / H of
 // 5 / 2, 4 / 1 and 6 / 3 took 1203, 1193 and 1205 where 4 / 2 took 1189.
-// Needs no CSR tail, columns in multiples of C and vectors below 4 GiB (checked by the host).
+// Needs no CSR tail, columns in multiples of an item's and vectors below 4 GiB (checked by the host).
 
 typedef uint32_t sq_u4 __attribute__((ext_vector_type(4)));
 typedef uint32_t sq_u2 __attribute__((ext_vector_type(2)));
@@ -99,7 +101,9 @@ __global__ void __launch_bounds__(512) k_sysq_pipe(TriArgs a, const int32_t *__r
 {
     using Rec = RowRec<T, W>;
     constexpr int P = 4, H = kSysqAhead;
-    constexpr unsigned RB = C * sizeof(T);  // bytes of a ring row
+    constexpr unsigned RB = C * sizeof(T);  // a thread's bytes of a ring row
+    const int cs = FAR ? 0 : a.cshift;
+    const unsigned rowb = RB << cs;
     extern __shared__ __align__(16) unsigned char smem[];
     int *s_q = reinterpret_cast<int *>(smem + a.lds_ctl);
     const int tid = threadIdx.x, nt = blockDim.x;
@@ -132,11 +136,12 @@ __global__ void __launch_bounds__(512) k_sysq_pipe(TriArgs a, const int32_t *__r
         const int item = __builtin_amdgcn_readfirstlane(*s_q);
         if (item >= a.nparts * a.cgroups) break;
         const int q = item / a.cgroups, cg = item - q * a.cgroups;
+        const size_t k0 = (size_t)(cg * C) << cs;  // the item's first column
         const int slots = rings[2 * q], wide = rings[2 * q + 1];
-        const unsigned zoff = (unsigned)(slots * wide) * RB;
+        const unsigned zoff = (unsigned)(slots * wide) * rowb;
         if (a.trace && tid == 0 && cg == 0 && a.trace_stride > 0)
             a.trace[2 * (size_t)q * a.trace_stride] = __builtin_amdgcn_s_memrealtime();
-        if (tid < C) *reinterpret_cast<T *>(smem + zoff + tid * sizeof(T)) = T(0);
+        if (tid < C << cs) *reinterpret_cast<T *>(smem + zoff + tid * sizeof(T)) = T(0);
         const int l0 = pcp[q], l1 = pcp[q + 1];
         // a Krylov solve's mask of unfinished (system, rhs) problems: an item
         // whose right-hand sides have all finished is skipped (its rows feed
@@ -144,7 +149,7 @@ __global__ void __launch_bounds__(512) k_sysq_pipe(TriArgs a, const int32_t *__r
         if (a.act && l1 > l0) {
             const int sys = a.seg ? a.seg[pc[l0].x] : 0;
             int live = 0;
-            for (int c = 0; c < C; ++c) live |= a.act[(size_t)sys * a.ldr + cg * C + c];
+            for (int c = 0; c < C << cs; ++c) live |= a.act[(size_t)sys * a.ldr + k0 + c];
             if (!live) {
                 __syncthreads();  // every thread has read the item before it is replaced
                 continue;
@@ -153,24 +158,29 @@ __global__ void __launch_bounds__(512) k_sysq_pipe(TriArgs a, const int32_t *__r
         // where the item's columns lie: in a vector of the caller (row after
         // row, all right-hand sides) or in a workspace that holds the column
         // groups one after the other
-        const TIn *bin = static_cast<const TIn *>(a.bin) + (a.bin_grouped ? (size_t)cg * a.n * C : (size_t)cg * C);
+        const TIn *bin = static_cast<const TIn *>(a.bin) + (a.bin_grouped ? k0 * a.n : k0);
         const size_t ldin = a.bin_grouped ? C : a.ldr;
         const unsigned ldo = MODE == 0 && a.xw_grouped ? C : (unsigned)a.ldr;
         constexpr unsigned TO = MODE == 0 ? sizeof(T) : (MODE == 1 ? 8 : 4);
-        const BufRsrc rout =
-            MODE == 0 ? rsrc(static_cast<T *>(a.xw) + (a.xw_grouped ? (size_t)cg * a.n * C : (size_t)cg * C), (size_t)a.n * ldo * TO)
-                      : rsrc(static_cast<unsigned char *>(a.xout) + (size_t)cg * C * TO, (size_t)a.n * ldo * TO - (size_t)cg * C * TO);
+        const BufRsrc rout = MODE == 0 && a.xw_grouped
+                                 ? rsrc(static_cast<T *>(a.xw) + k0 * a.n, ((size_t)a.n * C << cs) * TO)
+                                 : rsrc(static_cast<unsigned char *>(MODE == 0 ? a.xw : a.xout) + k0 * TO,
+                                        ((size_t)a.n * ldo - k0) * TO);
         // the workspace of a solve into the caller's vector is only read here
         const bool grouped = MODE != 0 || a.xw_grouped;
         const unsigned ldx = grouped ? C : (unsigned)a.ldr;
-        const BufRsrc rxw = rsrc(static_cast<T *>(a.xw) + (grouped ? (size_t)cg * a.n * C : (size_t)cg * C),
-                                 ((size_t)a.n + 1) * ldx * sizeof(T));
+        const BufRsrc rxw = rsrc(static_cast<T *>(a.xw) + (grouped ? k0 * a.n : k0), ((size_t)a.n + 1) * ldx * sizeof(T));
         // wavefront groups: k groups take the pieces in turn (group g solves
         // pieces l0 + g, l0 + g + k, ...)
-        const int need = (min(wide, M * nt) + 64 * M - 1) / (64 * M);
+        const int need = (min(wide << cs, M * nt) + 64 * M - 1) / (64 * M);
         int wpg = 1;
         while (wpg < need && wpg < nw) wpg *= 2;
-        const int k = nw / wpg, grp = wave / wpg, ng = wpg * 64, tl = tid - grp * ng;
+        const int k = nw / wpg, grp = wave / wpg;
+        // rows a group takes at a time; the thread's row among them and its columns
+        const int ng = wpg * 64 >> cs, tl = (tid - grp * wpg * 64) >> cs, sub = tid & ((1 << cs) - 1);
+        const unsigned kb = (unsigned)sub * RB;
+        const TIn *bsub = bin + (a.bin_grouped ? (size_t)sub * a.n * C : (size_t)(sub * C));
+        const unsigned osub = (MODE == 0 && a.xw_grouped ? (unsigned)(sub * a.n * C) : (unsigned)(sub * C)) * TO;
         auto bounds = [&](int l) {
             int4 b = pc[min(l, l1 - 1)];
             if (l >= l1) b.y = 0;
@@ -197,7 +207,7 @@ __global__ void __launch_bounds__(512) k_sysq_pipe(TriArgs a, const int32_t *__r
         auto rhs = [&](Row &u) {
 #pragma unroll
             for (int m = 0; m < M; ++m) {
-                const TIn *src = bin + (size_t)(unsigned)u.gi[m] * ldin;
+                const TIn *src = bsub + (size_t)(unsigned)u.gi[m] * ldin;
 #pragma unroll
                 for (int c = 0; c < C; ++c) u.b[m][c] = src[c];
                 if constexpr (FAR) {
@@ -217,7 +227,9 @@ __global__ void __launch_bounds__(512) k_sysq_pipe(TriArgs a, const int32_t *__r
             }
 #pragma unroll
             for (int e = 0; e < W; ++e) {
-                unsigned o = row_off<T, W, RB>(u.d[m], e);
+                unsigned o;
+                if constexpr (FAR) o = row_off<T, W, RB>(u.d[m], e);
+                else o = row_off<T, W>(u.d[m], e, rowb, kb);
                 const T v = row_val<T, W>(u.d[m], e);
                 const bool far = FAR && o >= kSysqFar1 * RB, first = o == kSysqFar0 * RB;
                 if (FAR) o = min(o, zoff);
@@ -230,12 +242,12 @@ __global__ void __launch_bounds__(512) k_sysq_pipe(TriArgs a, const int32_t *__r
             }
             const bool ok = i < u.pc.y;
             if (ok) {
-                const unsigned o = (unsigned)(u.pc.z + i) * RB;
+                const unsigned o = (unsigned)(u.pc.z + i) * rowb + kb;
 #pragma unroll
                 for (int c = 0; c < C; ++c) *(LdsPtr<T>)(uintptr_t)(o + c * (unsigned)sizeof(T)) = s[c];
             }
             const int row = MODE == 0 ? u.pc.x + i : u.dst[m];
-            sq_put<(TO == 8)>(rout, ok && row >= 0 ? (unsigned)row * ldo * TO : kSysqDropped, s);
+            sq_put<(TO == 8)>(rout, ok && row >= 0 ? (unsigned)row * ldo * TO + osub : kSysqDropped, s);
             if constexpr (FAR && MODE != 0)  // also read back by a later level
                 sq_put<(sizeof(T) == 8)>(
                     rxw, ok && u.keep[m] ? (unsigned)(u.pc.x + i) * ldx * (unsigned)sizeof(T) : kSysqDropped, s);

@@ -997,32 +997,65 @@ int32_t sysq_columns(const DevTri &d, int32_t R)
     return c;
 }
 
-// Columns of one item of the pipelined kernel (0: not for it, which needs
-// packed rows and vectors within 32-bit buffer offsets).  Four load a row's
-// data once for them, one gives more and shorter items; both triangles, four ->
-// one: 64 overlapping subdomains of a 128^3 grid with 4 / 8 / 16 right-hand
-// sides 1083 -> 712 / 1092 -> 1237 / 1195 -> 1938 us, 256 ILU(1) systems in
-// FP64 with 4 / 8 / 16 1541 -> 1074 / 1582 -> 2075 / 1788 -> 4160 us.  So four
-// from 8 right-hand sides on, unless items of one all run at once.
-int32_t sysq_pipe_columns(const DevTri &d, int32_t R)
+// An item of the pipelined kernel: 1 << shift threads to a row, each with one
+// or four columns (0: not for it, which needs packed rows and vectors within
+// 32-bit buffer offsets).
+struct SysqItem {
+    int32_t columns = 0, shift = 0;
+    int32_t all() const { return columns << shift; }
+};
+
+// More columns to an item read a system's rows fewer times and share its chain
+// of levels, fewer give more and shorter items.  A call takes about
+// cost(item) * max(1, 1.35 * rounds): `rounds` are the items times the average
+// system's work over the compute units and the largest system's (two
+// workgroups of a compute unit slow each other down, hence 1.35), and the costs
+// of items against one of one column are fitted to measurements: four columns
+// of a thread, two and four threads to a row.  Both triangles, us, items of one
+// column / four columns of a thread / two / four such threads:
+//   512 subdomains of 4096 rows, FP32, 16 right-hand sides 1236 / 610 / 396 / 320
+//   295 of 2280 rows, FP32, 16                              289 / 166 / 132 / 108
+//   295 of 1576 rows, FP64, 16                              416 / 201 / 139 / 143
+//   64 of 32768 rows, FP32, 4 and 8                239 / 303 / -, 501 / 353 / 390
+//   64 uneven ones of a 128^3 grid, FP32, 4, 8, 16  723 / 1100, 1259 / 1114, 1887 / 1196
+//   32 uneven ones of a 100^3 grid, FP64, 16       1116 / 1301
+//   256 uneven ILU(1) systems, FP32, 4 and 8        847 / 1176, 1656 / 1222 / 1598
+// and two threads of one column: 32 systems of 50000 to 150000 rows, FP32, 16
+// right-hand sides 1738 -> 1107 (four columns of a thread 1272).
+// One or four columns of one thread alone made many even systems slower than
+// items of all their columns had been (512 subdomains, 4 / 8 / 16 right-hand
+// sides 319 / 297 / 612 us, in one item each 173 / 225 / 359).
+SysqItem sysq_pipe_item(const DevTri &d, int32_t R)
 {
-    if (!d.sysq || !d.sq_packed || ((size_t)d.n + 1) * R * 8 >= kSysqDropped) return 0;
-    auto fits = [&](int32_t c) {
-        return (size_t)std::max(1, d.sq_lds_rows) * c * (d.dt == HEC_F64 ? 8 : 4) + 32 <= (size_t)device_max_lds();
-    };
-    if (R >= 2 * kSysqColumns && R % kSysqColumns == 0 && (int64_t)d.groups * R >= 2 * device_cus() && fits(kSysqColumns))
-        return kSysqColumns;
-    return fits(1) ? 1 : 0;
+    SysqItem best;
+    if (!d.sysq || !d.sq_packed || ((size_t)d.n + 1) * R * 8 >= kSysqDropped) return best;
+    static constexpr double four[2] = {1.6, 1.95}, threads[2][kSysqShifts] = {{1.0, 1.47, 2.16}, {1.0, 1.75, 2.6}};
+    const bool f64 = d.dt == HEC_F64;
+    double least = 0.0;
+    for (int32_t columns : {1, kSysqColumns})
+        for (int32_t shift = 0; shift < (d.sq_global ? 1 : kSysqShifts); ++shift) {
+            const int32_t all = columns << shift;
+            if (R % all != 0 || (size_t)std::max(1, d.sq_lds_rows) * all * (f64 ? 8 : 4) + 32 > (size_t)device_max_lds())
+                continue;
+            const double cost = (columns == 1 ? 1.0 : four[f64]) * threads[f64][shift];
+            const double t = cost * std::max(1.0, 1.35 * d.sq_balance * (R / all) / device_cus());
+            if (best.columns == 0 || t < least) {
+                least = t;
+                best.columns = columns;
+                best.shift = shift;
+            }
+        }
+    return best;
 }
 
-SysqKernel sysq_pipe_kernel(const DevTri &d, const TriArgs &a, int32_t columns)
+SysqKernel sysq_pipe_kernel(const DevTri &d, const TriArgs &a, int32_t columns, int32_t shift)
 {
     const bool in = a.in_f64 != 0, far = d.sq_global, f64 = d.dt == HEC_F64;
     const int out = !a.xout ? 0 : (a.out_f64 ? 1 : 2);
     using Select = SysqKernel (*)(int, bool, int, bool);
     static constexpr Select one[2][3] = {{sq_f32_x1, sq_f32_d1, sq_f32_f1}, {sq_f64_x1, sq_f64_d1, sq_f64_f1}};
     static constexpr Select four[2][3] = {{sq_f32_x4, sq_f32_d4, sq_f32_f4}, {sq_f64_x4, sq_f64_d4, sq_f64_f4}};
-    return (columns == 1 ? one : four)[f64][out](d.w, in, d.sq_rows, far);
+    return (columns == 1 ? one : four)[f64][out](d.w, in, d.sq_rows[shift], far);
 }
 
 // Right-hand sides one launch of a dataflow plan holds.
@@ -1133,20 +1166,21 @@ void launch_typed(DevTri &d, TriArgs a, hipStream_t st)
             fail(HEC_ERR_CAPACITY, "system queue: the LDS ring exceeds the device limit at this nrhs");
         a.nparts = d.groups;
         a.ldr = a.R;
-        const int32_t piped = sysq_pipe_columns(d, a.ldr);
-        a.R = piped ? piped : sysq_columns(d, a.ldr);
-        a.cgroups = (a.ldr + a.R - 1) / a.R;
+        const SysqItem piped = sysq_pipe_item(d, a.ldr);
+        a.R = piped.columns ? piped.columns : sysq_columns(d, a.ldr);
+        a.cshift = piped.shift;
+        a.cgroups = piped.columns ? a.ldr / piped.all() : (a.ldr + a.R - 1) / a.R;
         const int items = d.groups * a.cgroups;
-        const size_t lds = (size_t)std::max(1, d.sq_lds_rows) * a.R * sizeof(T);
-        if (piped) {
-            const SysqKernel k = sysq_pipe_kernel(d, a, piped);
+        const size_t lds = ((size_t)std::max(1, d.sq_lds_rows) * a.R << a.cshift) * sizeof(T);
+        if (piped.columns) {
+            const SysqKernel k = sysq_pipe_kernel(d, a, piped.columns, piped.shift);
             if (!k) fail(HEC_ERR_INVALID_ARG, "internal: system queue with an unsupported record width");
             const size_t all = ((lds + 15) & ~(size_t)15) + 16;
             a.lds_ctl = (int32_t)all - 16;
             const int32_t cap = capacity_of((const void *)k, kSysqThreads, all, true);
             const int grid = std::max(1, std::min(items, cap));
-            hipLaunchKernelGGL(k, dim3(grid), dim3(kSysqThreads), all, st, a, d.sq_pcp.as<int32_t>(), d.sq_pc.as<int4>(),
-                               a.sq_ring);
+            hipLaunchKernelGGL(k, dim3(grid), dim3(kSysqThreads), all, st, a, d.sq_pcp[a.cshift].as<int32_t>(),
+                               d.sq_pc[a.cshift].as<int4>(), a.sq_ring);
             hip_check(hipGetLastError(), "k_sysq_pipe launch");
             return;
         }
@@ -1430,7 +1464,8 @@ void launch_lu(DevTri &L, DevTri &U, bool lu_shared, const void *r, hec_dtype_t 
     }
     // two system queues: y is stored group of columns by group of columns, so
     // that an item writes and reads whole cache lines of it
-    const bool grouped = L.dt == U.dt && sysq_pipe_columns(L, R) > 0 && sysq_pipe_columns(L, R) == sysq_pipe_columns(U, R);
+    const bool grouped = L.dt == U.dt && sysq_pipe_item(L, R).columns > 0 &&
+                         sysq_pipe_item(L, R).columns == sysq_pipe_item(U, R).columns;
     TriArgs a = tri_args(L, r, in_dt, gather_l, y, nullptr, in_dt, nullptr, R);
     TriArgs b = tri_args(U, y, L.dt, qmap, uw, z, out_dt, scatter_u, R);
     a.xw_grouped = b.bin_grouped = grouped ? 1 : 0;

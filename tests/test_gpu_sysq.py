@@ -108,3 +108,75 @@ def test_automatic_choice_by_columns():
             H.ilu_apply(f, r, x)
         torch.cuda.synchronize()
         assert torch.equal(z[0], z[1]), nrhs
+
+
+# even systems, enough for items of many columns: levels of one row, of rows
+# that do not fill a wavefront's share, of one and of several pieces
+EVEN = [((1, 5, 1), 400), ((30, 12, 2), 300), ((129, 5, 1), 290), ((600, 3, 2), 270), ((1100, 2, 1), 260)]
+
+
+@pytest.mark.parametrize("dt", ["f64", "f32"])
+@pytest.mark.parametrize("system,count", EVEN)
+def test_several_threads_to_a_row(system, count, dt):
+    # 2, 6: two threads of one column; 8, 24: two of four; 16: four of four
+    A = banded([system] * count, True)
+    ptr = (np.arange(count + 1) * system[0] * system[1]).astype(np.int32)
+    f = [H.batch_setup(A, ptr, "ilu0", factor_dtype=dt, tune=H.tune_default(**t))
+         for t in (dict(schedule="level_launch"), dict(QUEUE, max_nrhs=24))]
+    assert H.tri_plan_stats(H.ilu_plans(f[1])[0])["sysq"] == 1
+    for nrhs in (1, 2, 4, 6, 7, 8, 16, 24):
+        for vt in (torch.float64, torch.float32):
+            r = torch.from_numpy(np.random.default_rng(nrhs).standard_normal((A.n, nrhs))).to(vt).cuda()
+            out = []
+            for h in f:
+                z = torch.full_like(r, float("nan"))
+                for _ in range(2):
+                    H.ilu_apply(h, r, z)
+                H.tri_solve_lower(H.ilu_plans(h)[0], r, r2 := torch.empty_like(r))
+                out.append((z, r2))
+            torch.cuda.synchronize()
+            assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1]), nrhs
+
+
+def test_finished_problems_of_an_item():
+    # BiCGSTAB with zero right-hand sides, finished from the start, in some of
+    # the columns that an item of eight solves together
+    import synth
+
+    A = synth.poisson3d(48, 40, 36)
+    owner = synth.grid_bisection(48, 40, 36, 300)
+    b = torch.from_numpy(np.random.default_rng(2).standard_normal((A.n, 16))).cuda()
+    b[:, [1, 8, 9, 10, 11, 12, 13, 14, 15]] = 0.0
+    M = H.hec_from_csr(A)
+    out = []
+    for t in (dict(schedule="level_launch"), QUEUE):
+        s = H.ras_setup(A, 300, owner, overlap=1, factor_dtype="f32", tune=H.tune_default(max_nrhs=16, **t))
+        x = torch.zeros_like(b)
+        st, info = H.krylov_solve(M, s, b, x, method="bicgstab", rtol=1e-8)
+        assert st == 0
+        out.append((x, [q.iters for q in info]))
+    assert out[0][1] == out[1][1] and torch.equal(out[0][0], out[1][0])
+
+
+def test_many_even_systems_share_their_rows_between_columns():
+    # 512 subdomains: sixteen columns together, not one or four at a time
+    import synth
+
+    A = synth.poisson3d(96)
+    s = H.ras_setup(A, 512, synth.grid_bisection(96, 96, 96, 512), overlap=0, factor_dtype="f32",
+                    tune=H.tune_default(max_nrhs=16, **QUEUE))
+    times = {}
+    for k in (1, 4, 16):
+        r = torch.zeros(A.n, k, dtype=torch.float64, device="cuda")
+        z = torch.empty_like(r)
+        laps = []
+        for _ in range(6):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(10):
+                H.ras_apply(s, r, z)
+            b.record()
+            b.synchronize()
+            laps.append(a.elapsed_time(b))
+        times[k] = min(laps)
+    assert times[4] < 2.2 * times[1] and times[16] < 4.5 * times[1], times
