@@ -130,15 +130,19 @@ __device__ __forceinline__ void df_copy_ints(int *dst, const int32_t *src, int c
     }
 }
 
-// Empty the mailbox half the next launch reads, each workgroup its share.
-// Every workgroup does it before its first wait, for all plans of the launch:
-// a launch whose waits give up still advances the epochs, so a slot left out
+// Empty this workgroup's share of the mailbox half the next launch reads: the
+// slots of part g, whose values it will write then (those that other
+// workgroups had emptied took longer to arrive: 20011 irregular rows 224 ->
+// 230 us), or, where parts are taken from a queue, of all slots.  Every
+// workgroup does it before its first wait, for all plans of the launch: a
+// launch whose waits give up still advances the epochs, so a slot left out
 // would offer the next launch the value of the one before.
-template <typename T> __device__ __forceinline__ void df_clear(const TriArgs &a, T *other)
+template <typename T> __device__ __forceinline__ void df_clear(const TriArgs &a, int g, T *other)
 {
-    const size_t count = (size_t)a.nexp * a.mbox_stride, step = (size_t)gridDim.x * gridDim.y * blockDim.x;
-    const size_t block = (size_t)blockIdx.y * gridDim.x + blockIdx.x;
-    for (size_t i = block * blockDim.x + threadIdx.x; i < count; i += step) other[i] = sentinel<T>();
+    const size_t m0 = a.queue ? 0 : (size_t)a.exp_ptr[g] * a.mbox_stride;
+    const size_t m1 = (size_t)(a.queue ? a.nexp : a.exp_ptr[g + 1]) * a.mbox_stride;
+    const size_t share = a.queue ? blockIdx.x : blockIdx.y, shares = a.queue ? gridDim.x : gridDim.y;
+    for (size_t i = m0 + share * blockDim.x + threadIdx.x; i < m1; i += shares * blockDim.x) other[i] = sentinel<T>();
 }
 
 // Everything but the right-hand side: sentinels, the zero row and index lists.
@@ -530,7 +534,7 @@ __global__ void __launch_bounds__(512) k_dataflow(TriArgs a)
         }
         const int g = a.queue ? ctl->part : (int)blockIdx.x;
         if (g >= a.nparts) {
-            if (round == 0) df_clear(a, other);
+            if (round == 0) df_clear(a, 0, other);  // queue: no part left for it
             break;
         }
         const DfPart<T> pt = df_part<T>(a, g, k0, R, smem);
@@ -539,7 +543,7 @@ __global__ void __launch_bounds__(512) k_dataflow(TriArgs a)
             if (a.in_f64) df_fill_b<T, UNIT, R1>(a, pt, R, static_cast<const double *>(a.bin));
             else df_fill_b<T, UNIT, R1>(a, pt, R, static_cast<const float *>(a.bin));
             df_fill_lists(a, pt, R);
-            if (round == 0) df_clear(a, other);
+            if (round == 0) df_clear(a, g, other);
         });
         const unsigned long long t_done = TRACE ? __builtin_amdgcn_s_memrealtime() : 0ull;
         df_report(a, ctl);
@@ -610,8 +614,8 @@ __global__ void __launch_bounds__(512) k_dataflow_lu(TriArgs l, TriArgs u)
         if (l.in_f64) df_fill_b<T, true, R1>(l, pl, R, static_cast<const double *>(l.bin));
         else df_fill_b<T, true, R1>(l, pl, R, static_cast<const float *>(l.bin));
         df_fill_lists(l, pl, R);
-        df_clear(l, half(l, ctl->epoch + 1u));
-        df_clear(u, half(u, ctl->epoch2 + 1u));
+        df_clear(l, g, half(l, ctl->epoch + 1u));
+        df_clear(u, g, half(u, ctl->epoch2 + 1u));
     });
     if (!ctl->abort) {
         const DfPart<T> pu = df_part<T>(u, g, k0, R, smem);
