@@ -142,7 +142,8 @@ typedef struct hec_tune {
                                every part, else 7 for at least half as many independent
                                systems as compute units or, with max_nrhs above 8 and where the
                                pipelined kernel takes it, at least as many columns of systems
-                               (nsys * max_nrhs) as compute units, else 5 unless the levels are very
+                               (nsys * max_nrhs) as compute units (calls with few of them
+                               then run on 5 where an estimate finds it faster), else 5 unless the levels are very
                                wide (2^20 (row, rhs) items per level on average or more),
                                else one launch per level */
 } hec_tune_t;

@@ -1148,6 +1148,7 @@ void build_sysq(ExecHost &ex, const Levels &lv, const std::vector<int32_t> &sys,
             all += work;
             most = std::max(most, work);
         }
+        s.sq_most = most;
         s.sq_balance = all / most;
         s.sq_zero.resize(n);
         for (int32_t x = 0; x < n; ++x) {
@@ -1537,7 +1538,14 @@ void build_exec(TriHost &t, const Csr &a, const Tune &tune, const DeviceShape &d
     ex.sched.kind = kind;
     ex.sched.df_accept = accept;
     if (sysq) {
+        std::vector<int32_t> col;
+        if (tune.sq_few) col = ex.ell_col;
         build_sysq(ex, lv, sq_sys, sq_lvrow, sq_lvp, R, t.dt == HEC_F64 ? 8 : 4, dev);
+        Schedule &s = ex.sched;
+        if (tune.sq_few && s.sq_packed && syncfree_us(lv.nlev, n, 1) < sysq_us(s.sq_most, s.sq_global)) {
+            s.sq_col = std::move(col);
+            s.sq_order = ex.xinv;
+        }
         return;
     }
     // the dataflow owner kernel runs each step as one wavefront's unit (at
@@ -1694,6 +1702,7 @@ TriHost analyze(const Csr &a, bool upper, bool unit, hec_dtype_t dt, const Tune 
             Tune q = tu;
             q.schedule = HEC_SCHED_LEVEL_PERSISTENT;
             q.variant = 7;
+            q.sq_few = !half;
             t.variant = 7;
             attempt(q);
             if (half) return t;

@@ -190,6 +190,13 @@ void upload_tri(DevTri &d, const TriHost &t, int32_t max_nrhs)
                 d.sq_rows[c] = s.sq_rows[c];
             }
             d.sq_balance = s.sq_balance;
+            d.sq_most = s.sq_most;
+            upload(d.sq_order, s.sq_order);
+            if (!s.sq_col.empty()) {
+                std::vector<int32_t> col((size_t)d.w * d.ld, d.n);
+                std::copy(s.sq_col.begin(), s.sq_col.end(), col.begin());
+                upload(d.ell_col, col);
+            }
         }
     }
     // epoch, workgroups done, work counter (part queue / chunk batches)

@@ -126,6 +126,7 @@ struct TriArgs {
     const int32_t *sq_lvp, *sq_lvrow, *sq_ring;  // system queue: levels per system, level rows, rings
     const int8_t *sq_keep;                        // system queue: rows also stored to xw (read beyond a ring)
     const int32_t *sq_far;                        // packed rows: the two rows read beyond the ring (n: none)
+    const int32_t *order;                         // barrier-free kernel: device rows in level order (null: as they are)
 };
 
 // Kernels of one launch per triangle that take nothing but TriArgs.
@@ -193,7 +194,8 @@ struct DevTri {
     bool sysq = false, sq_global = false;  // system queue kernel; some dependencies read from xw
     bool sq_packed = false;        // rows as records (w: their slots)
     int32_t sq_lds_rows = 0, sq_full_rows = 0, sq_cols = 1, sq_rows[kSysqShifts] = {1, 1, 1};  // as in Schedule
-    double sq_balance = 1.0;
+    double sq_most = 1.0, sq_balance = 1.0;
+    DevMem sq_order;               // device rows in level order (empty: not for the barrier-free kernel)
     DevMem sq_lvp, sq_lvrow, sq_ring, sq_keep, sq_far, sq_pcp[kSysqShifts], sq_pc[kSysqShifts];
     int32_t chunk_rows = 0;
     bool max_lanes_one = true;     // every step runs one thread per (row, rhs)

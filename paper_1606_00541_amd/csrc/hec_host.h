@@ -115,7 +115,11 @@ struct Schedule {
     // thread; pieces of each system; first row, rows, first ring row (and 0) of each
     int32_t sq_rows[kSysqShifts] = {1, 1, 1};
     std::vector<int32_t> sq_pcp[kSysqShifts], sq_pc[kSysqShifts];
+    double sq_most = 1.0;            // work of the largest system: its levels and a 128th of its rows
     double sq_balance = 1.0;         // all systems' work over the largest one's
+    // also laid out for the barrier-free kernel (few right-hand sides): the
+    // device rows in level order, and the ELL columns as device rows
+    std::vector<int32_t> sq_order, sq_col;
     std::vector<int32_t> sq_far;     // packed rows: two device rows read beyond the ring (n: none)
     std::vector<int32_t> sq_zero;    // packed rows: zero row of the row's ring
     std::vector<int8_t> sq_keep;     // rows read back from the global workspace
@@ -172,6 +176,7 @@ struct Tune {
                              // 4 owner dataflow
     // set by the analysis itself:
     bool choose_parts = false;  // dataflow kernel under an automatic schedule: pick the parts by estimate
+    bool sq_few = false;        // system queue: also lay out for the barrier-free kernel where that may win
     // parts of another triangle over the same rows (original row -> part), to be used as they are
     const std::vector<int32_t> *share_part = nullptr;
     int32_t share_parts = 0, share_accept = 0;
@@ -186,6 +191,12 @@ constexpr int32_t kSysqAhead = 2;       // turns its right-hand sides are loaded
 constexpr uint32_t kSysqFar0 = 0xffff, kSysqFar1 = 0xfffe;  // packed columns: the row's first, second value beyond the ring
 constexpr uint32_t kSysqDropped = 0xf0000000u;  // byte offset past every output vector of its kernel
 // ELL slots of a row record of the pipelined system queue for ELL width w.
+// Microseconds of one triangle on the barrier-free kernel (levels, then the
+// (row, rhs) items) and of the largest system on the queue (one column), fitted
+// to 16 to 64 uneven systems of 135 to 725 levels; queues that read values
+// beyond their rings take longer.
+inline double syncfree_us(int32_t nlev, int32_t n, int32_t R) { return 1.15 * nlev + 1e-5 * (double)n * R; }
+inline double sysq_us(double most, bool far) { return (far ? 0.28 : 0.2) * most; }
 inline int32_t sysq_width(int32_t w) { return w <= 2 ? 2 : (w <= 4 ? w : (w <= 6 ? 6 : 8)); }
 constexpr int32_t kDataflowPad = 16;  // descriptors the kernel may read past a part's last step
 size_t dataflow_lds_bytes(int32_t rows, int32_t ints, int32_t R, size_t tsize);

@@ -764,6 +764,13 @@ OwnerKernel split_kernel(int w, bool unit, size_t &lds, int rows, int CH)
     }
 }
 
+// Address of a dword of a packed row (RowRecord::first and stride).
+__device__ __forceinline__ const unsigned char *rec_dword(const TriArgs &a, const unsigned char *p, int x, int dw)
+{
+    if (dw < 4 * a.rec_chunks) return p + ((size_t)(dw / 4) * a.ld + x) * 16 + 4 * (dw % 4);
+    return p + (size_t)a.rec_chunks * a.ld * 16 + ((size_t)x * a.rec_rest + (dw - 4 * a.rec_chunks)) * 4;
+}
+
 // Barrier-free solve of a level-ordered plan through global memory, for
 // solutions too large for LDS (the alternative to one launch per level).  The
 // (row, rhs) items in level order are cut into chunks of 64, dealt
@@ -783,6 +790,8 @@ OwnerKernel split_kernel(int w, bool unit, size_t &lds, int rows, int CH)
 // MAXW > 0: rows of at most MAXW ELL slots keep their columns and values in
 // registers, loaded once, and every poll issues all input loads together (one
 // memory round trip per poll); MAXW = 0: any width, columns re-read per poll.
+// Packed rows (plans of the system queue that run here with few right-hand
+// sides; at most 8 slots) are taken in level order through `order`.
 template <typename T, typename TIn, typename TOut, int MAXW>
 __global__ void __launch_bounds__(256) k_syncfree(TriArgs a, int waves)
 {
@@ -796,8 +805,9 @@ __global__ void __launch_bounds__(256) k_syncfree(TriArgs a, int waves)
     for (long ch = wave; ch < nch; ch += waves) {
         const long t = (ch << 6) + lane;
         bool todo = t < items;
-        const int x = todo ? (int)(t / a.R) : 0;
-        const int k = todo ? (int)(t - (long)x * a.R) : 0;
+        const int row = todo ? (int)(t / a.R) : 0;
+        const int k = todo ? (int)(t - (long)row * a.R) : 0;
+        const int x = a.order ? a.order[row] : row;
         // a finished problem's rows are skipped: they feed only that problem
         if (todo && a.act && !a.act[(a.seg ? a.seg[x] : 0) * a.R + k]) todo = false;
         T b = T(0);
@@ -811,7 +821,11 @@ __global__ void __launch_bounds__(256) k_syncfree(TriArgs a, int waves)
 #pragma unroll
             for (int e = 0; e < NW; ++e) {
                 cr[e] = e < a.w ? a.ell_col[(size_t)e * a.ld + x] : a.n;
-                vr[e] = e < a.w ? ev[(size_t)e * a.ld + x] : T(0);
+                const T *v = ev + (size_t)e * a.ld + x;
+                if (a.rec_chunks >= 0)
+                    v = reinterpret_cast<const T *>(
+                        rec_dword(a, static_cast<const unsigned char *>(a.ell_val), x, e * (int)(sizeof(T) / 4)));
+                vr[e] = e < a.w ? *v : T(0);
             }
         }
         unsigned spins = 0;
@@ -876,13 +890,6 @@ __global__ void __launch_bounds__(256) k_syncfree(TriArgs a, int waves)
             }
         }
     }
-}
-
-// Address of a dword of a packed row (RowRecord::first and stride).
-__device__ __forceinline__ const unsigned char *rec_dword(const TriArgs &a, const unsigned char *p, int x, int dw)
-{
-    if (dw < 4 * a.rec_chunks) return p + ((size_t)(dw / 4) * a.ld + x) * 16 + 4 * (dw % 4);
-    return p + (size_t)a.rec_chunks * a.ld * 16 + ((size_t)x * a.rec_rest + (dw - 4 * a.rec_chunks)) * 4;
 }
 
 // System queue: every workgroup takes whole independent systems from a
@@ -997,11 +1004,22 @@ int32_t sysq_columns(const DevTri &d, int32_t R)
     return c;
 }
 
+bool capturing(hipStream_t st)
+{
+    hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &s) != hipSuccess) {
+        (void)hipGetLastError();  // another stream's capture forbids the question
+        return true;
+    }
+    return s != hipStreamCaptureStatusNone;
+}
+
 // An item of the pipelined kernel: 1 << shift threads to a row, each with one
 // or four columns (0: not for it, which needs packed rows and vectors within
 // 32-bit buffer offsets).
 struct SysqItem {
     int32_t columns = 0, shift = 0;
+    bool few = false;  // the barrier-free kernel instead
     int32_t all() const { return columns << shift; }
 };
 
@@ -1025,7 +1043,7 @@ struct SysqItem {
 // One or four columns of one thread alone made many even systems slower than
 // items of all their columns had been (512 subdomains, 4 / 8 / 16 right-hand
 // sides 319 / 297 / 612 us, in one item each 173 / 225 / 359).
-SysqItem sysq_pipe_item(const DevTri &d, int32_t R)
+SysqItem sysq_pipe_item(const DevTri &d, int32_t R, hipStream_t st)
 {
     SysqItem best;
     if (!d.sysq || !d.sq_packed || ((size_t)d.n + 1) * R * 8 >= kSysqDropped) return best;
@@ -1045,6 +1063,16 @@ SysqItem sysq_pipe_item(const DevTri &d, int32_t R)
                 best.shift = shift;
             }
         }
+    // A few uneven systems with few columns leave most compute units idle for
+    // the largest one's time, which every unit shares on the barrier-free
+    // kernel.  Both triangles, us, queue / barrier-free: 32 subdomains of a
+    // 100^3 grid, FP64, 1 / 4 / 16 right-hand sides 609 / 522, 757 / 642, 1119 /
+    // 1343; 64 of a 128^3 grid, FP32, 1 / 4 690 / 670, 725 / 942; 16 of a 64^3
+    // grid, FP32, one 215 / 304.  (That kernel is launched cooperatively, so
+    // not into a graph, where the queue stays.)
+    best.few = d.sq_order.p && !d.trace && syncfree_us(d.nlev, d.n, R) < sysq_us(d.sq_most, d.sq_global) * least &&
+               !capturing(st);
+    if (best.few) best.columns = 0;
     return best;
 }
 
@@ -1136,29 +1164,34 @@ template <typename T> void launch_dataflow(DevTri &d, TriArgs a, hipStream_t st)
     }
 }
 
+template <typename T, typename TIn, typename TOut> void launch_syncfree(DevTri &d, const TriArgs &a, hipStream_t st)
+{
+    const size_t cnt = ((size_t)d.n + 1) * a.R;
+    hipLaunchKernelGGL(k_fill_sentinel<T>, dim3((unsigned)((cnt + 255) / 256)), dim3(256), 0, st,
+                       static_cast<T *>(a.xw), cnt, (unsigned *)nullptr);
+    // about one wavefront per chunk of an average level (at least two
+    // workgroups per compute unit), within half the occupancy; the
+    // cooperative launch guarantees co-residency (it costs tens of
+    // microseconds, small beside this kernel's milliseconds)
+    const long chunks = ((long)d.n * a.R + 63) / 64;
+    // rows of at most 8 (or 16) ELL slots keep them in registers
+    const void *kern = d.w <= 8 ? (const void *)k_syncfree<T, TIn, TOut, 8>
+                     : (d.w <= 16 ? (const void *)k_syncfree<T, TIn, TOut, 16> : (const void *)k_syncfree<T, TIn, TOut, 0>);
+    const int cap = capacity_of(kern, 256, 0);
+    const long per_level = chunks / std::max(1, d.nlev);
+    const long lim = std::min<long>(std::max(1, cap / 2), std::max<long>(2L * device_cus(), per_level / 4));
+    const int grid = (int)std::max<long>(1, std::min<long>(lim, (chunks + 3) / 4));
+    int waves = grid * 4;
+    void *args[] = {(void *)&a, (void *)&waves};
+    hip_check(hipLaunchCooperativeKernel(kern, dim3(grid), dim3(256), args, 0, st), "k_syncfree cooperative launch");
+}
+
 template <typename T, typename TIn, typename TOut>
 void launch_typed(DevTri &d, TriArgs a, hipStream_t st)
 {
     if (d.n == 0) return;
     if (d.kind == HEC_SCHED_LEVEL_LAUNCH && d.variant == 5) {
-        const size_t cnt = ((size_t)d.n + 1) * a.R;
-        hipLaunchKernelGGL(k_fill_sentinel<T>, dim3((unsigned)((cnt + 255) / 256)), dim3(256), 0, st,
-                           static_cast<T *>(a.xw), cnt, (unsigned *)nullptr);
-        // about one wavefront per chunk of an average level (at least two
-        // workgroups per compute unit), within half the occupancy; the
-        // cooperative launch guarantees co-residency (it costs tens of
-        // microseconds, small beside this kernel's milliseconds)
-        const long chunks = ((long)d.n * a.R + 63) / 64;
-        // rows of at most 8 (or 16) ELL slots keep them in registers
-        const void *kern = d.w <= 8 ? (const void *)k_syncfree<T, TIn, TOut, 8>
-                         : (d.w <= 16 ? (const void *)k_syncfree<T, TIn, TOut, 16> : (const void *)k_syncfree<T, TIn, TOut, 0>);
-        const int cap = capacity_of(kern, 256, 0);
-        const long per_level = chunks / std::max(1, d.nlev);
-        const long lim = std::min<long>(std::max(1, cap / 2), std::max<long>(2L * device_cus(), per_level / 4));
-        const int grid = (int)std::max<long>(1, std::min<long>(lim, (chunks + 3) / 4));
-        int waves = grid * 4;
-        void *args[] = {(void *)&a, (void *)&waves};
-        hip_check(hipLaunchCooperativeKernel(kern, dim3(grid), dim3(256), args, 0, st), "k_syncfree cooperative launch");
+        launch_syncfree<T, TIn, TOut>(d, a, st);
         return;
     }
     if (d.sysq) {
@@ -1166,7 +1199,12 @@ void launch_typed(DevTri &d, TriArgs a, hipStream_t st)
             fail(HEC_ERR_CAPACITY, "system queue: the LDS ring exceeds the device limit at this nrhs");
         a.nparts = d.groups;
         a.ldr = a.R;
-        const SysqItem piped = sysq_pipe_item(d, a.ldr);
+        const SysqItem piped = sysq_pipe_item(d, a.ldr, st);
+        if (piped.few) {
+            a.order = d.sq_order.as<int32_t>();
+            launch_syncfree<T, TIn, TOut>(d, a, st);
+            return;
+        }
         a.R = piped.columns ? piped.columns : sysq_columns(d, a.ldr);
         a.cshift = piped.shift;
         a.cgroups = piped.columns ? a.ldr / piped.all() : (a.ldr + a.R - 1) / a.R;
@@ -1464,8 +1502,8 @@ void launch_lu(DevTri &L, DevTri &U, bool lu_shared, const void *r, hec_dtype_t 
     }
     // two system queues: y is stored group of columns by group of columns, so
     // that an item writes and reads whole cache lines of it
-    const bool grouped = L.dt == U.dt && sysq_pipe_item(L, R).columns > 0 &&
-                         sysq_pipe_item(L, R).columns == sysq_pipe_item(U, R).columns;
+    const bool grouped = L.dt == U.dt && sysq_pipe_item(L, R, st).columns > 0 &&
+                         sysq_pipe_item(L, R, st).columns == sysq_pipe_item(U, R, st).columns;
     TriArgs a = tri_args(L, r, in_dt, gather_l, y, nullptr, in_dt, nullptr, R);
     TriArgs b = tri_args(U, y, L.dt, qmap, uw, z, out_dt, scatter_u, R);
     a.xw_grouped = b.bin_grouped = grouped ? 1 : 0;

@@ -180,3 +180,62 @@ def test_many_even_systems_share_their_rows_between_columns():
             laps.append(a.elapsed_time(b))
         times[k] = min(laps)
     assert times[4] < 2.2 * times[1] and times[16] < 4.5 * times[1], times
+
+
+def uneven_slabs(nx, parts, nrhs, **tune):
+    """RAS in FP64 on contiguous subdomains of 1/4 to some 3 times the average size."""
+    import synth
+
+    A = synth.poisson3d(nx)
+    lo = A.n // (4 * parts)
+    size = lo + np.floor(np.random.default_rng(parts).dirichlet(np.full(parts, 2.0)) * (A.n - parts * lo)).astype(int)
+    size[-1] += A.n - size.sum()
+    owner = np.repeat(np.arange(parts, dtype=np.int32), size)
+    return A, H.ras_setup(A, parts, owner, overlap=1, tune=H.tune_default(max_nrhs=nrhs, **tune))
+
+
+def test_few_columns_of_a_few_uneven_systems():
+    # a plan made for 16 right-hand sides that the queue's columns chose; calls
+    # with few of them run on the barrier-free kernel, in a graph on the queue
+    A, ref = uneven_slabs(100, 32, 16, schedule="level_launch")
+    _, s = uneven_slabs(100, 32, 16)
+    for step in range(2):
+        for nrhs in (1, 2, 3, 4, 8, 16, 20):
+            r = torch.from_numpy(np.random.default_rng(nrhs).standard_normal((A.n, nrhs))).cuda()
+            want = torch.empty_like(r)
+            H.ras_apply(ref, r, want)
+            for _ in range(2):
+                z = torch.full_like(r, float("nan"))
+                H.ras_apply(s, r, z)
+                assert torch.equal(z, want), (step, nrhs)
+            if nrhs in (1, 16):
+                g = H.hec_graph_capture(s, r, z)
+                for _ in range(3):
+                    z.fill_(float("nan"))
+                    H.hec_graph_launch(g)
+                    H.ras_apply(s, r, torch.empty_like(r))
+                    torch.cuda.synchronize()
+                    assert torch.equal(z, want), (step, nrhs)
+        val = A.val * np.where(A.col == np.repeat(np.arange(A.n), np.diff(A.rowptr)), 1.25, 1.0)
+        B = CSR(A.n, A.rowptr, A.col, val)
+        for h in (ref, s):
+            H.ras_refactor(h, B)
+
+
+def test_few_columns_cost_what_the_barrier_free_kernel_takes():
+    times = []
+    for tune in (dict(schedule="level_launch", kernel_variant=5), {}):
+        A, s = uneven_slabs(100, 32, 16, **tune)
+        r = torch.zeros(A.n, 1, dtype=torch.float64, device="cuda")
+        z = torch.empty_like(r)
+        laps = []
+        for _ in range(8):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(10):
+                H.ras_apply(s, r, z)
+            b.record()
+            b.synchronize()
+            laps.append(a.elapsed_time(b))
+        times.append(min(laps))
+    assert times[1] < 1.1 * times[0], times
