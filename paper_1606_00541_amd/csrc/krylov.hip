@@ -232,21 +232,9 @@ struct LinArgs {
 // out[:,c] = sum_t coef[t][c] * in_t[:,c]; terms with a zero coefficient are
 // left out, so a stopped problem's stale vectors (possibly NaN) never reach
 // its output
-__global__ void __launch_bounds__(256) k_lincomb(LinArgs a, long total, int R, int P, const int32_t *seg)
+__device__ __forceinline__ void lincomb_put(const LinArgs &a, long t, const double (&cf)[kMaxTerms], const double (&v)[kMaxTerms])
 {
-    const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= total) return;
-    const int c = col_of(t, R, seg);
-    // every term's loads before the first use; a term left out is loaded and
-    // dropped (with the 32-bit index, 64^3 and 16 right-hand sides, two to
-    // three terms: 26.6 -> 22.1 us)
-    double cf[kMaxTerms], v[kMaxTerms], s = 0.0;
-#pragma unroll
-    for (int q = 0; q < kMaxTerms; ++q)
-        if (q < a.nt) {
-            cf[q] = a.coef[q * P + c];
-            v[q] = a.in[q][t];
-        }
+    double s = 0.0;
 #pragma unroll
     for (int q = 0; q < kMaxTerms; ++q)
         if (q < a.nt) {
@@ -255,6 +243,55 @@ __global__ void __launch_bounds__(256) k_lincomb(LinArgs a, long total, int R, i
         }
     a.out[t] = s;
     if (a.out2) a.out2[t] = s;
+}
+
+// Every term's loads before the first use; a term left out is loaded and
+// dropped (with the 32-bit index, 64^3 and 16 right-hand sides, two to three
+// terms: 26.6 -> 22.1 us).
+__global__ void __launch_bounds__(256) k_lincomb(LinArgs a, long total, int R, int P)
+{
+    const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= total) return;
+    const int c = col_of(t, R, nullptr);
+    double cf[kMaxTerms], v[kMaxTerms];
+#pragma unroll
+    for (int q = 0; q < kMaxTerms; ++q)
+        if (q < a.nt) {
+            cf[q] = a.coef[q * P + c];
+            v[q] = a.in[q][t];
+        }
+    lincomb_put(a, t, cf, v);
+}
+
+// The same for a batch, whose finished systems are whole rows: a term that no
+// lane of a wavefront has is not loaded.  The vectors then wait for the
+// coefficients and those for the row's system, so a thread takes four
+// elements, a wavefront's apart, for more loads in flight.  64 systems, 1.9
+// million rows, four right-hand sides, none / seven of eight systems finished:
+// every term loaded 46.2 / 44.2 us, one element a thread 51.9 / 39.1, four 44.5 /
+// 35.4 (term after term, before, 54.5 / 41.4).
+constexpr int kLinElems = 4;
+__global__ void __launch_bounds__(256) k_lincomb_batch(LinArgs a, long total, int R, int P, const int32_t *seg)
+{
+    const long t0 = ((long)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) * 64 * kLinElems + (threadIdx.x & 63);
+    double cf[kLinElems][kMaxTerms], v[kLinElems][kMaxTerms];
+#pragma unroll
+    for (int u = 0; u < kLinElems; ++u) {
+        const int c = col_of(min(t0 + 64 * u, total - 1), R, seg);
+#pragma unroll
+        for (int q = 0; q < kMaxTerms; ++q)
+            if (q < a.nt) cf[u][q] = a.coef[q * P + c];
+    }
+#pragma unroll
+    for (int u = 0; u < kLinElems; ++u)
+#pragma unroll
+        for (int q = 0; q < kMaxTerms; ++q) {
+            v[u][q] = 0.0;
+            if (q < a.nt && __ballot(cf[u][q] != 0.0) != 0) v[u][q] = a.in[q][min(t0 + 64 * u, total - 1)];
+        }
+#pragma unroll
+    for (int u = 0; u < kLinElems; ++u)
+        if (t0 + 64 * u < total) lincomb_put(a, t0 + 64 * u, cf[u], v[u]);
 }
 
 // w[:,c] -= sum_{i<nv} h[i][c] * V_i[:,c]   (V_i = V + i*stride); problems
@@ -839,7 +876,11 @@ struct Ctx {
         a.coef = coef.as<double>();
         const long total = n * R;
         if (total == 0) return;
-        hipLaunchKernelGGL(k_lincomb, dim3(blocks_for(total)), dim3(256), 0, st, a, total, R, P, seg);
+        if (seg)
+            hipLaunchKernelGGL(k_lincomb_batch, dim3(blocks_for((total + kLinElems - 1) / kLinElems)), dim3(256), 0, st, a,
+                               total, R, P, seg);
+        else
+            hipLaunchKernelGGL(k_lincomb, dim3(blocks_for(total)), dim3(256), 0, st, a, total, R, P);
         hip_check(hipGetLastError(), "k_lincomb launch");
     }
     void upload_coef(const std::vector<double> &c)
