@@ -134,7 +134,7 @@ typedef struct hec_tune {
                                barrier between levels, the last levels of the system held in
                                an LDS ring (no co-residency needed).  Without a CSR tail, with
                                ELL width 1..8 (the automatic width covers the longest row up
-                               to 8) and at most two values a row older than the ring, a
+                               to 8) and at most four values a row older than the ring, a
                                pipelined kernel of 512 threads loads each level's rows several
                                levels ahead and takes 1 to 16 columns of a system at a time;
                                otherwise block_threads sets the workgroup.

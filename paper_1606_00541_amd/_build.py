@@ -44,7 +44,7 @@ def _hip_units():
             for columns in (1, 4):
                 name = "sq_%s_%s%d" % (t, m, columns)
                 units.append(("sysq_inst.hip", name + ".o",
-                              ["-DHEC_SQ_T=" + typ, "-DHEC_SQ_MODE=%d" % mode, "-DHEC_SQ_C=%d" % columns,
+                              ["-DHEC_SQ_T=" + typ, "-DHEC_SQ_F64=%d" % (t == "f64"), "-DHEC_SQ_MODE=%d" % mode, "-DHEC_SQ_C=%d" % columns,
                                "-DHEC_SQ_NAME=" + name]))
     return units
 

@@ -1033,9 +1033,9 @@ void build_sysq(ExecHost &ex, const Levels &lv, const std::vector<int32_t> &sys,
             for (int32_t p = ex.tail_ptr[x]; p < ex.tail_ptr[x + 1]; ++p) f(ex.tail_col[p]);
     };
     const size_t cap = dev.lds > 0 ? (size_t)dev.lds : 163840;
-    s.sq_cols = std::min(R, kSysqColumns);
     int64_t full_rows = 1;
     const bool dense_far = ex.w < 1 || ex.w > 8 || !ex.tail_ptr.empty();  // not for the pipelined kernel
+    s.sq_cols = std::min(R, kSysqColumns);
     // two rows per thread if at least a quarter of the levels have more rows
     // than the workgroup has threads (overlapping 64^3 subdomains of a 128^3
     // grid, 1 -> 2 rows: 1228 -> 1192 us; always two rows: 256 ILU(1) systems
@@ -1053,7 +1053,7 @@ void build_sysq(ExecHost &ex, const Levels &lv, const std::vector<int32_t> &sys,
         while (wpg * 64 * s.sq_rows[0] < widest && wpg < kSysqThreads / 64) wpg *= 2;
         return kSysqAhead * (kSysqThreads / 64 / wpg);
     };
-    std::vector<int32_t> D(S, 0), W(S, 1);
+    std::vector<int32_t> D(S, 0), W(S, 1), whole(S, 0);
     for (int32_t k = 0; k < S; ++k) {
         for (int32_t l = lvp[k]; l < lvp[k + 1]; ++l) W[k] = std::max(W[k], lvrow[l + 1] - lvrow[l]);
         for (int32_t l = lvp[k]; l < lvp[k + 1]; ++l)
@@ -1072,7 +1072,24 @@ void build_sysq(ExecHost &ex, const Levels &lv, const std::vector<int32_t> &sys,
         const int32_t d = fit(D[k], s.sq_cols);
         int32_t half = d;
         while (half > ahead(W[k]) && ((size_t)(half + 1) * W[k] + 1) * s.sq_cols * ts > cap / 2 - 64) --half;
+        whole[k] = d;
         D[k] = d < D[k] && !dense_far ? half : d;
+    }
+    // most values a row reads beyond the ring; with all of the LDS where half
+    // leaves some rows more than the pipelined kernel takes
+    auto beyond = [&]() {
+        int32_t most = 0;
+        for (int32_t x = 0; x < n; ++x) {
+            int32_t f = 0;
+            each_col(x, [&](int32_t &c) { f += c < n && lev_of[x] - lev_of[c] > D[sys_of[x]]; });
+            most = std::max(most, f);
+        }
+        return most;
+    };
+    int32_t most_far = beyond();
+    if (most_far > kSysqFars && D != whole) {
+        D = whole;
+        most_far = beyond();
     }
     s.sq_full_rows = (int32_t)full_rows;
     s.sq_global = false;
@@ -1106,25 +1123,30 @@ void build_sysq(ExecHost &ex, const Levels &lv, const std::vector<int32_t> &sys,
     s.sq_lds_rows = (int32_t)lds_rows;
     // Rows as records for the pipelined kernel: columns as 16-bit ring rows,
     // padding as the system's zero row.
-    s.sq_packed = !dense_far && lds_rows < (int64_t)kSysqFar1 &&
+    s.sq_packed = !dense_far && lds_rows <= (int64_t)kSysqFar - kSysqFars && most_far <= kSysqFars &&
                   RowRecord(sysq_width(ex.w), ex.ld, (int32_t)ts).bytes() <= (size_t)UINT32_MAX;
     for (int32_t k = 0; k < S; ++k) s.sq_packed = s.sq_packed && (s.sq_ring[2 * k] > 0 || lvp[k] == lvp[k + 1]);
     if (s.sq_packed && s.sq_global) {
-        // at most two older values a row, stored before they are loaded
-        s.sq_far.assign(2 * (size_t)n, n);
+        // the older values of a row, stored before they are loaded
+        s.sq_fars = most_far <= 2 ? 2 : 4;
+        if (s.sq_fars == 4) s.sq_rows[0] = 1;  // as its kernel is built
+        s.sq_far.assign((size_t)s.sq_fars * n, n);
         for (int32_t x = 0; x < n && s.sq_packed; ++x) {
             int32_t f = 0;
             for (int32_t e = 0; e < ex.w; ++e) {
                 const int32_t c = ex.ell_col[(size_t)e * ex.ld + x];
                 if (c >= 0) continue;
-                if (f == 2 || D[sys_of[x]] < ahead(W[sys_of[x]])) {
+                if (D[sys_of[x]] < ahead(W[sys_of[x]])) {
                     s.sq_packed = false;
                     break;
                 }
-                s.sq_far[2 * (size_t)x + f++] = -2 - c;
+                s.sq_far[(size_t)s.sq_fars * x + f++] = -2 - c;
             }
         }
-        if (!s.sq_packed) s.sq_far.clear();
+        if (!s.sq_packed) {
+            s.sq_far.clear();
+            s.sq_fars = 0;
+        }
     }
     if (s.sq_packed) {
         for (int32_t c = 0; c < (s.sq_global ? 1 : kSysqShifts); ++c) {
@@ -1157,7 +1179,7 @@ void build_sysq(ExecHost &ex, const Levels &lv, const std::vector<int32_t> &sys,
             for (int32_t e = 0; e < ex.w; ++e) {
                 int32_t &c = ex.ell_col[(size_t)e * ex.ld + x];
                 if (c == kSqPad) c = zrow;
-                else if (c < 0) c = (int32_t)(f++ == 0 ? kSysqFar0 : kSysqFar1);
+                else if (c < 0) c = (int32_t)kSysqFar - f++;
             }
             s.sq_zero[x] = zrow;
         }

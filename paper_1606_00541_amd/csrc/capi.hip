@@ -184,6 +184,7 @@ void upload_tri(DevTri &d, const TriHost &t, int32_t max_nrhs)
             upload(d.sq_ring, s.sq_ring);
             upload(d.sq_keep, s.sq_keep);
             upload(d.sq_far, s.sq_far);
+            d.sq_fars = s.sq_fars;
             for (int32_t c = 0; c < kSysqShifts; ++c) {
                 upload(d.sq_pcp[c], s.sq_pcp[c]);
                 upload(d.sq_pc[c], s.sq_pc[c]);

@@ -87,6 +87,7 @@ struct TriArgs {
     int32_t ldr, k0;             // right-hand sides of a vector's row, the first of this launch (R: of this launch)
     int32_t cgroups;             // system queue: groups of R columns a system's columns are cut into
     int32_t cshift;              // system queue: log2 of the threads that share an item's row, each with its columns
+    int32_t sq_fars;             // system queue: values beyond the ring a packed row names (0, 2 or 4)
     int32_t rec_chunks, rec_rest;  // system queue: 16-byte chunks and remaining dwords of a packed row (-1: not packed)
     int32_t xw_grouped, bin_grouped;  // system queue: xw / bin hold the groups one after the other
     const int32_t *ell_col;
@@ -125,7 +126,7 @@ struct TriArgs {
     int32_t queue;               // dataflow kernel: workgroups take parts from a counter (epoch[2])
     const int32_t *sq_lvp, *sq_lvrow, *sq_ring;  // system queue: levels per system, level rows, rings
     const int8_t *sq_keep;                        // system queue: rows also stored to xw (read beyond a ring)
-    const int32_t *sq_far;                        // packed rows: the two rows read beyond the ring (n: none)
+    const int32_t *sq_far;                        // packed rows: the sq_fars rows each reads beyond the ring (n: none)
     const int32_t *order;                         // barrier-free kernel: device rows in level order (null: as they are)
 };
 
@@ -152,18 +153,18 @@ LuKernel lu_f32_many(int w);
 // Pipelined system queue by record width: value type and output (_x: the
 // workspace, _d / _f: the caller's FP64 / FP32 vector).
 using SysqKernel = void (*)(TriArgs, const int32_t *, const int4 *, const int32_t *);
-SysqKernel sq_f64_x1(int w, bool in_f64, int rows, bool far);
-SysqKernel sq_f64_x4(int w, bool in_f64, int rows, bool far);
-SysqKernel sq_f64_d1(int w, bool in_f64, int rows, bool far);
-SysqKernel sq_f64_d4(int w, bool in_f64, int rows, bool far);
-SysqKernel sq_f64_f1(int w, bool in_f64, int rows, bool far);
-SysqKernel sq_f64_f4(int w, bool in_f64, int rows, bool far);
-SysqKernel sq_f32_x1(int w, bool in_f64, int rows, bool far);
-SysqKernel sq_f32_x4(int w, bool in_f64, int rows, bool far);
-SysqKernel sq_f32_d1(int w, bool in_f64, int rows, bool far);
-SysqKernel sq_f32_d4(int w, bool in_f64, int rows, bool far);
-SysqKernel sq_f32_f1(int w, bool in_f64, int rows, bool far);
-SysqKernel sq_f32_f4(int w, bool in_f64, int rows, bool far);
+SysqKernel sq_f64_x1(int w, bool in_f64, int rows, int form);
+SysqKernel sq_f64_x4(int w, bool in_f64, int rows, int form);
+SysqKernel sq_f64_d1(int w, bool in_f64, int rows, int form);
+SysqKernel sq_f64_d4(int w, bool in_f64, int rows, int form);
+SysqKernel sq_f64_f1(int w, bool in_f64, int rows, int form);
+SysqKernel sq_f64_f4(int w, bool in_f64, int rows, int form);
+SysqKernel sq_f32_x1(int w, bool in_f64, int rows, int form);
+SysqKernel sq_f32_x4(int w, bool in_f64, int rows, int form);
+SysqKernel sq_f32_d1(int w, bool in_f64, int rows, int form);
+SysqKernel sq_f32_d4(int w, bool in_f64, int rows, int form);
+SysqKernel sq_f32_f1(int w, bool in_f64, int rows, int form);
+SysqKernel sq_f32_f4(int w, bool in_f64, int rows, int form);
 
 // Polls of a bounded device-side wait before it is declared hung (a plan may
 // set its own, tri_plan_set_wait_limit); at most kMaxSpin so that the
@@ -194,6 +195,7 @@ struct DevTri {
     bool sysq = false, sq_global = false;  // system queue kernel; some dependencies read from xw
     bool sq_packed = false;        // rows as records (w: their slots)
     int32_t sq_lds_rows = 0, sq_full_rows = 0, sq_cols = 1, sq_rows[kSysqShifts] = {1, 1, 1};  // as in Schedule
+    int32_t sq_fars = 0;
     double sq_most = 1.0, sq_balance = 1.0;
     DevMem sq_order;               // device rows in level order (empty: not for the barrier-free kernel)
     DevMem sq_lvp, sq_lvrow, sq_ring, sq_keep, sq_far, sq_pcp[kSysqShifts], sq_pc[kSysqShifts];

@@ -3,6 +3,7 @@
 // factorization and C-ABI translation units.
 #pragma once
 
+#include <algorithm>
 #include <cstdint>
 #include <functional>
 #include <string>
@@ -120,7 +121,8 @@ struct Schedule {
     // also laid out for the barrier-free kernel (few right-hand sides): the
     // device rows in level order, and the ELL columns as device rows
     std::vector<int32_t> sq_order, sq_col;
-    std::vector<int32_t> sq_far;     // packed rows: two device rows read beyond the ring (n: none)
+    int32_t sq_fars = 0;             // packed rows: values a row reads beyond the ring at most: 0, 2 or 4
+    std::vector<int32_t> sq_far;     // packed rows: sq_fars device rows each (n: none)
     std::vector<int32_t> sq_zero;    // packed rows: zero row of the row's ring
     std::vector<int8_t> sq_keep;     // rows read back from the global workspace
     int32_t nsteps() const { return (int32_t)step_lanes.size(); }
@@ -188,7 +190,9 @@ constexpr int32_t kDataflowCtlBytes = 16;
 constexpr int32_t kSysqColumns = 4;     // columns of one item of the system queue
 constexpr int32_t kSysqThreads = 512;   // threads of its pipelined kernel
 constexpr int32_t kSysqAhead = 2;       // turns its right-hand sides are loaded ahead
-constexpr uint32_t kSysqFar0 = 0xffff, kSysqFar1 = 0xfffe;  // packed columns: the row's first, second value beyond the ring
+constexpr uint32_t kSysqFar = 0xffff;   // packed columns: this less j for the row's j-th value beyond the ring
+constexpr int32_t kSysqFars = 4;        // values beyond the ring a row may read at most
+constexpr int32_t kSysqShared = 1;      // form of the pipelined kernel: several threads to a row, none beyond the ring
 constexpr uint32_t kSysqDropped = 0xf0000000u;  // byte offset past every output vector of its kernel
 // ELL slots of a row record of the pipelined system queue for ELL width w.
 // Microseconds of one triangle on the barrier-free kernel (levels, then the

@@ -27,8 +27,8 @@ namespace hec {
 // A row's values are computed as in k_level (right-hand side scaled by the
 // reciprocal diagonal, then the ELL slots in order; padding reads the ring's
 // zero row and subtracts 0 * 0), so results are bit-identical to it.
-// FAR: some rows read values older than the ring (at most two each; uneven
-// subdomain cuts give long level distances).  Those are loaded from the
+// FAR: some rows read values older than the ring (at most two or four each;
+// uneven subdomain cuts give long level distances).  Those are loaded from the
 // workspace together with the right-hand sides; the host sized the ring so
 // that they were stored before an earlier barrier by then.
 // Measured (both triangles, FP32 values, before: one item per system, rows
@@ -92,9 +92,13 @@ template <typename T, int C> __device__ __forceinline__ void sq_load(T (&f)[C], 
     }
 }
 
+// FORM: 2 or 4: values beyond the ring a row may read (FAR), kSysqShared: several
+// threads to a row, 0: neither.  (A kernel for both 0 and kSysqShared took a few
+// registers more, which cost rows of six entries their second workgroup on a
+// compute unit: 300 ILU(1) subdomains in FP32, one right-hand side 98 -> 119 us.)
 // MODE 0: results to the workspace xw in device order, 1 / 2: to the caller's
 // FP64 / FP32 vector through `scatter` (negative: not stored).
-template <typename T, typename TIn, int W, int C, int M, int MODE, bool FAR>
+template <typename T, typename TIn, int W, int C, int M, int MODE, int FORM>
 __global__ void __launch_bounds__(512) k_sysq_pipe(TriArgs a, const int32_t *__restrict__ pcp,
                                                    const int4 *__restrict__ pc,
                                                    const int32_t *__restrict__ rings)
@@ -102,7 +106,9 @@ __global__ void __launch_bounds__(512) k_sysq_pipe(TriArgs a, const int32_t *__r
     using Rec = RowRec<T, W>;
     constexpr int P = 4, H = kSysqAhead;
     constexpr unsigned RB = C * sizeof(T);  // a thread's bytes of a ring row
-    const int cs = FAR ? 0 : a.cshift;
+    constexpr bool SHARED = FORM == kSysqShared;
+    constexpr int FAR = FORM == kSysqShared ? 0 : FORM;
+    const int cs = SHARED ? a.cshift : 0;
     const unsigned rowb = RB << cs;
     extern __shared__ __align__(16) unsigned char smem[];
     int *s_q = reinterpret_cast<int *>(smem + a.lds_ctl);
@@ -124,8 +130,8 @@ __global__ void __launch_bounds__(512) k_sysq_pipe(TriArgs a, const int32_t *__r
         int gi[M], dst[M];      // gather and scatter indices
         T di[M];
         TIn b[M][C];
-        int fi[M][2], keep[M];  // rows read beyond the ring; read back itself
-        T f[M][2][C];
+        int fi[M][FAR > 0 ? FAR : 1], keep[M];  // rows read beyond the ring; read back itself
+        T f[M][FAR > 0 ? FAR : 1][C];
         int4 pc;                // the piece: first row, rows, first ring row
     };
     Row S[P];
@@ -195,12 +201,19 @@ __global__ void __launch_bounds__(512) k_sysq_pipe(TriArgs a, const int32_t *__r
                 row_load<T, W>(u.d[m], rrec, ld, 0u, Rec::CH * ld * 16u, x * 16u);
                 u.gi[m] = a.gather[x];
                 if (MODE != 0) u.dst[m] = a.scatter[x];
-                if constexpr (FAR) {
+                if constexpr (FAR == 2) {
                     const int2 f = reinterpret_cast<const int2 *>(a.sq_far)[x];
                     u.fi[m][0] = f.x;
                     u.fi[m][1] = f.y;
-                    if (MODE != 0) u.keep[m] = a.sq_keep[x];
                 }
+                if constexpr (FAR == 4) {
+                    const int4 f = reinterpret_cast<const int4 *>(a.sq_far)[x];
+                    u.fi[m][0] = f.x;
+                    u.fi[m][1] = f.y;
+                    u.fi[m][2] = f.z;
+                    u.fi[m][3] = f.w;
+                }
+                if (FAR && MODE != 0) u.keep[m] = a.sq_keep[x];
                 u.di[m] = (scaled ? static_cast<const T *>(a.dinv) : static_cast<const T *>(a.ell_val))[x];
             }
         };
@@ -212,7 +225,7 @@ __global__ void __launch_bounds__(512) k_sysq_pipe(TriArgs a, const int32_t *__r
                 for (int c = 0; c < C; ++c) u.b[m][c] = src[c];
                 if constexpr (FAR) {
 #pragma unroll
-                    for (int j = 0; j < 2; ++j)
+                    for (int j = 0; j < FAR; ++j)
                         sq_load(u.f[m][j], rxw, (unsigned)u.fi[m][j] * ldx * (unsigned)sizeof(T));
                 }
             }
@@ -228,15 +241,16 @@ __global__ void __launch_bounds__(512) k_sysq_pipe(TriArgs a, const int32_t *__r
 #pragma unroll
             for (int e = 0; e < W; ++e) {
                 unsigned o;
-                if constexpr (FAR) o = row_off<T, W, RB>(u.d[m], e);
-                else o = row_off<T, W>(u.d[m], e, rowb, kb);
+                if constexpr (SHARED) o = row_off<T, W>(u.d[m], e, rowb, kb);
+                else o = row_off<T, W, RB>(u.d[m], e);
                 const T v = row_val<T, W>(u.d[m], e);
-                const bool far = FAR && o >= kSysqFar1 * RB, first = o == kSysqFar0 * RB;
+                const unsigned code = o;
                 if (FAR) o = min(o, zoff);
 #pragma unroll
                 for (int c = 0; c < C; ++c) {
                     T dep = *(LdsPtr<T>)(uintptr_t)(o + c * (unsigned)sizeof(T));
-                    if (FAR) dep = far ? (first ? u.f[m][0][c] : u.f[m][1][c]) : dep;
+#pragma unroll
+                    for (int j = 0; j < FAR; ++j) dep = code == (kSysqFar - (unsigned)j) * RB ? u.f[m][j][c] : dep;
                     s[c] -= v * dep;
                 }
             }

@@ -7,11 +7,11 @@ namespace hec {
 
 namespace {
 
-template <typename TIn, int M, bool FAR> SysqKernel by_width(int w)
+template <typename TIn, int M, int FORM> SysqKernel by_width(int w)
 {
     switch (w) {
 #define HEC_SQ_CASE(W) \
-    case W: return k_sysq_pipe<HEC_SQ_T, TIn, W, HEC_SQ_C, M, HEC_SQ_MODE, FAR>;
+    case W: return k_sysq_pipe<HEC_SQ_T, TIn, W, HEC_SQ_C, M, HEC_SQ_MODE, FORM>;
         HEC_SQ_CASE(2)
         HEC_SQ_CASE(3)
         HEC_SQ_CASE(4)
@@ -21,18 +21,40 @@ template <typename TIn, int M, bool FAR> SysqKernel by_width(int w)
     default: return nullptr;
     }
 }
-
-template <typename TIn> SysqKernel by_rows(int w, int rows, bool far)
+// four values beyond the ring: rows of three entries or more, one row a thread
+// (two, or four columns in FP64, would spill most of their registers)
+template <typename TIn> SysqKernel by_width_far4(int w)
 {
-    if (rows == 1) return far ? by_width<TIn, 1, true>(w) : by_width<TIn, 1, false>(w);
-    return far ? by_width<TIn, 2, true>(w) : by_width<TIn, 2, false>(w);
+#if HEC_SQ_C == 1 || !HEC_SQ_F64
+    switch (w) {
+#define HEC_SQ_CASE(W) \
+    case W: return k_sysq_pipe<HEC_SQ_T, TIn, W, HEC_SQ_C, 1, HEC_SQ_MODE, 4>;
+        HEC_SQ_CASE(3)
+        HEC_SQ_CASE(4)
+        HEC_SQ_CASE(6)
+        HEC_SQ_CASE(8)
+#undef HEC_SQ_CASE
+    default: break;
+    }
+#endif
+    return nullptr;
+}
+
+template <typename TIn> SysqKernel by_form(int w, int rows, int form)
+{
+    switch (form) {
+    case 0: return rows == 1 ? by_width<TIn, 1, 0>(w) : by_width<TIn, 2, 0>(w);
+    case kSysqShared: return rows == 1 ? by_width<TIn, 1, kSysqShared>(w) : by_width<TIn, 2, kSysqShared>(w);
+    case 2: return rows == 1 ? by_width<TIn, 1, 2>(w) : by_width<TIn, 2, 2>(w);
+    default: return by_width_far4<TIn>(w);
+    }
 }
 
 }  // namespace
 
-SysqKernel HEC_SQ_NAME(int w, bool in_f64, int rows, bool far)
+SysqKernel HEC_SQ_NAME(int w, bool in_f64, int rows, int form)
 {
-    return in_f64 ? by_rows<double>(w, rows, far) : by_rows<float>(w, rows, far);
+    return in_f64 ? by_form<double>(w, rows, form) : by_form<float>(w, rows, form);
 }
 
 }  // namespace hec

@@ -904,7 +904,9 @@ __global__ void __launch_bounds__(256) k_syncfree(TriArgs a, int waves)
 // 0 * 0), so results are bit-identical to it.
 // With several right-hand sides an item of the queue is a system and a group
 // of at most a.R of its columns (see k_sysq_pipe).
-template <typename T, typename TIn, typename TOut>
+// PACKED: rows as records (vectors beyond the pipelined kernel's offsets); a
+// test of it per entry instead took 2 to 4% more.
+template <typename T, typename TIn, typename TOut, bool PACKED>
 __global__ void __launch_bounds__(1024) k_sysq(TriArgs a)
 {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -941,11 +943,11 @@ __global__ void __launch_bounds__(1024) k_sysq(TriArgs a)
                 for (int e = 0; e < a.w; ++e) {
                     int c;
                     T v;
-                    if (a.rec_chunks >= 0) {  // packed rows
+                    if constexpr (PACKED) {
                         const unsigned char *p = static_cast<const unsigned char *>(a.ell_val);
                         v = *reinterpret_cast<const T *>(rec_dword(a, p, x, e * (int)(sizeof(T) / 4)));
                         c = reinterpret_cast<const uint16_t *>(rec_dword(a, p, x, a.w * (int)(sizeof(T) / 4) + e / 2))[e & 1];
-                        if (a.sq_far && c >= (int)kSysqFar1) c = -2 - a.sq_far[2 * (size_t)x + (c == (int)kSysqFar1 ? 1 : 0)];
+                        if (c > (int)kSysqFar - a.sq_fars) c = -2 - a.sq_far[(size_t)a.sq_fars * x + ((int)kSysqFar - c)];
                     } else {
                         c = a.ell_col[(size_t)e * a.ld + x];
                         v = ev[(size_t)e * a.ld + x];
@@ -994,8 +996,8 @@ __global__ void __launch_bounds__(256) k_fill_sentinel(T *p, size_t count, unsig
     if (counter && i == 0) *counter = 0u;  // the next launch's chunk counter
 }
 
-// Columns of one item of the system queue: those the rings were sized for, or
-// fewer right-hand sides if the call has fewer.
+// Columns of one item of the system queue without packed rows: those the rings
+// were sized for, or fewer right-hand sides if the call has fewer.
 int32_t sysq_columns(const DevTri &d, int32_t R)
 {
     const size_t row = (size_t)std::max(1, d.sq_lds_rows) * (d.dt == HEC_F64 ? 8 : 4);
@@ -1053,6 +1055,7 @@ SysqItem sysq_pipe_item(const DevTri &d, int32_t R, hipStream_t st)
     for (int32_t columns : {1, kSysqColumns})
         for (int32_t shift = 0; shift < (d.sq_global ? 1 : kSysqShifts); ++shift) {
             const int32_t all = columns << shift;
+            if (columns > 1 && f64 && d.sq_fars == 4) continue;  // not built
             if (R % all != 0 || (size_t)std::max(1, d.sq_lds_rows) * all * (f64 ? 8 : 4) + 32 > (size_t)device_max_lds())
                 continue;
             const double cost = (columns == 1 ? 1.0 : four[f64]) * threads[f64][shift];
@@ -1078,12 +1081,12 @@ SysqItem sysq_pipe_item(const DevTri &d, int32_t R, hipStream_t st)
 
 SysqKernel sysq_pipe_kernel(const DevTri &d, const TriArgs &a, int32_t columns, int32_t shift)
 {
-    const bool in = a.in_f64 != 0, far = d.sq_global, f64 = d.dt == HEC_F64;
+    const bool in = a.in_f64 != 0, f64 = d.dt == HEC_F64;
     const int out = !a.xout ? 0 : (a.out_f64 ? 1 : 2);
-    using Select = SysqKernel (*)(int, bool, int, bool);
+    using Select = SysqKernel (*)(int, bool, int, int);
     static constexpr Select one[2][3] = {{sq_f32_x1, sq_f32_d1, sq_f32_f1}, {sq_f64_x1, sq_f64_d1, sq_f64_f1}};
     static constexpr Select four[2][3] = {{sq_f32_x4, sq_f32_d4, sq_f32_f4}, {sq_f64_x4, sq_f64_d4, sq_f64_f4}};
-    return (columns == 1 ? one : four)[f64][out](d.w, in, d.sq_rows[shift], far);
+    return (columns == 1 ? one : four)[f64][out](d.w, in, d.sq_rows[shift], shift > 0 ? kSysqShared : d.sq_fars);
 }
 
 // Right-hand sides one launch of a dataflow plan holds.
@@ -1223,10 +1226,11 @@ void launch_typed(DevTri &d, TriArgs a, hipStream_t st)
             return;
         }
         const int block = std::max(64, std::min(1024, d.block));
-        const int32_t cap = capacity_of((const void *)k_sysq<T, TIn, TOut>, block, lds);
+        auto k = d.sq_packed ? k_sysq<T, TIn, TOut, true> : k_sysq<T, TIn, TOut, false>;
+        const int32_t cap = capacity_of((const void *)k, block, lds);
         if (d.sq_global) a.write_xw = 1;  // dependencies beyond the ring are read back from xw
         const int grid = std::max(1, std::min(items, cap));
-        hipLaunchKernelGGL((k_sysq<T, TIn, TOut>), dim3(grid), dim3(block), lds, st, a);
+        hipLaunchKernelGGL(k, dim3(grid), dim3(block), lds, st, a);
         hip_check(hipGetLastError(), "k_sysq launch");
         return;
     }
@@ -1447,6 +1451,7 @@ TriArgs tri_args(const DevTri &d, const void *bin, hec_dtype_t in_dt, const int3
     a.sq_ring = d.sq_ring.as<int32_t>();
     a.sq_keep = d.sq_keep.as<int8_t>();
     a.sq_far = d.sq_far.as<int32_t>();
+    a.sq_fars = d.sq_fars;
     a.rec_chunks = -1;
     if (d.sysq && d.sq_packed) {
         const RowRecord rec(d.w, d.ld, d.dt == HEC_F64 ? 8 : 4);

@@ -239,3 +239,76 @@ def test_few_columns_cost_what_the_barrier_free_kernel_takes():
             laps.append(a.elapsed_time(b))
         times.append(min(laps))
     assert times[1] < 1.1 * times[0], times
+
+
+@pytest.mark.parametrize("nrhs", [1, 4, 5, 16])
+@pytest.mark.parametrize("dt", ["f64", "f32"])
+def test_rows_that_read_more_than_two_values_beyond_the_ring(dt, nrhs):
+    # ILU(1) of thin slabs: up to four such values a row
+    import synth
+
+    A = synth.poisson3d(40, 40, 80)
+    owner = ((np.arange(A.n) * 130) // A.n).astype(np.int32)
+    r = torch.from_numpy(np.random.default_rng(nrhs).standard_normal((A.n, nrhs))).cuda()
+    out = []
+    for t in (dict(schedule="level_launch"), dict(QUEUE, max_nrhs=max(4, nrhs))):
+        s = H.ras_setup_ilu(A, 130, owner, overlap=1, kind="iluk", k=1, factor_dtype=dt, tune=H.tune_default(**t))
+        z = torch.full_like(r, float("nan"))
+        for _ in range(2):
+            H.ras_apply(s, r, z)
+        torch.cuda.synchronize()
+        out.append(z)
+    assert torch.equal(out[0], out[1])
+
+
+def far_systems(m, nlev, backs):
+    """Systems of levels of m rows that read the row above and one row from each
+    of `backs` levels away."""
+    rows = []
+    for i in range(m * nlev):
+        c = {i - m} | {i - m * b for b in backs}
+        rows.append(sorted(j for j in c if j >= 0) + [i])
+    rp = np.cumsum([0] + [len(q) for q in rows]).astype(np.int32)
+    ci = np.concatenate([np.asarray(q) for q in rows]).astype(np.int32)
+    v = np.random.default_rng(m).uniform(-0.2, 0.2, ci.size)
+    v[rp[1:] - 1] = 1.5
+    return CSR(m * nlev, rp, ci, v)
+
+
+@pytest.mark.parametrize("dt", ["f64", "f32"])
+@pytest.mark.parametrize("backs", [(90,), (88, 90), (80, 88, 90), (70, 80, 88, 90), (60, 70, 80, 88, 90)])
+def test_one_to_five_values_beyond_the_ring(backs, dt):
+    # levels of 300 rows: FP64 rings of four columns hold 17 levels, FP32 34
+    L = far_systems(300, 120, backs)
+    for nrhs in (1, 4, 8):
+        b = torch.from_numpy(np.random.default_rng(nrhs).standard_normal((L.n, nrhs))).cuda()
+        out = []
+        for t in (dict(schedule="level_launch"), dict(QUEUE, max_nrhs=nrhs)):
+            p = H.tri_analyze(L, "lower", dtype=dt, tune=H.tune_default(**t))
+            x = torch.full_like(b, float("nan"))
+            for _ in range(2):
+                H.tri_solve_lower(p, b, x)
+            torch.cuda.synchronize()
+            out.append(x)
+        assert torch.equal(out[0], out[1]), nrhs
+
+
+def test_four_values_beyond_the_ring_stay_on_the_pipelined_kernel():
+    # the plain kernel takes about eight times as long as this one
+    times = []
+    for backs in ((88, 90), (70, 80, 88, 90)):
+        L = far_systems(300, 120, backs)
+        p = H.tri_analyze(L, "lower", dtype="f32", tune=H.tune_default(**dict(QUEUE, max_nrhs=4)))
+        b = torch.zeros(L.n, 4, dtype=torch.float64, device="cuda")
+        x = torch.empty_like(b)
+        laps = []
+        for _ in range(6):
+            e = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e[0].record()
+            for _ in range(5):
+                H.tri_solve_lower(p, b, x)
+            e[1].record()
+            e[1].synchronize()
+            laps.append(e[0].elapsed_time(e[1]))
+        times.append(min(laps))
+    assert times[1] < 2.5 * times[0], times
