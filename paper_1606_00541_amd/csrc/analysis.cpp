@@ -784,7 +784,7 @@ std::vector<int32_t> queue_parts(const Csr &a, bool upper, const Levels &lv, con
 // Parts of the dataflow kernel under the automatic schedule.  Every handoff
 // between workgroups on a dependency chain costs about ten steps inside one,
 // so a small problem is faster on few workgroups: a 64^2 ILU(0) application
-// takes 109 us on 256 parts (30 handoffs a triangle) and 39 us on one; 32^3
+// takes 109 us on 256 parts (30 handoffs a triangle) and 39 us on one or two; 32^3
 // 88 us on 256 and 50 us on 8; an irregular triangle of 20011 rows 816 us on
 // 256 and 258 us on 4.  Larger parts also hold more rows of a level, which a
 // wavefront solves 64 at a time, and take longer to fill.  The estimate walks
@@ -995,9 +995,11 @@ int32_t block_parts(int32_t n, const std::vector<int32_t> &ptr, int32_t P, std::
     return g + 1;
 }
 
-// Above this many rows only the full set of parts is considered: the LDS
-// leaves at most a factor of two, worth a few percent (1000^2 ILU(0) 437 us
-// on 128 parts, 460 on 256), and the estimate would cost setup time.
+// Above this many rows only the full set of parts is considered, for the setup
+// time: a walk of the estimate takes some 15 ms per half a million rows of three
+// entries (ten times that for the longer rows of ILUT).  In FP64 with one
+// right-hand side the LDS leaves a factor of two there, worth a few percent
+// (1000^2 ILU(0) 437 us on 128 parts, 460 on 256); FP32 leaves more, not used.
 constexpr int32_t kEstimateRows = 500000;
 
 // System queue: every column becomes a row of its system's LDS ring, which
@@ -1377,27 +1379,17 @@ void build_exec(TriHost &t, const Csr &a, const Tune &tune, const DeviceShape &d
             double best = INFINITY;
             int32_t best_parts = 0;
             PartCut cut(a, t.upper, lv, df_waves, w0, R);
-            // twice the parts make more handoffs and smaller parts: a shape
-            // that loses twice in a row is not cut further
-            enum { kBlocks, kGrid, kContiguous };
-            int32_t left[3] = {2, 2, 2};
-            bool doubled = false;
-            auto consider = [&](int shape, std::vector<int32_t> &&po, int32_t count) {
+            auto consider = [&](std::vector<int32_t> &&po, int32_t count) {
                 if (count < 1 || count > parts) return;
-                if (doubled) left[shape] -= 1;
                 cut.set(po, count);
                 if (cut.least() >= best) return;
                 // parts that fill most of the LDS: their imports come first
                 const bool tight = 2 * (size_t)cut.largest() * R * ts > lds_cap - lds_cap / 8;
                 if (tight) cut.lists();
-                if (tight && !fits(cut)) {
-                    if (doubled) left[shape] += 1;  // says nothing about its time
-                    return;
-                }
+                if (tight && !fits(cut)) return;
                 const double us = cut.time(best);
                 if (us == INFINITY) return;
                 cut.lists();
-                left[shape] = 2;
                 if (!fits(cut) || !weighed(po, count, cut)) return;
                 best = us;
                 best_parts = count;
@@ -1413,13 +1405,12 @@ void build_exec(TriHost &t, const Csr &a, const Tune &tune, const DeviceShape &d
             if (8 * p2 >= parts) counts.push_back(parts);
             std::vector<int32_t> po;
             for (int32_t c : counts) {
-                doubled = c >= p2;
-                if (blocks && left[kBlocks] > 0) {
+                if (blocks) {
                     const int32_t k = block_parts(n, *sys_ptr, c, po);
-                    consider(kBlocks, std::move(po), k);
+                    consider(std::move(po), k);
                 }
-                if (grid && left[kGrid] > 0) consider(kGrid, grid_parts(n, gx, gy, gz, c), c);
-                if (left[kContiguous] > 0) consider(kContiguous, contiguous(c), c);
+                if (grid) consider(grid_parts(n, gx, gy, gz, c), c);
+                consider(contiguous(c), c);
             }
             if (best_parts == 0) {
                 // imports can outweigh the rows (16 entries a row anywhere
@@ -1579,7 +1570,7 @@ void build_exec(TriHost &t, const Csr &a, const Tune &tune, const DeviceShape &d
         fail(HEC_ERR_CAPACITY, "dataflow kernel: ELL part beyond 4 GiB (32-bit buffer offsets)");
     if (want_df && tune.block_threads > dataflow_max_block(w) - 128)
         fail(HEC_ERR_CAPACITY, "dataflow kernel: block_threads above " + std::to_string(dataflow_max_block(w) - 128) +
-                                   " for ELL width " + std::to_string(w) + " (two more wavefronts are added)");
+                                   " for ELL width " + std::to_string(w) + " (two or three more wavefronts are added)");
     if (kind == HEC_SCHED_OWNER_PERSISTENT) {
         const int32_t piece = want_df ? std::max(1, 64 / R) : tune.chunk_rows;
         if (piece <= 0) fail(HEC_ERR_INVALID_ARG, "internal: chunk_rows must be positive");
