@@ -130,19 +130,24 @@ __device__ __forceinline__ void df_copy_ints(int *dst, const int32_t *src, int c
     }
 }
 
-// Empty this workgroup's share of the mailbox half the next launch reads: the
-// slots of part g, whose values it will write then (those that other
-// workgroups had emptied took longer to arrive: 20011 irregular rows 224 ->
-// 230 us), or, where parts are taken from a queue, of all slots.  Every
-// workgroup does it before its first wait, for all plans of the launch: a
-// launch whose waits give up still advances the epochs, so a slot left out
+// Empty slots of the mailbox half the next launch reads: those of this
+// workgroup's part (those that other workgroups had emptied took longer to
+// arrive: 20011 irregular rows 228 -> 230 us), by the first group of columns
+// for all of them.  Every launch does it before its first wait, for all its
+// plans: one whose waits give up still advances the epochs, so a slot left out
 // would offer the next launch the value of the one before.
-template <typename T> __device__ __forceinline__ void df_clear(const TriArgs &a, int g, T *other)
+template <typename T> __device__ __forceinline__ void df_clear(const TriArgs &a, int e0, int nex, T *other)
 {
-    const size_t m0 = a.queue ? 0 : (size_t)a.exp_ptr[g] * a.mbox_stride;
-    const size_t m1 = (size_t)(a.queue ? a.nexp : a.exp_ptr[g + 1]) * a.mbox_stride;
-    const size_t share = a.queue ? blockIdx.x : blockIdx.y, shares = a.queue ? gridDim.x : gridDim.y;
-    for (size_t i = m0 + share * blockDim.x + threadIdx.x; i < m1; i += shares * blockDim.x) other[i] = sentinel<T>();
+    if (blockIdx.y != 0) return;
+    const size_t m0 = (size_t)e0 * a.mbox_stride, m1 = (size_t)(e0 + nex) * a.mbox_stride;
+    for (size_t i = m0 + threadIdx.x; i < m1; i += blockDim.x) other[i] = sentinel<T>();
+}
+// The same for parts taken from a queue: every workgroup a share of all slots,
+// also of the parts that no workgroup comes to when waits give up.
+template <typename T> __device__ __forceinline__ void df_clear_share(const TriArgs &a, T *other)
+{
+    const size_t count = (size_t)a.nexp * a.mbox_stride, step = (size_t)gridDim.x * blockDim.x;
+    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < count; i += step) other[i] = sentinel<T>();
 }
 
 // Everything but the right-hand side: sentinels, the zero row and index lists.
@@ -416,6 +421,11 @@ __device__ __forceinline__ void df_sweep(const TriArgs &a, const DfPart<T> &pt, 
             offsets(S[0]);
             read(on);
             const int rounds = (jend - j) / K, rest = (jend - j) - K * rounds;
+            // the loop's place in the instruction stream, which a change of the
+            // code before it moves: by four bytes the same steps of 20011
+            // irregular rows, two right-hand sides, took 222 to 232 us (at 64
+            // bytes plus 0, 4, 8 and 12: 224.7, 224.4, 229.4, 228.2)
+            asm volatile(".p2align 6\n\ts_nop 0");
             for (int q = 0; q < rounds; ++q) {
 #pragma unroll
                 for (int p = 0; p < K; ++p) step(p, true);
@@ -533,17 +543,15 @@ __global__ void __launch_bounds__(512) k_dataflow(TriArgs a)
             break;
         }
         const int g = a.queue ? ctl->part : (int)blockIdx.x;
-        if (g >= a.nparts) {
-            if (round == 0) df_clear(a, 0, other);  // queue: no part left for it
-            break;
-        }
+        if (a.queue && round == 0) df_clear_share(a, other);
+        if (g >= a.nparts) break;
         const DfPart<T> pt = df_part<T>(a, g, k0, R, smem);
         unsigned long long t_fill = 0;
         df_sweep<T, W, TAIL, R1, TRACE>(a, pt, R, mrd, &ctl->abort, t_fill, [&]() {
             if (a.in_f64) df_fill_b<T, UNIT, R1>(a, pt, R, static_cast<const double *>(a.bin));
             else df_fill_b<T, UNIT, R1>(a, pt, R, static_cast<const float *>(a.bin));
             df_fill_lists(a, pt, R);
-            if (round == 0) df_clear(a, g, other);
+            if (!a.queue) df_clear(a, pt.e0, pt.nex, other);
         });
         const unsigned long long t_done = TRACE ? __builtin_amdgcn_s_memrealtime() : 0ull;
         df_report(a, ctl);
@@ -599,6 +607,7 @@ __global__ void __launch_bounds__(512) k_dataflow_lu(TriArgs l, TriArgs u)
     extern __shared__ __align__(16) unsigned char smem[];
     DfCtl *ctl = reinterpret_cast<DfCtl *>(smem + l.lds_ctl);
     const int k0 = l.k0 + (int)blockIdx.y * l.R, R = R1 ? 1 : min(l.R, l.ldr - k0), g = blockIdx.x;
+    const int ue0 = u.exp_ptr[g], ue1 = u.exp_ptr[g + 1];  // on their way with the epochs
     if (threadIdx.x == 0) {
         ctl->epoch = __hip_atomic_load(l.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         ctl->epoch2 = __hip_atomic_load(u.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -614,8 +623,8 @@ __global__ void __launch_bounds__(512) k_dataflow_lu(TriArgs l, TriArgs u)
         if (l.in_f64) df_fill_b<T, true, R1>(l, pl, R, static_cast<const double *>(l.bin));
         else df_fill_b<T, true, R1>(l, pl, R, static_cast<const float *>(l.bin));
         df_fill_lists(l, pl, R);
-        df_clear(l, g, half(l, ctl->epoch + 1u));
-        df_clear(u, g, half(u, ctl->epoch2 + 1u));
+        df_clear(l, pl.e0, pl.nex, half(l, ctl->epoch + 1u));
+        df_clear(u, ue0, ue1 - ue0, half(u, ctl->epoch2 + 1u));
     });
     if (!ctl->abort) {
         const DfPart<T> pu = df_part<T>(u, g, k0, R, smem);

@@ -187,7 +187,7 @@ struct DevTri {
     DevMem imp_ptr, imp_slot, exp_row, wave_ptr, step_pack;
     DevMem seg;                    // device row -> independent system (batches; empty: one system)
     const int8_t *act = nullptr;   // per-launch: active (system, rhs) problems; others may be skipped
-    int32_t df_waves = 0;          // compute wavefronts per group (block = 64 * df_waves + 128)
+    int32_t df_waves = 0;          // compute wavefronts per group (block: 64 * (df_waves + 1 + import wavefronts), see launch_dataflow)
     int32_t df_rows = 0, df_ints = 0;
     int32_t df_step_rows = 0;      // longest step (one wavefront covers step rows x nrhs)
     int32_t df_accept = 0;         // right-hand sides taken in groups of columns
