@@ -189,25 +189,42 @@ def _tune(H, args, **kw):
     return H.tune_default(schedule=sched, kernel_variant=args.kernel_variant, **kw)
 
 
+def _one_launch(H, pl, pu):
+    """Whether both triangles of an application run in one dataflow launch:
+    parts of the same rows, one ELL width, no CSR tail."""
+    import numpy as np
+
+    st = [H.tri_plan_stats(p) for p in (pl, pu)]
+    if not all(q["dataflow"] and not q["queue"] and q["nnz_tail"] == 0 for q in st):
+        return False
+    own = []
+    for p in (pl, pu):
+        rows, owner = H.tri_plan_layout(p)
+        own.append(np.empty_like(owner))
+        own[-1][rows] = owner
+    return (st[0]["ell_width"] == st[1]["ell_width"] and st[0]["num_groups"] == st[1]["num_groups"]
+            and bool(np.array_equal(own[0], own[1])))
+
+
 def _kernel_name(st):
     """The kernel a plan runs (from tri_plan_stats)."""
     if st["dataflow"]:
-        return "k_dataflow" + (" (part queue)" if st.get("queue") else "")
+        return "k_dataflow_lu" if st.get("one_launch") else "k_dataflow" + (" (part queue)" if st.get("queue") else "")
     if st["syncfree"]:
         return "k_syncfree"
     if st["sysq"]:
-        # the pipelined system queue: no CSR tail, ELL width 1..8, RHS in
-        # groups of 4 or 8; otherwise the plain system queue
-        R = st.get("nrhs", 0)
-        ok = st["nnz_tail"] == 0 and 1 <= st["ell_width"] <= 8 and R % 4 == 0
+        # the pipelined system queue: no CSR tail, ELL width 1..8; otherwise
+        # the plain system queue
+        ok = st["nnz_tail"] == 0 and 1 <= st["ell_width"] <= 8
         return "k_sysq_pipe" if ok else "k_sysq"
     return "k_level" if st["schedule"] == 1 else "k_persistent"
 
 
 def _roofline(st, bytes_per_apply, ms):
-    """Roofline of the dominant kernel: the L and U launches share it, so its
-    average launch moves half the counted bytes in half the application."""
-    launches = st["nlev"] * 2 if (st["schedule"] == 1 and not st["syncfree"]) else 2
+    """Roofline of the dominant kernel: one launch for both triangles, or the L
+    and U launches share it, so that its average launch moves half the counted
+    bytes in half the application."""
+    launches = st["nlev"] * 2 if (st["schedule"] == 1 and not st["syncfree"]) else 1 if st.get("one_launch") else 2
     per_launch = bytes_per_apply / launches
     achieved = per_launch / (ms / launches * 1e-3) / 1e9
     return {"bound": "hbm", "kernel": _kernel_name(st), "achieved": round(achieved, 2), "peak": HBM_PEAK_GBS,
@@ -291,7 +308,7 @@ def _cfg3(H, torch, np, synth, args):
         _log("config 3: timing applies (%s)" % fdt)
         ms = _time_apply(H, torch, f, b, z, args.steps, args.warmup)
         row = {"apply_ms": round(ms, 4), "apply_GBps": round(B / (ms * 1e-3) / 1e9, 3),
-               "counted_bytes_per_apply": int(B), "roofline": _roofline(stl, B, ms),
+               "counted_bytes_per_apply": int(B), "roofline": _roofline(dict(stl, one_launch=_one_launch(H, pl, pu)), B, ms),
                "nlev_L": stl["nlev"], "nlev_U": stu["nlev"], "nnz_offdiag_L": stl["nnz_offdiag"],
                "nnz_offdiag_U": stu["nnz_offdiag"], "ell_width_L": stl["ell_width"],
                "nnz_tail_L": stl["nnz_tail"], "setup_s": round(setup, 3)}
@@ -347,7 +364,7 @@ def _cfg4(H, torch, np, synth, args):
     out = {"workload": "RAS on 128^3 Poisson (n=2097152): 64 seeded contiguous subdomains (8192..61440 rows), "
                        "overlap 1, ILU(0) per subdomain in FP32, 16 RHS; FP64 BiCGSTAB to 1e-10",
            "apply_ms": round(ms, 4), "apply_GBps": round(B / (ms * 1e-3) / 1e9, 3), "counted_bytes_per_apply": int(B),
-           "solves_per_s": round(1000.0 * R / ms, 2), "roofline": _roofline(dict(stl, nrhs=R), B, ms),
+           "solves_per_s": round(1000.0 * R / ms, 2), "roofline": _roofline(dict(stl, one_launch=_one_launch(H, pl, pu)), B, ms),
            "extended_rows": int(tot), "nlev_L": stl["nlev"], "nlev_U": stu["nlev"], "setup_s": round(setup, 3),
            "parts_L": stl["num_groups"]}
     zg = torch.empty_like(r)
@@ -410,7 +427,7 @@ def _cfg5(H, torch, np, synth, args):
         reps = max(5, args.steps // 2)
         ms = _time_apply(H, torch, f, b, z, reps, 2)
         row = {"apply_ms": round(ms, 4), "apply_GBps": round(B / (ms * 1e-3) / 1e9, 3),
-               "counted_bytes_per_apply": int(B), "roofline": _roofline(dict(stl, nrhs=R), B, ms),
+               "counted_bytes_per_apply": int(B), "roofline": _roofline(dict(stl, one_launch=_one_launch(H, pl, pu)), B, ms),
                "solves_per_s": round(1000.0 * len(mats) * R / ms, 1),
                "nlev_L": stl["nlev"], "nlev_U": stu["nlev"], "setup_s": round(setup, 3), "parts_L": stl["num_groups"]}
         zg = torch.empty_like(b)
@@ -696,7 +713,8 @@ def main(argv=None):
     if not args.timed_loop_only:
         refac, refac_first, refac_same, reps, reps_cold = _extras(H, torch, np, f, A, r, z, stream, args)
 
-    # dominant kernel: the triangular-solve kernel; L and U launches share it
+    # dominant kernel: the triangular-solve kernel, one launch for both
+    # triangles or one that the L and U launches share
     bl = per_launch_bytes(n, stl["nnz_offdiag"], 1, diag=False)
     bu = per_launch_bytes(n, stu["nnz_offdiag"], 1, diag=True)
     if stl["syncfree"] and stu["syncfree"]:
@@ -706,8 +724,9 @@ def main(argv=None):
         kname, tag = "k_level", "launch"
         launches = stl["nlev"] + stu["nlev"]
     elif stl["dataflow"] and stu["dataflow"]:
-        kname, tag = "k_dataflow", "dataflow"
-        launches = 2
+        one = _one_launch(H, pl, pu)
+        kname, tag = "k_dataflow_lu" if one else "k_dataflow", "dataflow"
+        launches = 1 if one else 2
     elif stl["schedule"] == 3 and stl["nnz_tail"] == 0 and stu["nnz_tail"] == 0:
         kname, tag = "k_owner", "owner"
         launches = 2

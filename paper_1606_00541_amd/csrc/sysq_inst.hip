@@ -1,5 +1,6 @@
 // Instances of the pipelined system queue for one value type (HEC_SQ_T),
-// columns of an item (HEC_SQ_C) and output (HEC_SQ_MODE); HEC_SQ_NAME is the selector.  Compiled once per
+// columns of a thread (HEC_SQ_C) and output (HEC_SQ_MODE; HEC_SQ_F64: 1 if the type is FP64); HEC_SQ_NAME is
+// the selector.  Compiled once per
 // combination.
 #include "sysq.h"
 

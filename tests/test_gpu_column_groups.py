@@ -39,6 +39,19 @@ def test_parts_that_end_with_the_systems_take_what_even_parts_take():
     assert torch.equal(out[0], out[1])
 
 
+def share_parts(pl, pu):
+    """Whether both triangles run in one launch: parts of the same rows, one ELL
+    width, no CSR tail."""
+    st, own = [], []
+    for p in (pl, pu):
+        st.append(H.tri_plan_stats(p))
+        x, o = H.tri_plan_layout(p)
+        own.append(np.empty_like(o))
+        own[-1][x] = o
+    return (all(s["dataflow"] and s["nnz_tail"] == 0 for s in st) and np.array_equal(*own)
+            and st[0]["ell_width"] == st[1]["ell_width"] and st[0]["num_groups"] == st[1]["num_groups"])
+
+
 @pytest.mark.parametrize("dt", ["f64", "f32"])
 @pytest.mark.parametrize("shape,counts", [((32, 32, 32), (2, 3, 5, 16)), ((64, 64, 1), (4, 5, 7, 31)), ((200, 200, 1), (3, 6)),
                                           ((64, 64, 64), (2, 4)), ((700, 700, 1), (2, 5))])
@@ -50,7 +63,7 @@ def test_groups_side_by_side(shape, counts, dt):
     f = H.ilu_setup(A, "ilu0", factor_dtype=dt)
     pl, pu = H.ilu_plans(f)
     st = H.tri_plan_stats(pl)
-    assert st["dataflow"] and st["num_groups"] > 1 and st["nexport"] > 0
+    assert st["dataflow"] and st["num_groups"] > 1 and st["nexport"] > 0 and share_parts(pl, pu)
     for nrhs in counts + (1,):
         r = torch.from_numpy(np.random.default_rng(nrhs).standard_normal((A.n, nrhs))).cuda()
         want = torch.empty_like(r)
