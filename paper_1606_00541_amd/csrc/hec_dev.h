@@ -84,7 +84,7 @@ constexpr unsigned int kSentinel32 = 0x7FA0BEEFu;
 struct TriArgs {
     int32_t n, w, ld, R;
     int32_t imp_waves;           // dataflow kernel: wavefronts that fetch imports
-    int32_t ldr, k0;             // right-hand sides of a vector's row, the first of this launch (R: of this launch)
+    int32_t ldr, k0;             // right-hand sides of a vector's row, the first of this launch (R: of a workgroup)
     int32_t cgroups;             // system queue: groups of R columns a system's columns are cut into
     int32_t cshift;              // system queue: log2 of the threads that share an item's row, each with its columns
     int32_t sq_fars;             // system queue: values beyond the ring a packed row names (0, 2 or 4)

@@ -33,7 +33,7 @@ namespace hec {
 // that they were stored before an earlier barrier by then.
 // Measured (both triangles, FP32 values, before: one item per system, rows
 // gathered slot by slot): 64 overlapping subdomains of a 128^3 grid, 16
-// right-hand sides 1985 -> 1192 us (they ran on the barrier-free kernel; on
+// right-hand sides 1985 -> 1140 us (they ran on the barrier-free kernel; on
 // this queue without column groups 10.9 ms); 256 ILU(1) systems, 8 right-hand
 // sides 2769 -> 1215 us; in FP64 with 1 / 4 / 5 right-hand sides 7850 -> 1035
 // (items of one column), 2750 -> 1070 and 18240 -> 1310 us.  Column groups
